@@ -82,19 +82,27 @@ rn_status check_queries(const rn_graph *g, const rn_query *q, int32_t nq, int32_
     return RN_OK;
 }
 
-// First on-chip table of a theta-join when the caller set none: the handle's
-// size, raised to hold 1.3x the expected ball (a planar road graph holds
-// about 2 (theta / mean arc weight)^2 vertices within theta; a table is
-// filled to 3/4).  Larger balls would overflow the small table and re-run.
-int first_table(const rn_graph *g, int32_t graph, uint32_t theta) {
-    if (!g->hash_auto) return g->hash_log2;
-    const double r = static_cast<double>(theta) / std::max(1.0, g->wmean[graph]);
-    const double need = 1.3 * 2.0 * r * r / 0.75;
-    int hb = g->hash_log2;
-    while (hb < kMaxHB && static_cast<double>(1u << hb) < need) ++hb;
+// First on-chip table of a query when the caller set none: for a theta-join the
+// smallest whose fill limit (3/4) holds the expected ball (about
+// 2 (theta / mean arc weight)^2 vertices on a planar road graph) with a margin of
+// 1.3; balls of less than 2^11 slots vary more and take 1.8.  (Over quads only:
+// the window search keeps 2^11 as its smallest.  32 768 searches of 66 vertices:
+// 153 us with 2^8 slots, 384 with 2^11.)  A larger ball overflows the table and
+// is searched again.
+int first_table(const rn_graph *g, const rn_query &x) {
+    if (x.k == 0 && !g->hash_auto) return g->hash_log2;
+    const bool quads = g->quads && (x.delta == RN_DELTA_DEFAULT ? g->delta : x.delta) == 0;
+    const double r = static_cast<double>(x.theta) / std::max(1.0, g->wmean[x.graph]);
+    auto fits = [&](int hb, double ball) { return static_cast<double>(1u << hb) >= ball / 0.75; };
+    int hb = kMinHB;
+    if (x.k > 0) return hb;
+    if (quads)
+        while (hb < 11 && !fits(hb, 1.8 * 2.0 * r * r)) ++hb;
+    else
+        hb = 11;
+    while (hb < kMaxHB && hb >= 11 && !fits(hb, 1.3 * 2.0 * r * r)) ++hb;
     return hb;
 }
-
 // Queries whose searches are sure to outgrow the largest on-chip table go to
 // the global tier from the start instead of failing through every tier: a
 // theta-join whose expected ball (as first_table estimates it, capped at the
@@ -151,10 +159,36 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p)
     for (int32_t i = 0; i < nq; ++i) {
         const rn_query &x = q[i];
         hb[i] = x.hash_log2 ? x.hash_log2
-                            : (sure_global(g, x) ? kGlobalHB : (x.k ? kMinHB : first_table(g, x.graph, x.theta)));
+                            : (sure_global(g, x) ? kGlobalHB : first_table(g, x));
         p.any_kcp |= x.k > 0;
         dmax = std::max(dmax, x.theta);
         p.total_R += static_cast<uint64_t>(std::max(x.nR, 0));
+    }
+    // one-wave tables chosen here: where the searches of two sizes fit on the
+    // device together with the larger table, the smaller size gains nothing, and
+    // one launch takes both (sources that fit, by table size: measured residency
+    // per CU times 256)
+    for (int kcp = 0; kcp < 2 && nq > 1; ++kcp) {
+        static const uint64_t fit[4] = {8192, 8192, 6144, 4096};   // 2^8 .. 2^11
+        uint64_t srcs[4] = {0, 0, 0, 0};
+        auto small = [&](int32_t i) {
+            return (q[i].k > 0) == (kcp != 0) && q[i].hash_log2 == 0 && hb[i] >= kMinHB && hb[i] <= kRetryHB1 &&
+                   (q[i].k > 0 || g->hash_auto);
+        };
+        for (int32_t i = 0; i < nq; ++i)
+            if (small(i)) srcs[hb[i] - kMinHB] += static_cast<uint64_t>(g->can_swap ? std::min(q[i].nR, q[i].nS) : q[i].nR);
+        int to[4] = {0, 1, 2, 3};
+        int top = 3;
+        for (int t = 2; t >= 0; --t) {
+            if (srcs[top] == 0 || srcs[top] + srcs[t] > fit[top]) {
+                top = t;
+                continue;
+            }
+            srcs[top] += srcs[t];
+            to[t] = top;
+        }
+        for (int32_t i = 0; i < nq; ++i)
+            if (small(i)) hb[i] = kMinHB + to[hb[i] - kMinHB];
     }
     // staging order: grouped by first table size and kind, query order within a group
     for (int32_t i = 0; i < nq; ++i) p.perm[i] = static_cast<uint32_t>(i);
@@ -181,6 +215,7 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p)
         d.nS = swap ? x.nR : x.nS;
         d.orient = swap ? (kOrientSwap | g->rev_rpo) : 0u;
         d.voff = g->voff[x.graph];
+        d.quads = g->quads ? g->qbase[x.graph + (swap && g->rev_rpo ? g->ngraphs : 0)] : 0u;
         d.V = V;
         d.theta = x.theta;
         d.k = static_cast<uint32_t>(x.k);
@@ -199,27 +234,31 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p)
         if (sw >= 0xFFFFFFFFull || rw >= 0xFFFFFFFFull) return fail(RN_ERR_ARG, "too many vertices in one call");
         if (p.groups.empty() || p.groups.back().hb != hb[i] ||
             (hb[i] != kGlobalHB && p.groups.back().kcp != (x.k > 0)))
-            p.groups.push_back(Group{hb[i], x.k > 0, true, s, s + 1, 0});
+            p.groups.push_back(Group{hb[i], x.k > 0, true, true, true, s, s + 1, 0});
         Group &gr = p.groups.back();
         gr.kcp = gr.kcp || x.k > 0;
         gr.end = s + 1;
+        gr.ring = gr.ring && d.delta == 0;
+        gr.sized = gr.sized && x.k == 0 && x.hash_log2 == 0 && g->hash_auto;
+        p.all_ring = p.all_ring && d.delta == 0;
         gr.sources += static_cast<uint64_t>(d.nR);
         // compact tables: local ids below 2^24, and (theta-joins) every
         // distance within theta fits the compact word; a k-closest-pairs
         // search whose bound is larger moves on if it meets such a distance
         // (the compact 2^11 search's lists hold 64 entries: with buckets, delta
         // > 0, too few for its pending sets, so such groups keep wide tables)
-        gr.compact = gr.compact && hb[i] >= kCompactMinHB && hb[i] <= kMaxHB && g->Vmax < kCompactVertices &&
+        const bool quads = g->quads && d.delta == 0 && x.k == 0;
+        gr.compact = gr.compact && (quads || hb[i] >= kCompactMinHB) && hb[i] <= kMaxHB && g->Vmax < kCompactVertices &&
                      (hb[i] != kCompactSmallRingHB || d.delta == 0) &&
-                     g->A * (g->rev_rpo ? 2 : 1) < static_cast<int64_t>(kCompactArcs) &&
-                     (x.k > 0 || x.theta <= compact_max_dist(hb[i]));
+                     (quads || g->A * (g->rev_rpo ? 2 : 1) < static_cast<int64_t>(kCompactArcs)) &&
+                     ((x.k > 0 && hb[i] >= kCompactMinHB) || x.theta <= compact_max_dist(hb[i]));
     }
     p.rbase[nq] = static_cast<uint32_t>(rw);
     p.total_elems = p.ebase[nq];
     p.sbits_words = static_cast<uint32_t>(sw);
     p.rbits_words = static_cast<uint32_t>(rw);
     for (const Group &gr : p.groups) {
-        p.need_list0 |= gr.hb < kRetryHB1;
+        p.need_list0 |= gr.hb < kRetryHB1 && !gr.sized;
         p.need_list1 |= gr.hb < kMaxHB;
         p.any_global |= gr.hb == kGlobalHB;
     }
@@ -441,10 +480,13 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
     a.rec_cap = b.rec_cap;
     a.bins = p.nbins ? b.bins : nullptr;
     a.binbase = b.binbase;
+    a.one = p.nq == 1 ? 1 : 0;
     a.count_work = g->count_work ? 1 : 0;
     a.big_deg = g->big_deg ? 1 : 0;
     a.order = g->d_order;
     a.first = g->d_first;
+    a.quads = g->d_quads;
+    a.further = g->d_further;
     if (p.any_kcp) {
         JoinArgs k = a;
         k.src = b.src;
@@ -490,14 +532,14 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
             // (without global-tier slots yet, a global group takes the largest
             // table, whose overflows get the slots and a re-run of the call)
             const int hbt = std::min(gr.hb, kMaxHB);
-            const int li = retry_list_after(hbt);
+            const int li = gr.sized && hbt < kMaxHB ? 1 : retry_list_after(hbt);
             t.ovf = b.list[li];
             t.ovfq = b.listq[li];
             t.novf = &b.ctl->nlist[li];
             t.first_tier = 1;
             t.tier = 0;
-            RN_HIP(launch_join(t, hbt, gr.kcp, gr.compact, static_cast<uint32_t>(gr.sources), !shared,
-                               on_chip_stream(gi)),
+            RN_HIP(launch_join(t, hbt, gr.kcp, gr.compact, g->quads && gr.ring && !gr.kcp, static_cast<uint32_t>(gr.sources),
+                               !shared, on_chip_stream(gi)),
                    "launching the relaxation");
         }
     }
@@ -524,7 +566,7 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
         // the re-run tiers take wide tables: they must hold any search the
         // first tiers sent on, whatever its distances (a compact 2^14 re-run
         // could only send those on to the global tier)
-        RN_HIP(launch_join(t, li == 0 ? kRetryHB1 : kMaxHB, true, false, maxs, !shared, s),
+        RN_HIP(launch_join(t, li == 0 ? kRetryHB1 : kMaxHB, true, false, g->quads && p.all_ring && !p.any_kcp, maxs, !shared, s),
                "launching the relaxation");
     }
     if (gside) RN_HIP(hipStreamWaitEvent(s, ws.join[0], 0), "joining streams");   // the early global launch
@@ -733,6 +775,53 @@ int32_t graph_of(const rn_graph *g, int32_t x) {
     return static_cast<int32_t>(std::upper_bound(g->voff.begin(), g->voff.end(), x) - g->voff.begin()) - 1;
 }
 
+// Whether the graphs keep arc quads (rrow: row pointers of the reversed arcs),
+// and where each graph's start: the vertices' first quads, then the further
+// quads of its vertices of more than 4 arcs (a renumbering of the vertices
+// leaves their number as it is).
+void choose_quads(rn_graph *g, const std::vector<int32_t> &rrow) {
+    const int dirs = g->rev_rpo ? 2 : 1;
+    g->qbase.assign(static_cast<size_t>(dirs) * g->ngraphs + 1, 0u);
+    g->quads = false;
+    int64_t n = 0;
+    for (int dir = 0; dir < dirs; ++dir) {
+        const std::vector<int32_t> &rp = dir ? rrow : g->row_ptr;
+        for (int32_t i = 0; i < g->ngraphs; ++i) {
+            const int64_t first = n;
+            g->qbase[static_cast<size_t>(dir) * g->ngraphs + i] = static_cast<uint32_t>(n);
+            for (int32_t x = g->voff[i]; x < g->voff[i + 1]; ++x) {
+                const int32_t deg = rp[x + 1] - rp[x];
+                if (deg > kQuadMaxDeg) return;
+                n += row_quads(deg);
+            }
+            if (n - first > kQuadMaxIds) return;
+        }
+    }
+    g->qbase[static_cast<size_t>(dirs) * g->ngraphs] = static_cast<uint32_t>(n);
+    g->quads = n < 0x7FFFFFFFLL && 8 * n <= 3 * g->A * dirs;
+}
+
+// Lay out the device copy's arcs as quads.
+rn_status upload_quads(rn_graph *g) {
+    const size_t dirs = g->rev_rpo ? 2 : 1;
+    const uint32_t nquads = g->qbase.back();
+    hipError_t e = hipSuccess;
+    const size_t ngr = static_cast<size_t>(g->ngraphs), nv = g->voff.size(), nb = dirs * ngr;
+    if ((!g->d_quads && (e = dev_alloc(&g->d_quads, 4 * static_cast<size_t>(nquads))) != hipSuccess) ||
+        (!g->d_further && (e = dev_alloc(&g->d_further, static_cast<size_t>(nquads))) != hipSuccess) ||
+        (!g->d_qgraph && (e = dev_alloc(&g->d_qgraph, nv + 2 * nb)) != hipSuccess) ||
+        (e = hipMemcpy(g->d_qgraph, g->voff.data(), nv * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess ||
+        (e = hipMemcpy(g->d_qgraph + nv, g->qbase.data(), nb * sizeof(uint32_t), hipMemcpyHostToDevice)) != hipSuccess ||
+        (e = launch_build_quads(g->d_row_ptr, g->d_arcs, g->d_further, g->d_qgraph,
+                                reinterpret_cast<const uint32_t *>(g->d_qgraph + nv),
+                                reinterpret_cast<uint32_t *>(g->d_qgraph + nv + nb), static_cast<uint32_t>(ngr),
+                                static_cast<uint32_t>(dirs), static_cast<uint32_t>(g->V), nquads, g->d_quads, nullptr)) !=
+            hipSuccess ||
+        (e = hipStreamSynchronize(nullptr)) != hipSuccess)
+        return hip_fail(e, "laying out the graph's arc quads");
+    return RN_OK;
+}
+
 // Build the device copy of the resident graphs from the host CSR (caller
 // numbering), with global vertex x renumbered perm[x] (perm null: as is), and
 // copy it into g->d_row_ptr / g->d_arcs (allocated on the first call; the
@@ -831,7 +920,7 @@ rn_status upload_csr(rn_graph *g, const int32_t *perm) {
         (!arcs.empty() &&
          (e = hipMemcpy(g->d_arcs, arcs.data(), arcs.size() * sizeof(ArcRec), hipMemcpyHostToDevice)) != hipSuccess))
         return hip_fail(e, "uploading the graph");
-    return RN_OK;
+    return g->quads ? upload_quads(g) : RN_OK;
 }
 
 }  // namespace
@@ -936,6 +1025,12 @@ rn_status rn_graph_load_many(int32_t n, const int32_t *V, const int64_t *A, cons
     const bool keep_rev = !symmetric && 2 * totA < 0x7FFFFFFFLL;
     g->can_swap = symmetric || keep_rev;
     g->rev_rpo = keep_rev ? static_cast<uint32_t>(totV + 1) : 0u;
+    try {
+        choose_quads(g, rrow);
+    } catch (...) {
+        delete g;
+        return fail(RN_ERR_NOMEM, "laying out the graph's arc quads");
+    }
     rcol.clear();
     rw.clear();
     // the resident copy, in the caller's numbering until rn_partition, and the
@@ -1100,6 +1195,9 @@ void rn_graph_free(rn_graph *g) {
     g->ws.release();
     dev_free(g->d_row_ptr);
     dev_free(g->d_arcs);
+    dev_free(g->d_quads);
+    dev_free(g->d_further);
+    dev_free(g->d_qgraph);
     dev_free(g->d_rank);
     dev_free(g->d_order);
     dev_free(g->d_first);

@@ -129,6 +129,9 @@ struct Group {
     int hb;
     bool kcp;               // some query of the group asks for k closest pairs
     bool compact;           // its launch uses compact on-chip tables
+    bool ring;              // no query of the group has buckets (delta = 0)
+    bool sized;             // theta-joins whose table was chosen for their balls: the few searches
+                            // that outgrow it go on to the largest table at once
     int32_t first;          // staging positions [first, end)
     int32_t end;
     uint64_t sources;       // sum of nR
@@ -145,6 +148,7 @@ struct Prepared {
     bool any_kcp = false;
     bool need_list0 = false;
     bool need_list1 = false;
+    bool all_ring = true;           // no query of the call has buckets (delta = 0)
     bool any_global = false;        // a first-tier group runs in the global tier
     uint32_t qb = 0, vb = 1, max_passes = 1;
     uint64_t total_R = 0;
@@ -212,6 +216,12 @@ struct rn_graph {
 
     int32_t *d_row_ptr = nullptr;
     rn::ArcRec *d_arcs = nullptr;
+    // Arc quads (graphs whose degrees suit them):
+    bool quads = false;
+    std::vector<uint32_t> qbase;    // first quad of each graph, then of each reversed graph, then their number
+    uint2 *d_quads = nullptr;
+    uint32_t *d_further = nullptr;  // per quad: the next quad of its vertex (of more than 4 arcs)
+    int32_t *d_qgraph = nullptr;    // voff, then qbase, then counters of the build
     // The device copy of the graphs is numbered in partition-leaf order once
     // rn_partition has run (identity until then); the two maps, both
     // allocated at load:

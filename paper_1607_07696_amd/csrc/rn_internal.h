@@ -71,7 +71,8 @@ struct QueryDesc {
     uint32_t wmin;              // lightest arc weight of the query's graph
     uint32_t slack;             // delta = 0: a step of the on-chip search puts back the vertices
                                 // more than this above its least distance (kInf: none)
-    uint32_t pad[2];
+    uint32_t quads;             // first arc quad of the (reversed) graph searched
+    uint32_t pad;
 };
 static_assert(sizeof(QueryDesc) == 80, "QueryDesc is 80 bytes");
 constexpr uint32_t kOrientSwap = 1u << 31;
@@ -155,9 +156,12 @@ struct JoinArgs {
     const uint32_t *binbase;    //   first bin of each query
     int32_t first_tier;         // 1: count re-queued searches in ctl->nretry
     int32_t tier;               // 0 first table, 1 and 2 the re-run tables, 3 the global tier
+    int32_t one;                // 1: the call has one query (its records are counted in ctl only)
     int32_t count_work;         // 1: accumulate ctl->arcs / ctl->settled
     int32_t big_deg;            // 1: some vertex has 2^16 or more arcs (searches reaching one move on)
     const int32_t *order;       // global vertex of the device copy -> local id in the caller's numbering
+    const uint2 *quads;         // arc quads (null: the graphs keep none)
+    const uint32_t *further;    //   per quad: the next quad of its vertex (local), if it has one
     const uint32_t *first;      // bit a: arc a is the first lightest of the arcs from its tail to its
                                 //   target (parallel arcs give one pair, at that arc's weight)
     uint32_t *work;             // global tier: counter of sources claimed past the grid (zero at the start)
@@ -238,8 +242,23 @@ constexpr uint32_t compact_max_dist(int hash_log2) {
 constexpr int kCompactMinHB = 10;
 // The compact table size whose search takes a 128-entry ring (lists of 64).
 constexpr int kCompactSmallRingHB = 11;
-hipError_t launch_join(const JoinArgs &a, int hash_log2, bool generic, bool compact, uint32_t max_sources,
+// quads: search over the arc quads (a.quads set, every query of the launch
+// with delta = 0).
+hipError_t launch_join(const JoinArgs &a, int hash_log2, bool generic, bool compact, bool quads, uint32_t max_sources,
                        bool persistent, hipStream_t s);
+// Arc quads: four {target, weight} records of 8 bytes per vertex (then those of
+// the reversed arcs), padded with arcs of infinite weight; the further quads of
+// vertices of more arcs follow each graph's.  Kept for graphs whose vertices
+// have at most kQuadMaxDeg arcs each way (a target's flags count up to three
+// further quads) and whose quads hold at most half as many records again as
+// there are arcs: beyond that the padding costs a search more than the arc
+// windows do.
+constexpr int32_t kQuadMaxDeg = 16;
+constexpr int32_t kQuadMaxIds = 1 << 27;   // per graph: quad numbers below the flags
+__host__ __device__ inline int32_t row_quads(int32_t deg) { return deg <= 4 ? 1 : (deg + 3) / 4; }
+hipError_t launch_build_quads(const int32_t *row_ptr, const ArcRec *arcs, uint32_t *further, const int32_t *voff,
+                              const uint32_t *qbase, uint32_t *next, uint32_t ngr, uint32_t dirs, uint32_t V,
+                              uint32_t nquads, uint2 *quads, hipStream_t s);
 int join_tier_supported(int hash_log2);
 // The global-memory tier: one block per source, nslots slots of
 // global_slot_words(Vmax) words in the layout above.

@@ -34,6 +34,9 @@ namespace {
 
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;  // empty table key (vertex ids are below 2^31 - 1)
 constexpr uint32_t kWin = 256;            // frontier arcs expanded per window (4 per lane)
+constexpr uint32_t kQuadId = (1u << 27) - 1u;   // a quad's number below the flags
+constexpr uint32_t kQuadMore = 3u << 27;        // further quads after it
+constexpr uint32_t kQuadFurther = 1u << 29;     // it is a further quad
 
 // ------------------------------------------------------------------ wave helpers
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63u; }
@@ -162,7 +165,6 @@ struct Tier {
     // outgrew it); a search that does goes on to the next tier.  Calls with delta > 0 take
     // the wide 2^11 table instead, whose lists of 128 entries their buckets need
     static constexpr int PC = (CT && HB == kCompactSmallRingHB) ? 64 : (HB <= 12 ? 128 : (HB == 13 ? 256 : 512));
-    static constexpr int U = (H / 64) < 8 ? (H / 64) : 8;   // table rows scanned per batch
     // waves per search: a large table leaves room for few searches per CU, so
     // several waves share each one (a block): two for 2^12, four for 2^13,
     // eight for a wide 2^14 table (one search per CU) and three for a compact
@@ -243,44 +245,48 @@ struct Compact {
     static_assert(((((MAXD << 1) | 1u) << SH) | IDM) < kNoKey, "a compact word never equals kNoKey");
 };
 
-__device__ __forceinline__ uint32_t hash24(uint32_t y) { return (y * kHash24) & 0xFFFFFFu; }
+// (only the low 24 bits of y count, so the full-rate 24-bit multiply gives the product)
+__device__ __forceinline__ uint32_t mul24(uint32_t y, uint32_t k) {
+    uint32_t z;
+    asm("v_mul_u32_u24_e32 %0, %1, %2" : "=v"(z) : "s"(k), "v"(y));   // (the compiler takes the quarter-rate product)
+    return z;
+}
+__device__ __forceinline__ uint32_t hash24(uint32_t y) { return mul24(y, kHash24) & 0xFFFFFFu; }
 
+// The distance table of one search.
 template <int HB, bool CT>
-struct SearchLds;
+struct Table;
 
 template <int HB>
-struct SearchLds<HB, false> {
-    static constexpr int H = Tier<HB, false>::H;
-    static constexpr int PC = Tier<HB, false>::PC;
+struct Table<HB, false> {
+    static constexpr uint32_t H = 1u << HB;
     uint32_t key[H];            // vertex id (global), or kEmpty
     uint32_t dw[H];             // distance word, kWordNone when empty
-    uint2 lst[2][PC];           // two vertex lists of {slot | (arc count << 16), first arc} (with
-                                //   delta = 0, one ring of 2 PC entries over the same words)
-    uint2 win[Tier<HB, false>::W * Tier<HB, false>::NW];   // per wave: window arc -> {arc index,
-                                //   distance of the arc's tail}; outside a window step, entry
-                                //   lane is the write sink of lanes with nothing to store
-                                //   (distinct addresses, no serialised writes) and the staging
-                                //   area of emitted pairs
-    __device__ uint2 *wwin() {
-        if constexpr (Tier<HB, false>::NW == 1) return win;
-        else return win + wave_in_block() * Tier<HB, false>::W;
-    }
-    __device__ uint2 *sink() { return wwin() + lane_id(); }
 };
 
 template <int HB>
-struct SearchLds<HB, true> {
-    static constexpr int H = Tier<HB, true>::H;
-    static constexpr int PC = Tier<HB, true>::PC;
+struct Table<HB, true> {
+    static constexpr uint32_t H = 1u << HB;
     uint32_t t[H];              // compact word, kWordNone when empty
-    uint2 lst[2][PC];           // as in the wide table
-    using WinEntry = std::conditional_t<Tier<HB, true>::LW, uint32_t, uint2>;
-    WinEntry win[Tier<HB, true>::W * Tier<HB, true>::NW];   // per wave: as in the wide table, or
-                                //   (Tier::LW) window arc -> (lane holding its tail << 26) | arc
-                                //   index (below 2^26), the tail's distance coming over the lanes
+};
+
+// A search over arc windows (graphs whose degrees vary too much for quads, and
+// queries with buckets): the table, the vertex lists, a window per wave.
+template <int HB, bool CT>
+struct SearchLds : Table<HB, CT> {
+    static constexpr int PC = Tier<HB, CT>::PC;
+    using WinEntry = std::conditional_t<Tier<HB, CT>::LW, uint32_t, uint2>;
+    uint2 lst[2][PC];           // two vertex lists of {slot | (arc count << 16), first arc} (with
+                                //   delta = 0, one ring of 2 PC entries over the same words)
+    WinEntry win[Tier<HB, CT>::W * Tier<HB, CT>::NW];   // per wave: window arc -> {arc index,
+                                //   distance of the arc's tail}, or (Tier::LW) (lane holding its
+                                //   tail << 26) | arc index (below 2^26), the tail's distance coming
+                                //   over the lanes; outside a window step, entry lane is the write
+                                //   sink of lanes with nothing to store (distinct addresses, no
+                                //   serialised writes)
     __device__ WinEntry *wwin() {
-        if constexpr (Tier<HB, true>::NW == 1) return win;
-        else return win + wave_in_block() * Tier<HB, true>::W;
+        if constexpr (Tier<HB, CT>::NW == 1) return win;
+        else return win + wave_in_block() * Tier<HB, CT>::W;
     }
     __device__ uint2 *sink() { return reinterpret_cast<uint2 *>(wwin()) + lane_id(); }
 };
@@ -288,21 +294,21 @@ struct SearchLds<HB, true> {
 // ---- table access shared by both layouts
 // Distance held in slot s.
 template <int HB, bool CT>
-__device__ __forceinline__ uint32_t slot_dist(SearchLds<HB, CT> &L, uint32_t s) {
+__device__ __forceinline__ uint32_t slot_dist(Table<HB, CT> &L, uint32_t s) {
     if constexpr (CT) return L.t[s] >> (Compact<HB>::SH + 1u);
     else return L.dw[s] >> 1;
 }
 
 // Clear the pending bit of slot s (lanes with !valid issue a no-op on their own slot).
 template <int HB, bool CT>
-__device__ __forceinline__ void clear_pending(SearchLds<HB, CT> &L, uint32_t s, bool valid) {
+__device__ __forceinline__ void clear_pending(Table<HB, CT> &L, uint32_t s, bool valid) {
     if constexpr (CT) atomicAnd(&L.t[valid ? s : lane_id()], valid ? ~Compact<HB>::PEND : 0xFFFFFFFFu);
     else atomicAnd(&L.dw[valid ? s : lane_id()], valid ? ~1u : 0xFFFFFFFFu);
 }
 
 // Set slot s pending again; returns whether it already was.
 template <int HB, bool CT>
-__device__ __forceinline__ bool mark_pending(SearchLds<HB, CT> &L, uint32_t s, bool valid) {
+__device__ __forceinline__ bool mark_pending(Table<HB, CT> &L, uint32_t s, bool valid) {
     if constexpr (CT)
         return (atomicOr(&L.t[valid ? s : lane_id()], valid ? Compact<HB>::PEND : 0u) & Compact<HB>::PEND) != 0u;
     else
@@ -311,7 +317,7 @@ __device__ __forceinline__ bool mark_pending(SearchLds<HB, CT> &L, uint32_t s, b
 
 // Empty slot s.
 template <int HB, bool CT>
-__device__ __forceinline__ void clear_slot(SearchLds<HB, CT> &L, uint32_t s) {
+__device__ __forceinline__ void clear_slot(Table<HB, CT> &L, uint32_t s) {
     if constexpr (CT) {
         lds_store(&L.t[s], kWordNone);
     } else {
@@ -322,13 +328,13 @@ __device__ __forceinline__ void clear_slot(SearchLds<HB, CT> &L, uint32_t s) {
 
 // Vertex (global id) and distance in slot s; false if the slot is empty.
 template <int HB, bool CT>
-__device__ __forceinline__ bool read_slot(SearchLds<HB, CT> &L, uint32_t s, int32_t voff, uint32_t &y,
+__device__ __forceinline__ bool read_slot(Table<HB, CT> &L, uint32_t s, int32_t voff, uint32_t &y,
                                           uint32_t &d) {
     if constexpr (CT) {
         using K = Compact<HB>;
         const uint32_t w = lds_load(&L.t[s]);
-        const uint32_t home = (s - ((w >> K::IDB) & K::MAXP)) & (Tier<HB, true>::H - 1u);
-        y = ((((home << K::IDB) | (w & K::REM)) * kHash24Inv) & 0xFFFFFFu) + static_cast<uint32_t>(voff);
+        const uint32_t home = (s - ((w >> K::IDB) & K::MAXP)) & (Table<HB, true>::H - 1u);
+        y = (mul24(((home << K::IDB) | (w & K::REM)), kHash24Inv) & 0xFFFFFFu) + static_cast<uint32_t>(voff);
         d = w >> (K::SH + 1u);
         return w != kWordNone;
     } else {
@@ -341,7 +347,7 @@ __device__ __forceinline__ bool read_slot(SearchLds<HB, CT> &L, uint32_t s, int3
 // Put source u (global id) at distance 0, pending, into the empty table;
 // returns its slot.
 template <int HB, bool CT>
-__device__ __forceinline__ uint32_t put_source(SearchLds<HB, CT> &L, int32_t u, int32_t voff) {
+__device__ __forceinline__ uint32_t put_source(Table<HB, CT> &L, int32_t u, int32_t voff) {
     if constexpr (CT) {
         using K = Compact<HB>;
         const uint32_t z = hash24(static_cast<uint32_t>(u - voff));
@@ -384,28 +390,47 @@ struct SrcCtx {
     uint32_t slack;                 // delta = 0: how far above a step's least distance a vertex waits
     bool swapped;                   // the search runs from S: emitted pairs are reversed
     bool big_deg;                   // some vertex of the graph has 2^16 or more arcs
+    const uint2 *quads;             // the arc quads searched, by local id
+    const uint32_t *further;        // the next quad of a quad's vertex, by local number
     const uint32_t *sbits;          // the query's S bitmap (local ids)
     uint32_t *hist;                 // k > 0: the query's histogram region (else null)
     QueryState *qs;                 // the query's state
+    const unsigned long long *npairs;   // records the query has emitted
 };
 
-__device__ __forceinline__ SrcCtx load_ctx(const JoinArgs &a, uint32_t q) {
+__device__ __forceinline__ uint32_t uni(uint32_t v) {
+    return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
+}
+
+// The context of query q.  U: q is wave-uniform, and so is all that is read (in
+// scalar registers, which keeps a search's control flow scalar).
+template <bool U = false>
+__device__ __forceinline__ SrcCtx load_ctx(const JoinArgs &a, uint32_t q0) {
+    auto same = [](uint32_t v) {
+        if constexpr (U) return uni(v);
+        else return v;
+    };
+    const uint32_t q = same(q0);
     const QueryDesc &d = a.qd[q];
     SrcCtx c;
-    c.theta = d.theta;
-    c.k = d.k;
-    c.delta = d.delta;
-    c.voff = d.voff;
+    c.theta = same(d.theta);
+    c.k = same(d.k);
+    c.delta = same(d.delta);
+    c.voff = static_cast<int32_t>(same(static_cast<uint32_t>(d.voff)));
     c.q = q;
     c.tier = static_cast<uint32_t>(a.tier);
-    c.rpo = d.orient & ~kOrientSwap;
-    c.wmin = d.wmin;
-    c.slack = d.slack;
-    c.swapped = (d.orient & kOrientSwap) != 0;
+    const uint32_t orient = same(d.orient), quads = same(d.quads);
+    c.rpo = orient & ~kOrientSwap;
+    c.wmin = same(d.wmin);
+    c.slack = same(d.slack);
+    c.swapped = (orient & kOrientSwap) != 0;
     c.big_deg = a.big_deg != 0;
-    c.sbits = a.sbits + d.sbits;
-    c.hist = d.k ? a.hists + d.hist : nullptr;
+    c.quads = a.quads + 4ull * quads;
+    c.further = a.further + quads;
+    c.sbits = a.sbits + same(d.sbits);
+    c.hist = c.k ? a.hists + same(d.hist) : nullptr;
     c.qs = a.qs + q;
+    c.npairs = a.one ? &a.ctl->npairs : &a.qs[q].npairs;
     return c;
 }
 
@@ -458,23 +483,23 @@ __device__ __forceinline__ void probe_phase(const SrcCtx &c, uint32_t &pnew, boo
     if (lane_id() == 0) atomicMin(&c.qs->bound, b);
 }
 
-// Relax NJ window arcs per lane (slot j holds window arc j*64 + lane) and
-// append targets that became pending to list P.  Two LDS steps, each issued
-// for all NJ slots before any result is used: claim-or-find the target's slot
-// (compare-and-swap on an empty home slot doubles as the first probe), then
-// the packed atomicMin.  Idle lanes issue no-op atomics instead of branching.
-// Called by all 64 lanes; st.ovf is wave-uniform afterwards.
+// Relax NJ arcs per lane (targets y[j], tentative distances nd[j]; kInf: none)
+// into the table.  Two LDS steps, each issued for all NJ before any result is
+// used: claim-or-find the target's slot (compare-and-swap on an empty home
+// slot doubles as the first probe), then the packed atomicMin.  Idle lanes
+// issue no-op atomics instead of branching.  Returns the slots h, and per arc
+// whether the vertex's distance improved (imp), whether its slot was empty
+// before (fresh: a new table entry), and whether this lane appends the vertex
+// (app: it was idle or new, and improved); the result is whether some distance
+// or probe sequence does not fit the table.  Called by all 64 lanes.
 template <int HB, bool CT, int NJ>
-__device__ __forceinline__ void relax_window(SearchLds<HB, CT> &L, WaveState &st, const SrcCtx &c,
-                                             const ArcRec *r, const uint32_t *nd, uint32_t bound) {
-    constexpr uint32_t H = Tier<HB, CT>::H;
+__device__ __forceinline__ bool relax_table(Table<HB, CT> &L, uint32_t voff, const uint32_t *y, const uint32_t *nd,
+                                            uint32_t bound, uint32_t *h, bool *fresh, bool *app, bool *imp) {
+    constexpr uint32_t H = Table<HB, CT>::H;
     // slot states: 0 idle, 1 slot holds y, 2 slot claimed for y, 3 keep probing;
     // after the min, flags: the distance improved (imp), and the vertex was
     // idle or new, so this lane appends it (app)
-    uint32_t h[NJ], stt[NJ], old[NJ];
-    bool fresh[NJ];   // the slot was empty before this window: a new table entry
-    bool app[NJ];     // this lane appends the vertex (it was idle or new, and improved)
-    bool imp[NJ];     // the vertex's distance improved
+    uint32_t stt[NJ], old[NJ];
     // a distance the table's word cannot hold (possible only when the bound
     // itself is that large) sends the search on to the next tier
     constexpr uint32_t kMaxWord = CT ? Compact<HB>::MAXD : kPackMax;
@@ -494,7 +519,7 @@ __device__ __forceinline__ void relax_window(SearchLds<HB, CT> &L, WaveState &st
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             const bool act = nd[j] <= lim;
-            const uint32_t z = hash24(static_cast<uint32_t>(r[j].y - c.voff));
+            const uint32_t z = hash24(y[j] - voff);
             // idle lanes aim their no-op atomics at distinct slots: a shared address would serialise
             h[j] = act ? z >> K::IDB : lane_id();
             nw[j] = act ? ((((nd[j] << 1) | 1u) << K::SH) | (z & K::REM)) : kWordNone;
@@ -562,17 +587,16 @@ __device__ __forceinline__ void relax_window(SearchLds<HB, CT> &L, WaveState &st
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             // idle lanes aim their no-op atomics at distinct slots: a shared address would serialise
-            h[j] = nd[j] <= lim ? slot_hash<HB>(static_cast<uint32_t>(r[j].y)) : lane_id();
+            h[j] = nd[j] <= lim ? slot_hash<HB>(y[j]) : lane_id();
         }
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-            old[j] = atomicCAS(&L.key[h[j]], nd[j] <= lim ? kEmpty : kNoKey, static_cast<uint32_t>(r[j].y));
+            old[j] = atomicCAS(&L.key[h[j]], nd[j] <= lim ? kEmpty : kNoKey, y[j]);
         __builtin_amdgcn_sched_barrier(0);   // every claim is issued before the first result is used
         bool probe = false;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            const uint32_t y = static_cast<uint32_t>(r[j].y);
-            stt[j] = nd[j] > lim ? 0u : (old[j] == kEmpty ? 2u : (old[j] == y ? 1u : 3u));
+            stt[j] = nd[j] > lim ? 0u : (old[j] == kEmpty ? 2u : (old[j] == y[j] ? 1u : 3u));
             probe |= stt[j] == 3u;
         }
         if (__ballot(probe) != 0) {
@@ -587,13 +611,12 @@ __device__ __forceinline__ void relax_window(SearchLds<HB, CT> &L, WaveState &st
                     const bool act = stt[j] == 3u;
                     h[j] = act ? ((h[j] + 1u) & (H - 1)) : h[j];
                     old[j] = atomicCAS(&L.key[act ? h[j] : lane_id()], act ? kEmpty : kNoKey,
-                                       static_cast<uint32_t>(r[j].y));
+                                       y[j]);
                 }
                 bool more = false;
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
-                    const uint32_t y = static_cast<uint32_t>(r[j].y);
-                    if (stt[j] == 3u) stt[j] = old[j] == kEmpty ? 2u : (old[j] == y ? 1u : 3u);
+                    if (stt[j] == 3u) stt[j] = old[j] == kEmpty ? 2u : (old[j] == y[j] ? 1u : 3u);
                     more |= stt[j] == 3u;
                 }
                 if (__ballot(more) == 0) break;
@@ -617,6 +640,21 @@ __device__ __forceinline__ void relax_window(SearchLds<HB, CT> &L, WaveState &st
             fresh[j] = imp[j] && old[j] == kWordNone;
         }
     }
+    return lost;
+}
+
+// Relax NJ window arcs per lane (slot j holds window arc j*64 + lane) and
+// append targets that became pending to list P.  Called by all 64 lanes;
+// st.ovf is wave-uniform afterwards.
+template <int HB, bool CT, int NJ>
+__device__ __forceinline__ void relax_window(SearchLds<HB, CT> &L, WaveState &st, const SrcCtx &c,
+                                             const ArcRec *r, const uint32_t *nd, uint32_t bound) {
+    constexpr uint32_t H = Tier<HB, CT>::H;
+    uint32_t h[NJ], y[NJ];
+    bool fresh[NJ], app[NJ], imp[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) y[j] = static_cast<uint32_t>(r[j].y);
+    bool lost = relax_table<HB, CT, NJ>(L, static_cast<uint32_t>(c.voff), y, nd, bound, h, fresh, app, imp);
     uint64_t mA[NJ];
     uint32_t nadd = 0, ins = 0;
 #pragma unroll
@@ -726,20 +764,21 @@ __device__ __forceinline__ void window_step(SearchLds<HB, CT> &L, WaveState &st,
 // seen: the count at this wave's last recomputation for the query; the bound
 // is recomputed only once the count has grown by an eighth since then.
 __device__ __forceinline__ void tighten_bound(const SrcCtx &c, unsigned long long &seen) {
-    const unsigned long long n = __hip_atomic_load(&c.qs->npairs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long n = __hip_atomic_load(c.npairs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (n < c.k || n < seen + (seen >> 3) + 1ull) return;
     seen = n;
     const uint32_t b = wave_bound_from_hist(c.hist + kHistEmit, c.k);
     if ((threadIdx.x & 63u) == 0) atomicMin(&c.qs->bound, b);
 }
 
-// Reserve n record slots for query c (one atomic per wave); the base is
-// returned to every lane.
+// Reserve n record slots for query c (one atomic per wave, and one on the
+// query's own count if the call has several queries: thousands of waves add to
+// these words, which serialise); the base is returned to every lane.
 __device__ __forceinline__ unsigned long long reserve_recs(const JoinArgs &a, const SrcCtx &c, uint32_t n) {
     unsigned long long base = 0;
     if (lane_id() == 0) {
         base = atomicAdd(&a.ctl->npairs, static_cast<unsigned long long>(n));
-        atomicAdd(&c.qs->npairs, static_cast<unsigned long long>(n));
+        if (!a.one) atomicAdd(&c.qs->npairs, static_cast<unsigned long long>(n));
     }
     return (static_cast<unsigned long long>(readlane(static_cast<uint32_t>(base >> 32), 0)) << 32) |
            readlane(static_cast<uint32_t>(base), 0);
@@ -754,9 +793,8 @@ static_assert(kMaxQueries <= 0x10000, "query numbers fit the low 16 bits of a re
 __device__ __forceinline__ uint32_t bin_place(uint32_t place) { return min(place, kPlaceNone) << 16; }
 
 // Write this wave's staged pairs ({dist, v} in stg) for source u.
-template <int HB, bool CT>
-__device__ __forceinline__ void flush_pairs(SearchLds<HB, CT> &L, const JoinArgs &a, const SrcCtx &c, int32_t u,
-                                            uint32_t &nst, const uint2 *stg) {
+__device__ __forceinline__ void flush_pairs(const JoinArgs &a, const SrcCtx &c, int32_t u, uint32_t &nst,
+                                            const uint2 *stg) {
     if (nst == 0) return;
     const unsigned long long base = reserve_recs(a, c, nst);
     const uint32_t bin0 = a.bins ? a.binbase[c.q] : 0u;
@@ -777,6 +815,91 @@ __device__ __forceinline__ void flush_pairs(SearchLds<HB, CT> &L, const JoinArgs
     }
     wave_sync();
     nst = 0;
+}
+
+// Table rows (64 slots) the emission scans per batch, so that the S-bitmap
+// words of a batch are loaded together.
+template <int HB>
+constexpr uint32_t table_rows() { return (1 << HB) / 64 < 8 ? (1 << HB) / 64 : 8; }
+
+// The end of a search from u: emit the table entries in S (none when the search
+// outgrew the tier: ovf) and clear the table for the next source.  This wave
+// takes the rows from slot first on, 64 table_rows slots at a time, `step`
+// apart, and stages its pairs in stg (cap >= 64 entries, free once the search
+// has ended).
+template <int HB, bool CT, bool Q>
+__device__ __forceinline__ void emit_and_clear(Table<HB, CT> &L, const JoinArgs &a, const SrcCtx &c, int32_t u,
+                                               uint32_t bound, bool ovf, uint2 *stg, uint32_t cap, uint32_t first,
+                                               uint32_t step, unsigned long long &tseen) {
+    constexpr uint32_t U = table_rows<HB>();
+    const uint32_t lane = lane_id();
+    uint32_t nst = 0, emitted = 0;
+    unsigned long long warcs = 0;
+    uint32_t wsettled = 0;
+    for (uint32_t g0 = first; g0 < Table<HB, CT>::H; g0 += step) {
+        uint32_t k[U], d[U];
+        bool occ[U], sb[U];
+#pragma unroll
+        for (uint32_t j = 0; j < U; ++j) {
+            const uint32_t slot = g0 + j * 64 + lane;
+            occ[j] = read_slot(L, slot, c.voff, k[j], d[j]);
+            if constexpr (Q && !CT) k[j] += static_cast<uint32_t>(c.voff);   // (its keys are local ids)
+            sb[j] = !ovf && occ[j] && in_s(c, k[j]);
+        }
+        if (a.count_work && !ovf) {
+#pragma unroll
+            for (uint32_t j = 0; j < U; ++j)
+                if (occ[j] && d[j] <= bound) {
+                    warcs += static_cast<unsigned long long>(a.row_ptr[c.rpo + k[j] + 1] - a.row_ptr[c.rpo + k[j]]);
+                    wsettled += 1;
+                }
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < U; ++j) clear_slot(L, g0 + j * 64 + lane);
+#pragma unroll
+        for (uint32_t j = 0; j < U; ++j) {
+            const bool m = sb[j] && d[j] <= bound;
+            const uint64_t mM = __ballot(m);
+            if (mM == 0) continue;   // (wave-uniform)
+            if (c.k && m) atomicAdd(&c.hist[kHistEmit + dist_bin(d[j])], 1u);
+            if (nst + popc(mM) > cap) {
+                emitted += nst;
+                wave_sync();
+                flush_pairs(a, c, u, nst, stg);
+            }
+            if (m) stg[nst + mbcnt(mM)] = make_uint2(d[j], k[j]);
+            nst += popc(mM);
+        }
+    }
+    emitted += nst;
+    wave_sync();
+    flush_pairs(a, c, u, nst, stg);
+    if constexpr (Q) {
+        // entries of an idle ring name a slot and a quad that exist: the next
+        // source's graph may have fewer quads than this one
+        for (uint32_t i = lane; i < cap; i += 64) stg[i] = make_uint2(0u, 0u);
+    }
+    if (c.k && emitted != 0) tighten_bound(c, tseen);
+    if (a.count_work && !ovf) {
+        for (int o = 32; o > 0; o >>= 1) {
+            const uint32_t lo = static_cast<uint32_t>(__shfl_xor(static_cast<int>(warcs & 0xFFFFFFFFull), o));
+            const uint32_t hi = static_cast<uint32_t>(__shfl_xor(static_cast<int>(warcs >> 32), o));
+            warcs += (static_cast<unsigned long long>(hi) << 32) | lo;
+            wsettled += static_cast<uint32_t>(__shfl_xor(static_cast<int>(wsettled), o));
+        }
+        if (lane == 0) {
+            atomicAdd(&a.ctl->arcs, warcs);
+            atomicAdd(&a.ctl->settled, static_cast<unsigned long long>(wsettled));
+        }
+    }
+}
+
+// Queue source u for the next tier (one thread).
+__device__ __forceinline__ void queue_next_tier(const JoinArgs &a, const SrcCtx &c, int32_t u) {
+    const uint32_t idx = atomicAdd(a.novf, 1u);
+    a.ovf[idx] = u;
+    a.ovfq[idx] = c.q;
+    if (a.first_tier) atomicAdd(&a.ctl->nretry, 1u);
 }
 
 // Expand up to 64 G queued vertices (G per lane: list entries eb[g], valid[g],
@@ -843,14 +966,12 @@ __device__ __forceinline__ void expand_chunk(SearchLds<HB, CT> &L, WaveState &st
 // the direct arcs from u into S no heavier than the bound, at the weight of
 // the lightest arc of each pair (parallel arcs: the first lightest).  The
 // source emits those without a search.  Whole wave.
-template <int HB, bool CT>
-__device__ __forceinline__ void direct_pairs(SearchLds<HB, CT> &L, const JoinArgs &a, const SrcCtx &c, int32_t u,
+// stg: cap >= 64 entries of staging (no search runs).
+__device__ __forceinline__ void direct_pairs(const JoinArgs &a, const SrcCtx &c, int32_t u, uint2 *stg, uint32_t cap,
                                              unsigned long long &tseen) {
-    constexpr uint32_t PC = Tier<HB, CT>::PC;
     const uint32_t lane = lane_id();
     const uint32_t bound = current_bound(c);
     const int32_t ub = a.row_ptr[c.rpo + u], ue = a.row_ptr[c.rpo + u + 1];
-    uint2 *const stg = &L.lst[0][0];   // both lists, 2 PC entries: free, no search runs
     uint32_t nst = 0, emitted = 0;
     for (int32_t x0 = ub; x0 < ue; x0 += 64) {
         const int32_t x = x0 + static_cast<int32_t>(lane);
@@ -863,15 +984,15 @@ __device__ __forceinline__ void direct_pairs(SearchLds<HB, CT> &L, const JoinArg
         const uint64_t mM = __ballot(m);
         if (m) atomicAdd(&c.hist[kHistEmit + dist_bin(r.w)], 1u);
         emitted += popc(mM);
-        *(m ? stg + nst + mbcnt(mM) : L.sink()) = make_uint2(r.w, static_cast<uint32_t>(r.y));
+        if (m) stg[nst + mbcnt(mM)] = make_uint2(r.w, static_cast<uint32_t>(r.y));
         nst += popc(mM);
-        if (nst + 64 > 2u * PC) {
+        if (nst + 64 > cap) {
             wave_sync();
-            flush_pairs<HB, CT>(L, a, c, u, nst, stg);
+            flush_pairs(a, c, u, nst, stg);
         }
     }
     wave_sync();
-    flush_pairs<HB, CT>(L, a, c, u, nst, stg);
+    flush_pairs(a, c, u, nst, stg);
     if (emitted != 0) tighten_bound(c, tseen);
     wave_sync();
 }
@@ -889,9 +1010,8 @@ __device__ __forceinline__ void direct_pairs(SearchLds<HB, CT> &L, const JoinArg
 template <int HB, bool CT>
 __device__ void search_source(SearchLds<HB, CT> &L, const JoinArgs &a, const SrcCtx &c, int32_t u,
                               unsigned long long &tseen) {
-    constexpr int H = Tier<HB, CT>::H;
     constexpr int PC = Tier<HB, CT>::PC;
-    constexpr int U = Tier<HB, CT>::U;
+    constexpr uint32_t U = table_rows<HB>();
     const uint32_t lane = lane_id();
     const int32_t ub = a.row_ptr[c.rpo + u];
     const int32_t ue = a.row_ptr[c.rpo + u + 1];
@@ -1013,66 +1133,8 @@ __device__ void search_source(SearchLds<HB, CT> &L, const JoinArgs &a, const Src
         }
     }
 
-    // ---- emit table entries in S, and clear the table for the next source
-    bound = current_bound(c);
-    uint2 *const stg = &L.lst[0][0];   // both lists, 2 PC entries: the search has ended
-    uint32_t nst = 0, emitted = 0;
-    unsigned long long warcs = 0;
-    uint32_t wsettled = 0;
-    for (uint32_t g0 = 0; g0 < static_cast<uint32_t>(H); g0 += 64 * U) {
-        uint32_t k[U], d[U];
-        bool occ[U], sb[U];
-#pragma unroll
-        for (int j = 0; j < U; ++j) {
-            const uint32_t slot = g0 + j * 64 + lane;
-            occ[j] = read_slot(L, slot, c.voff, k[j], d[j]);
-            sb[j] = !st.ovf && occ[j] && in_s(c, k[j]);
-        }
-        if (a.count_work && !st.ovf) {
-#pragma unroll
-            for (int j = 0; j < U; ++j)
-                if (occ[j] && d[j] <= bound) {
-                    warcs += static_cast<unsigned long long>(a.row_ptr[c.rpo + k[j] + 1] - a.row_ptr[c.rpo + k[j]]);
-                    wsettled += 1;
-                }
-        }
-#pragma unroll
-        for (int j = 0; j < U; ++j) clear_slot(L, g0 + j * 64 + lane);
-#pragma unroll
-        for (int j = 0; j < U; ++j) {
-            const bool m = sb[j] && d[j] <= bound;
-            const uint64_t mM = __ballot(m);
-            if (c.k && m) atomicAdd(&c.hist[kHistEmit + dist_bin(d[j])], 1u);
-            emitted += popc(mM);
-            *(m ? stg + nst + mbcnt(mM) : L.sink()) = make_uint2(d[j], k[j]);
-            nst += popc(mM);
-            if (nst + 64 > 2u * PC) {
-                wave_sync();
-                flush_pairs<HB, CT>(L, a, c, u, nst, stg);
-            }
-        }
-    }
-    wave_sync();
-    flush_pairs<HB, CT>(L, a, c, u, nst, stg);
-    if (c.k && emitted != 0) tighten_bound(c, tseen);
-    if (a.count_work && !st.ovf) {
-        for (int o = 32; o > 0; o >>= 1) {
-            const uint32_t lo = static_cast<uint32_t>(__shfl_xor(static_cast<int>(warcs & 0xFFFFFFFFull), o));
-            const uint32_t hi = static_cast<uint32_t>(__shfl_xor(static_cast<int>(warcs >> 32), o));
-            warcs += (static_cast<unsigned long long>(hi) << 32) | lo;
-            wsettled += static_cast<uint32_t>(__shfl_xor(static_cast<int>(wsettled), o));
-        }
-        if (lane == 0) {
-            atomicAdd(&a.ctl->arcs, warcs);
-            atomicAdd(&a.ctl->settled, static_cast<unsigned long long>(wsettled));
-        }
-    }
-    if (st.ovf && lane == 0) {
-        const uint32_t idx = atomicAdd(a.novf, 1u);
-        a.ovf[idx] = u;
-        a.ovfq[idx] = c.q;
-        if (a.first_tier) atomicAdd(&a.ctl->nretry, 1u);
-    }
+    emit_and_clear<HB, CT, false>(L, a, c, u, current_bound(c), st.ovf, &L.lst[0][0], 2u * PC, 0u, 64u * U, tseen);
+    if (st.ovf && lane == 0) queue_next_tier(a, c, u);
     wave_sync();
 }
 
@@ -1089,9 +1151,8 @@ __device__ void search_source(SearchLds<HB, CT> &L, const JoinArgs &a, const Src
 template <int HB, bool CT>
 __device__ void search_source_block(SearchLds<HB, CT> &L, BlockRing &B, const JoinArgs &a, const SrcCtx &c,
                                     int32_t u, unsigned long long &tseen) {
-    constexpr int H = Tier<HB, CT>::H;
     constexpr int NW = Tier<HB, CT>::NW;
-    constexpr int U = Tier<HB, CT>::U;
+    constexpr uint32_t U = table_rows<HB>();
     constexpr uint32_t RC = 2u * Tier<HB, CT>::PC;
     const uint32_t lane = lane_id(), wv = wave_in_block();
     const int32_t ub = a.row_ptr[c.rpo + u];
@@ -1169,55 +1230,173 @@ __device__ void search_source_block(SearchLds<HB, CT> &L, BlockRing &B, const Jo
         __syncthreads();   // every append of the step is done
     }
     const bool ovf = B.ovf != 0;
+    // the waves take the table's chunks of 64 U slots in turn, each staging in
+    // its slice of the ring, free once the search has ended
+    emit_and_clear<HB, CT, false>(L, a, c, u, current_bound(c), ovf, q + wv * (RC / NW), RC / NW, wv * 64u * U,
+                           NW * 64u * U, tseen);
+    if (ovf && threadIdx.x == 0) queue_next_tier(a, c, u);
+    __syncthreads();   // the table is clear and B is free before the next source
+}
 
-    // ---- emit table entries in S (the waves take the table's chunks of 64 U
-    // slots in turn, staged in each wave's slice of the ring, free once the
-    // search has ended; the window areas take the sink writes), and clear the
-    // table for the next source
-    const uint32_t bound = current_bound(c);
-    constexpr uint32_t SC = RC / NW;   // staging entries per wave
-    static_assert(SC >= 128, "a wave's staging slice holds a flush threshold plus a chunk row");
-    static_assert(H % (64 * U) == 0, "the table is a whole number of chunks");
-    uint2 *stg = q + wv * SC;
-    uint32_t nst = 0, emitted = 0;
-    unsigned long long warcs = 0;
-    uint32_t wsettled = 0;
-    for (uint32_t g0 = wv * 64u * U; g0 < static_cast<uint32_t>(H); g0 += NW * 64u * U) {
-        uint32_t k[U], d[U];
-        bool occ[U], sb[U];
-#pragma unroll
-        for (int j = 0; j < U; ++j) {
-            const uint32_t slot = g0 + j * 64 + lane;
-            occ[j] = read_slot(L, slot, c.voff, k[j], d[j]);
-            sb[j] = !ovf && occ[j] && in_s(c, k[j]);
-        }
-        if (a.count_work && !ovf) {
-#pragma unroll
-            for (int j = 0; j < U; ++j)
-                if (occ[j] && d[j] <= bound) {
-                    warcs += static_cast<unsigned long long>(a.row_ptr[c.rpo + k[j] + 1] - a.row_ptr[c.rpo + k[j]]);
-                    wsettled += 1;
-                }
-        }
-#pragma unroll
-        for (int j = 0; j < U; ++j) clear_slot(L, g0 + j * 64 + lane);
-#pragma unroll
-        for (int j = 0; j < U; ++j) {
-            const bool mm = sb[j] && d[j] <= bound;
-            const uint64_t mM = __ballot(mm);
-            if (c.k && mm) atomicAdd(&c.hist[kHistEmit + dist_bin(d[j])], 1u);
-            emitted += popc(mM);
-            *(mm ? stg + nst + mbcnt(mM) : L.sink()) = make_uint2(d[j], k[j]);
-            nst += popc(mM);
-            if (nst + 64 > SC) {
-                wave_sync();
-                flush_pairs<HB, CT>(L, a, c, u, nst, stg);
-            }
-        }
+// ------------------------------------------------------------------ searches over arc quads
+// Graphs whose vertices have few arcs (road graphs: 3.4 on average, rarely more
+// than 4) also keep their arcs as quads: four {target, weight} records of 8
+// bytes at an address that the vertex's id gives, padded with arcs of infinite
+// weight (a vertex of more arcs has further quads elsewhere, one step apart).  A
+// row of 64 lanes then relaxes the arcs of 16 vertices, four lanes each, with
+// nothing to lay out: lane l takes arc l mod 4 of ring entry l / 4, loaded
+// straight from the entry.  Beside those loads one lane per entry reads the
+// vertex's distance, defers or takes it, and the rows get the distances over
+// the lanes.  A step is so one chain of ring read, arc load, claim, min, append,
+// where the window search has a prefix sum, a window map through LDS and a
+// dependent arc load in between.  Lane states are kept as 64-bit masks in scalar
+// registers.  A step is bound by its instructions (a wave issues one every four
+// cycles at best) and the LDS round trips between them.  Whole theta-joins on the
+// 1024 x 1024 road graph, windows -> quads: theta = 700 (32 768 searches) 455 ->
+// 224 us (with tables sized to the balls), 5 700 701 -> 612, 8 000 2 159 -> 1 689;
+// theta = 3 000 (2^11, bound the same way) 240 -> 239.
+template <int HB, bool CT>
+struct QTier {
+    // ring entries (a power of two), waves per search, rows of 16 vertices a
+    // wave takes per step.  (2^12: 3 waves of 3 rows 357 us at theta = 4 000, 2 of
+    // 4 367; 2^13: 4 of 3 609 us at 5 700, 4 of 4 622, 8 of 2 812; 2^14: 8 of 3
+    // 1 699 us at 8 000, 8 of 4 1 728, 4 of 4 1 980, 16 of 1 2 824)
+    static constexpr uint32_t RC = HB <= 9 ? 128 : (HB <= 11 ? 256 : (HB <= 13 ? 512 : 1024));
+    static constexpr int NW = HB >= 14 ? 8 : (HB == 13 ? 4 : (HB == 12 ? 3 : 1));
+    static constexpr int NR = HB == 11 ? 4 : 3;
+};
+
+// Ring entries: {byte offset of the vertex's table slot, quad | flags}; every
+// entry of the ring, also one not in use, names a slot and a quad that exist
+// (rows read a few entries past the last; the ring is cleared after each
+// search, since the next one may be on a smaller graph).  The flags (from bit 27
+// on, where an address computed from the word drops them): two bits count the
+// vertex's further quads after this one, kQuadFurther marks an entry that names
+// a further quad itself.  The pending bit of a vertex stands for its first
+// quad's entry; a step queues the next quad of what it expands.  Ids are the
+// graph's own, without gaps for the further quads: numbered with such gaps,
+// balls spread unevenly over the table (multiplicative hashing spreads runs of
+// ids evenly) and a tenth of the benchmark's searches outgrew the probe field.
+// Pairs found wait in a stage until 64 are there: {distance, local id} and
+// their source; searches over tables up to 2^10 find few each, and share the
+// stage (a theta-join's pairs need not be counted at once), larger ones stage
+// in the ring once the search has ended.
+constexpr uint32_t kStage = 64;
+template <int HB>
+constexpr bool quad_stages() { return HB <= 10; }
+
+template <int HB, bool CT, bool ST = quad_stages<HB>()>
+struct QuadLds : Table<HB, CT> {
+    uint2 ring[QTier<HB, CT>::RC];
+};
+template <int HB, bool CT>
+struct QuadLds<HB, CT, true> : Table<HB, CT> {
+    uint2 ring[QTier<HB, CT>::RC];
+    uint2 stg[kStage];
+    int32_t stu[kStage];
+};
+
+__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// mbcnt on top of a base.
+__device__ __forceinline__ uint32_t mbcnt_from(uint64_t m, uint32_t base) {
+    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), base));
+}
+
+__device__ __forceinline__ uint32_t *at_byte(uint32_t *p, uint32_t off) {
+    return reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(p) + off);
+}
+
+// Distance words of the slot at byte offset off.
+template <int HB, bool CT>
+__device__ __forceinline__ uint32_t *quad_word(Table<HB, CT> &L, uint32_t off) {
+    if constexpr (CT) return at_byte(L.t, off);
+    else return at_byte(L.dw, off);
+}
+template <int HB, bool CT>
+constexpr uint32_t quad_pend() {
+    if constexpr (CT) return Compact<HB>::PEND;
+    else return 1u;
+}
+template <int HB, bool CT>
+constexpr uint32_t quad_dist_shift() {
+    if constexpr (CT) return Compact<HB>::SH + 1u;
+    else return 1u;
+}
+
+// Write the n <= 64 staged pairs of query c.  Whole wave.
+__device__ __forceinline__ void flush_stage(const JoinArgs &a, const SrcCtx &c, uint32_t &n, const uint2 *stg,
+                                            const int32_t *stu) {
+    if (n == 0) return;
+    const uint32_t i = min(lane_id(), n - 1u);
+    wave_sync();
+    const uint2 e = stg[i];
+    const int32_t us = stu[i];
+    const int32_t from = caller_id(a, us, c.voff), to = caller_id(a, static_cast<int32_t>(e.y), c.voff);
+    const unsigned long long idx = reserve_recs(a, c, n) + lane_id();
+    if (lane_id() < n && idx < a.rec_cap) {
+        Rec r;
+        r.u = c.swapped ? to : from;
+        r.v = c.swapped ? from : to;
+        r.d = e.x;
+        r.q = c.q;
+        if (a.bins) r.q |= bin_place(atomicAdd(&a.bins[a.binbase[c.q] + r.d], 1u));
+        a.recs[idx] = r;
     }
     wave_sync();
-    flush_pairs<HB, CT>(L, a, c, u, nst, stg);
-    if (c.k && emitted != 0) tighten_bound(c, tseen);
+    n = 0;
+}
+
+// The end of a search over quads from u: stage the table entries in S (none when
+// the search outgrew the tier: ovf), clear the table and the ring.  Whole wave.
+template <int HB, bool CT>
+__device__ __forceinline__ void quad_emit(QuadLds<HB, CT, true> &L, const JoinArgs &a, const SrcCtx &c, int32_t u,
+                                          bool ovf, uint32_t &nst, unsigned long long &tseen) {
+    constexpr uint32_t U = Table<HB, CT>::H / 64u;
+    const uint32_t lane = lane_id(), bound = current_bound(c), before = nst;
+    uint32_t emitted = 0;
+    unsigned long long warcs = 0;
+    uint32_t wsettled = 0;
+    uint32_t k[U], d[U], sw[U];
+#pragma unroll
+    for (uint32_t j = 0; j < U; ++j) {
+        const bool occ = read_slot(L, j * 64 + lane, c.voff, k[j], d[j]);
+        if constexpr (!CT) k[j] += static_cast<uint32_t>(c.voff);   // (its keys are local ids)
+        if (!occ || ovf) d[j] = kInf;
+        sw[j] = 0;
+        const uint32_t yl = k[j] - static_cast<uint32_t>(c.voff);
+        if (occ) sw[j] = c.sbits[yl >> 5] >> (yl & 31u);
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < U; ++j) clear_slot(L, j * 64 + lane);
+    for (uint32_t i = lane; i < QTier<HB, CT>::RC; i += 64) L.ring[i] = make_uint2(0u, 0u);
+#pragma unroll
+    for (uint32_t j = 0; j < U; ++j) {
+        if (a.count_work && d[j] <= bound) {
+            warcs += static_cast<unsigned long long>(a.row_ptr[c.rpo + k[j] + 1] - a.row_ptr[c.rpo + k[j]]);
+            wsettled += 1;
+        }
+        const uint64_t m = __ballot((sw[j] & 1u) != 0u) & __ballot(d[j] <= bound);
+        if (m == 0) continue;
+        if (c.k && lane_in(m)) atomicAdd(&c.hist[kHistEmit + dist_bin(d[j])], 1u);
+        if (nst + popc(m) > kStage) {
+            emitted += nst;
+            flush_stage(a, c, nst, L.stg, L.stu);
+        }
+        if (lane_in(m)) {
+            const uint32_t i = mbcnt_from(m, nst);
+            L.stg[i] = make_uint2(d[j], k[j]);
+            L.stu[i] = u;
+        }
+        nst += popc(m);
+    }
+    if (c.k) {
+        // k-closest pairs: counted at once, for the bound
+        emitted += nst - before;
+        flush_stage(a, c, nst, L.stg, L.stu);
+        if (emitted != 0) tighten_bound(c, tseen);
+    }
     if (a.count_work && !ovf) {
         for (int o = 32; o > 0; o >>= 1) {
             const uint32_t lo = static_cast<uint32_t>(__shfl_xor(static_cast<int>(warcs & 0xFFFFFFFFull), o));
@@ -1230,12 +1409,528 @@ __device__ void search_source_block(SearchLds<HB, CT> &L, BlockRing &B, const Jo
             atomicAdd(&a.ctl->settled, static_cast<unsigned long long>(wsettled));
         }
     }
-    if (ovf && threadIdx.x == 0) {
-        const uint32_t idx = atomicAdd(a.novf, 1u);
-        a.ovf[idx] = u;
-        a.ovfq[idx] = c.q;
-        if (a.first_tier) atomicAdd(&a.ctl->nretry, 1u);
+}
+
+// What one wave does in a step, from the entries' distances to the appends.
+struct QuadState {
+    uint32_t tail;     // ring index of the next append (block: at the step's start)
+    uint32_t nins;     // table entries in use (block: at the step's start)
+    uint32_t imin;     // block: per-lane least distance queued in the step
+    uint32_t pnew;     // k-closest pairs: discoveries counted, not yet published
+    bool ovf;          // the search outgrew this tier
+    bool probing;      // k-closest pairs: count discoveries of S members
+};
+
+// Relax the rows' arcs: arc[j] {target | flags, weight}, d[j] the distance they
+// leave from (kInf: none), and append the vertices that became pending.  Per
+// row, the table step claims or finds the target's slot by compare-and-swap
+// from its home slot on (linear probing in rounds, each for the lanes still
+// searching), and lowers the found slots' words that are larger by atomicMin
+// (two thirds of the arcs reach a vertex at a better distance and are done
+// after the claim).  reserve(nadd, ins, lost) returns the ring index of nadd
+// entries, or sets st.ovf.
+template <int HB, bool CT, int NJ, bool MIN, typename Reserve>
+__device__ __forceinline__ void quad_relax(QuadLds<HB, CT> &L, QuadState &st, const SrcCtx &c, const uint2 *arc,
+                                           const uint32_t *d, uint32_t bound, Reserve reserve) {
+    constexpr uint32_t M = QTier<HB, CT>::RC - 1u;
+    constexpr uint32_t HM = (Table<HB, CT>::H - 1u) << 2;   // slot byte offsets
+    constexpr uint32_t kMaxWord = CT ? Compact<HB>::MAXD : kPackMax;
+    const uint32_t lim = min(bound, kMaxWord);
+    uint32_t nd[NJ], off[NJ], nw[NJ], old[NJ], sw[NJ];
+    uint64_t claimed[NJ], found[NJ], probe[NJ];
+    bool lost = false;   // a distance or probe sequence the table cannot hold
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) nd[j] = sat_add(d[j], arc[j].y);
+    if (bound > kMaxWord) {   // (only when the bound itself is that large)
+        uint64_t m = 0;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) m |= __ballot(nd[j] <= bound) & __ballot(nd[j] > kMaxWord);
+        lost = m != 0;
     }
+    if (st.probing) {   // (k-closest pairs) the S-bitmap words, read beside the claims
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const uint32_t yl = arc[j].x & kQuadId;
+            sw[j] = nd[j] <= lim ? c.sbits[yl >> 5] >> (yl & 31u) : 0u;
+        }
+    }
+    if constexpr (CT) {
+        using K = Compact<HB>;
+        uint64_t act[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            // (the 24-bit product reads the id below the flags; idle lanes
+            // compare with a word no slot holds)
+            const uint32_t z = mul24(arc[j].x, kHash24);
+            off[j] = (z >> (K::IDB - 2u)) & HM;
+            nw[j] = (nd[j] << (K::SH + 1u)) | ((z & K::REM) | K::PEND);
+            act[j] = __ballot(nd[j] <= lim);
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) old[j] = atomicCAS(at_byte(L.t, off[j]), lane_in(act[j]) ? kWordNone : kNoKey, nw[j]);
+        __builtin_amdgcn_sched_barrier(0);   // every claim is issued before the first result is used
+        uint64_t any = 0;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            claimed[j] = act[j] & __ballot(old[j] == kWordNone);
+            found[j] = act[j] & __ballot(((old[j] ^ nw[j]) & K::IDM) == 0u);
+            probe[j] = act[j] & ~claimed[j] & ~found[j];
+            any |= probe[j];
+        }
+#pragma unroll 1
+        for (uint32_t round = 1; any != 0; ++round) {
+            if (round > K::MAXP) {   // the probe distance field is full
+                lost = true;
+                break;
+            }
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                if (lane_in(probe[j])) {   // one slot on, in the identity too
+                    off[j] = (off[j] + 4u) & HM;
+                    nw[j] += 1u << K::IDB;
+                    old[j] = atomicCAS(at_byte(L.t, off[j]), kWordNone, nw[j]);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            any = 0;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const uint64_t cl = probe[j] & __ballot(old[j] == kWordNone);
+                const uint64_t fo = probe[j] & __ballot(((old[j] ^ nw[j]) & K::IDM) == 0u);
+                claimed[j] |= cl;
+                found[j] |= fo;
+                probe[j] &= ~cl & ~fo;
+                any |= probe[j];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) found[j] &= __ballot(nw[j] < old[j]);   // a word only falls
+    } else {
+        uint32_t y[NJ];
+        uint64_t act[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            y[j] = arc[j].x & kQuadId;
+            off[j] = slot_hash<HB>(y[j]) << 2;
+            nw[j] = (nd[j] << 1) | 1u;
+            act[j] = __ballot(nd[j] <= lim);
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) old[j] = atomicCAS(at_byte(L.key, off[j]), lane_in(act[j]) ? kEmpty : kNoKey, y[j]);
+        __builtin_amdgcn_sched_barrier(0);   // every claim is issued before the first result is used
+        uint64_t any = 0;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            found[j] = act[j] & (__ballot(old[j] == kEmpty) | __ballot(old[j] == y[j]));
+            probe[j] = act[j] & ~found[j];
+            any |= probe[j];
+        }
+#pragma unroll 1
+        for (uint32_t round = 1; any != 0; ++round) {
+            if (round > Table<HB, CT>::H) {   // every slot visited: the table is full
+                lost = true;
+                break;
+            }
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                if (lane_in(probe[j])) {
+                    off[j] = (off[j] + 4u) & HM;
+                    old[j] = atomicCAS(at_byte(L.key, off[j]), kEmpty, y[j]);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            any = 0;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const uint64_t fo = probe[j] & (__ballot(old[j] == kEmpty) | __ballot(old[j] == y[j]));
+                found[j] |= fo;
+                probe[j] &= ~fo;
+                any |= probe[j];
+            }
+        }
+    }
+    uint64_t any = 0;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) any |= found[j];
+    uint64_t app[NJ], fresh[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        if constexpr (CT) app[j] = fresh[j] = claimed[j];
+        else app[j] = fresh[j] = 0;
+    }
+    if (any != 0) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            if (lane_in(found[j])) old[j] = atomicMin(quad_word(L, off[j]), nw[j]);
+        __builtin_amdgcn_sched_barrier(0);   // every min is issued before the first result is used
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            // appended by the lane that improved an idle (or new) vertex
+            const uint64_t imp = found[j] & __ballot(nw[j] < old[j]);
+            const uint64_t idle = __ballot((old[j] & quad_pend<HB, CT>()) == 0u);
+            if constexpr (CT) {
+                app[j] |= imp & idle;
+            } else {
+                fresh[j] = imp & __ballot(old[j] == kWordNone);
+                app[j] = imp & (idle | fresh[j]);
+            }
+            if constexpr (MIN) st.imin = min(st.imin, lane_in(imp | fresh[j]) ? nd[j] : kInf);
+        }
+    } else if constexpr (MIN) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) st.imin = min(st.imin, lane_in(fresh[j]) ? nd[j] : kInf);
+    }
+    uint32_t nadd = 0, ins = 0;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        nadd += popc(app[j]);
+        ins += popc(fresh[j]);
+    }
+    if (st.probing && ins != 0) {
+        // k-closest pairs: a first discovery of an S member is a pair with a
+        // path of length nd
+        uint32_t *ph = probe_hist(c);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const uint64_t hit = fresh[j] & __ballot((sw[j] & 1u) != 0u);
+            if (lane_in(hit)) atomicAdd(&ph[dist_bin(nd[j])], 1u);
+            st.pnew += popc(hit);
+        }
+    }
+    uint32_t base = reserve(nadd, ins, lost);
+    if (st.ovf) return;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        if (lane_in(app[j])) L.ring[mbcnt_from(app[j], base) & M] = make_uint2(off[j], arc[j].x);
+        base += popc(app[j]);
+    }
+}
+
+// Arc lane l mod 4 (lane8: its byte offset) of quad q (a 32-bit byte offset, which drops the flags).
+__device__ __forceinline__ uint2 quad_arc(const SrcCtx &c, uint32_t q, uint32_t lane8) {
+    return *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(c.quads) + ((q << 5) + lane8));
+}
+
+__device__ __forceinline__ uint32_t from_lane(uint32_t byte_lane, uint32_t v) {
+    return static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(static_cast<int>(byte_lane), static_cast<int>(v)));
+}
+
+// The end of a step's variant for NJ rows: keeps the compiler from merging the
+// last, lane-masked write of the variants into one block, after which it takes
+// everything carried around the loop (ring indices, counts) as lane-dependent
+// and keeps it in vector registers.
+template <int NJ>
+__device__ __forceinline__ void keep_apart() {
+    asm volatile("; %0 rows" ::"n"(NJ));
+}
+
+// Append, for the lanes of m, the next quad of the entries e (nq: its number).
+template <int HB, bool CT>
+__device__ __forceinline__ void push_further(QuadLds<HB, CT> &L, uint64_t m, uint32_t base, uint2 e, uint32_t nq) {
+    constexpr uint32_t M = QTier<HB, CT>::RC - 1u;
+    if (lane_in(m))
+        L.ring[mbcnt_from(m, base) & M] =
+            make_uint2(e.x, nq | ((e.y & ~kQuadId) - (kQuadId + 1u)) | kQuadFurther);
+}
+
+// One step of a one-wave search: the m oldest ring entries (16 (NJ - 1) < m <=
+// 16 NJ) from index head on.
+template <int HB, bool CT, int NJ>
+__device__ __forceinline__ void quad_step(QuadLds<HB, CT> &L, QuadState &st, const SrcCtx &c, uint32_t head,
+                                          uint32_t m, uint32_t bound) {
+    constexpr uint32_t M = QTier<HB, CT>::RC - 1u;
+    const uint32_t lane = lane_id(), lane4 = lane >> 2, lane8 = (lane & 3u) << 3;
+    uint2 arc[NJ];
+    uint32_t q[NJ], d[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) q[j] = L.ring[(lane4 + (head + 16u * j)) & M].y;
+    const uint2 e = L.ring[(lane + head) & M];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) arc[j] = quad_arc(c, q[j], lane8);
+    const uint32_t dl = *quad_word(L, e.x) >> quad_dist_shift<HB, CT>();
+    wave_sync();  // the taken entries are read before appends reuse their slots
+    uint64_t val = m >= 64u ? ~0ull : (1ull << m) - 1ull;   // lanes with an entry
+    const uint64_t further = __ballot(e.y >= kQuadFurther);
+    if (c.slack != kInf) {
+        // a vertex far above the step's least distance goes back to the tail,
+        // still pending: its distance is likely to improve before it comes
+        // round again, which saves expanding it twice (further quads, whose
+        // vertices were expanded a step ago, do not count for the least)
+        const uint32_t lim = sat_add(wave_min(lane_in(val & ~further) ? dl : kInf), c.slack);
+        uint64_t later = val & __ballot(dl > lim);
+        if (c.hist != nullptr) later &= __ballot(dl <= bound);   // (a theta-join's table holds nothing beyond)
+        if (lane_in(later)) L.ring[mbcnt_from(later, st.tail) & M] = e;
+        st.tail = uni(st.tail + popc(later));
+        val &= ~later;
+    }
+    // expanded now (or beyond the bound): not pending
+    if (lane_in(val & ~further)) atomicAnd(quad_word(L, e.x), ~quad_pend<HB, CT>());
+    if (c.hist != nullptr) val &= __ballot(dl <= bound);
+    const uint32_t dx = lane_in(val) ? dl : kInf;
+    const uint64_t more = val & __ballot((e.y & kQuadMore) != 0u);
+    uint32_t nq = 0;
+    if (lane_in(more)) nq = c.further[e.y & kQuadId];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) d[j] = from_lane((lane & ~3u) + 64u * j, dx);
+    const uint32_t taken = head + m;
+    quad_relax<HB, CT, NJ, false>(L, st, c, arc, d, bound, [&](uint32_t nadd, uint32_t ins, bool lost) {
+        const uint32_t base = st.tail;
+        st.nins = uni(st.nins + ins);
+        st.tail = uni(st.tail + nadd + popc(more));
+        st.ovf = uni((lost || st.nins > (3u * Table<HB, CT>::H) / 4u || st.tail - taken > M + 1u) ? 1u : 0u) != 0u;
+        if (!st.ovf) push_further(L, more, base + nadd, e, nq);
+        return base;
+    });
+    keep_apart<NJ>();
+}
+
+// k-closest pairs, at the start of a step: as probe_phase, on a count n and a
+// bound read during the step before (a late value only prunes less).
+__device__ __forceinline__ void probe_step(const SrcCtx &c, uint32_t n, uint32_t &pnew, bool &probing,
+                                           uint32_t &seen) {
+    if (pnew) {
+        if (lane_id() == 0) atomicAdd(probe_count(c), pnew);
+        n += pnew;
+        pnew = 0;
+    }
+    probing = n < probe_cap(c);
+    if (n < c.k || n < seen + (seen >> 3) + 1u) return;
+    seen = n;
+    const uint32_t b = wave_bound_from_hist(probe_hist(c), c.k);
+    if (lane_id() == 0) atomicMin(&c.qs->bound, b);
+}
+
+// The bound and the count are read every kPoll steps, and used a step later, so
+// that no step waits for them.
+constexpr uint32_t kPoll = 2;
+__device__ __forceinline__ void poll_bound(const SrcCtx &c, uint32_t &phase, uint32_t &nbound, uint32_t &ncount,
+                                           uint32_t &bound, uint32_t &pnew, bool &probing, uint32_t &seen) {
+    // small searches (the first two steps) never count discoveries
+    if (phase >= 2 && phase % kPoll == 0) {
+        bound = min(uni(nbound), c.theta);
+        probe_step(c, uni(ncount), pnew, probing, seen);
+    }
+    ++phase;
+    if (phase >= 2 && phase % kPoll == 0) {
+        nbound = __hip_atomic_load(&c.qs->bound, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ncount = __hip_atomic_load(probe_count(c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// Byte offset of the slot where source u (local id) is put at distance 0,
+// pending, into the empty table.
+template <int HB, bool CT>
+__device__ __forceinline__ uint32_t put_quad_source(Table<HB, CT> &L, uint32_t u) {
+    return put_source(L, static_cast<int32_t>(u), 0) << 2;
+}
+
+// The ring entry of source u (local id).
+__device__ __forceinline__ uint2 source_entry(const JoinArgs &a, const SrcCtx &c, uint32_t off, uint32_t u) {
+    const int32_t r = static_cast<int32_t>(u) + c.voff + static_cast<int32_t>(c.rpo);
+    const int32_t deg = a.row_ptr[r + 1] - a.row_ptr[r];
+    return make_uint2(off, u + (deg > 4 ? (static_cast<uint32_t>(deg) - 1u) / 4u : 0u) * (kQuadId + 1u));
+}
+
+// Bounded search from u by one wave: the delta = 0 search of search_source
+// (a FIFO ring of pending vertices, steps of at most 16 NR of them) over quads.
+template <int HB, bool CT>
+__device__ void search_quads(QuadLds<HB, CT> &L, const JoinArgs &a, const SrcCtx &c, int32_t u, uint32_t &nst,
+                             unsigned long long &tseen) {
+    using T = QTier<HB, CT>;
+    const uint32_t lane = lane_id(), ul = static_cast<uint32_t>(u - c.voff);
+    if (lane == 0) L.ring[0] = source_entry(a, c, put_quad_source(L, ul), ul);
+    wave_sync();
+    QuadState st;
+    st.tail = 1;
+    st.nins = 1;
+    st.imin = kInf;
+    st.pnew = 0;
+    st.ovf = false;
+    st.probing = false;
+    uint32_t head = 0, seen = 0, phase = 0;
+    uint32_t bound = uni(current_bound(c)), nbound = bound, ncount = 0;
+    if (c.hist != nullptr) ncount = __hip_atomic_load(probe_count(c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (true) {
+        head = uni(head);
+        const uint32_t np = st.tail - head;
+        if (np == 0 || st.ovf) break;
+        if (c.hist != nullptr) {
+            poll_bound(c, phase, nbound, ncount, bound, st.pnew, st.probing, seen);
+        }
+        const uint32_t m = min(16u * T::NR, np);
+        switch ((m + 15u) / 16u) {
+            case 1: quad_step<HB, CT, 1>(L, st, c, head, m, bound); break;
+            case 2: quad_step<HB, CT, 2>(L, st, c, head, m, bound); break;
+            case 3: if constexpr (T::NR >= 3) quad_step<HB, CT, 3>(L, st, c, head, m, bound); break;
+            default: if constexpr (T::NR >= 4) quad_step<HB, CT, 4>(L, st, c, head, m, bound); break;
+        }
+        head += m;
+        wave_sync();   // the appends are written before the next step reads them
+    }
+    if constexpr (quad_stages<HB>())
+        quad_emit<HB, CT>(L, a, c, u, st.ovf, nst, tseen);
+    else
+        emit_and_clear<HB, CT, true>(L, a, c, u, current_bound(c), st.ovf, L.ring, T::RC, 0u, 64u * table_rows<HB>(),
+                                     tseen);
+    if (st.ovf && lane == 0) queue_next_tier(a, c, u);
+    wave_sync();
+}
+
+// State shared by the waves of a block that runs one search over quads, kept by
+// step modulo 3, since one barrier separates the steps: while a fast wave
+// already appends in step s, a slow one still reads what step s - 1 left, and
+// step s + 1's words are cleared in between.
+struct alignas(8) QuadStep {
+    uint32_t fill;   // ring entries appended (low 16 bits), table entries added (next 15), kQuadOvf
+    uint32_t dmin;   // least distance queued for the next step
+};
+struct QuadBlock {
+    QuadStep step[3];
+};
+constexpr uint32_t kQuadOvf = 1u << 31;   // the search outgrew this tier
+
+// One wave's rows of a block step: row j takes the entries head + 16 (j NW + wv)
+// on of the step's m.
+template <int HB, bool CT, int NJ>
+__device__ __forceinline__ void quad_block_step(QuadLds<HB, CT> &L, QuadStep *now, QuadState &st, const SrcCtx &c,
+                                                uint32_t head, uint32_t m, uint32_t wv, uint32_t lim, uint32_t bound) {
+    using T = QTier<HB, CT>;
+    constexpr uint32_t M = T::RC - 1u;
+    static_assert(64 * T::NR * T::NW < 0x8000, "a step's counts fit their fields");
+    const uint32_t lane = lane_id(), lane4 = lane >> 2, lane8 = (lane & 3u) << 3;
+    uint2 arc[NJ];
+    uint32_t q[NJ], d[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) q[j] = L.ring[(lane4 + (head + 16u * (j * T::NW + wv))) & M].y;
+    // this lane's entry: lane mod 16 of row lane / 16
+    const uint32_t i = (lane & 15u) + 16u * ((lane >> 4) * T::NW + wv);
+    const uint2 e = L.ring[(i + head) & M];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) arc[j] = quad_arc(c, q[j], lane8);
+    uint64_t val = __ballot(i < m);
+    if constexpr (NJ < 4) val &= (1ull << (16 * NJ)) - 1ull;
+    const uint64_t further = __ballot(e.y >= kQuadFurther);
+    // entries stop being pending as their distance is read, in one LDS atomic:
+    // a wave that improves one of these vertices later finds it idle and queues
+    // it again
+    uint32_t dl = kInf;
+    if (lane_in(val))
+        dl = atomicAnd(quad_word(L, e.x), lane_in(further) ? 0xFFFFFFFFu : ~quad_pend<HB, CT>()) >>
+             quad_dist_shift<HB, CT>();
+    st.imin = kInf;
+    uint64_t later = 0;
+    if (c.slack != kInf) {
+        // what lies far above the least distance queued for this step goes back,
+        // pending again, with the step's appends (a vertex that another wave has
+        // queued since is then in the ring twice, which costs an expansion)
+        later = val & __ballot(dl > lim);
+        if (c.hist != nullptr) later &= __ballot(dl <= bound);
+        if (lane_in(later & ~further)) atomicOr(quad_word(L, e.x), quad_pend<HB, CT>());
+        st.imin = lane_in(later) ? dl : kInf;
+        val &= ~later;
+    }
+    if (c.hist != nullptr) val &= __ballot(dl <= bound);
+    const uint32_t dx = lane_in(val) ? dl : kInf;
+    const uint64_t more = val & __ballot((e.y & kQuadMore) != 0u);
+    uint32_t nq = 0;
+    if (lane_in(more)) nq = c.further[e.y & kQuadId];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) d[j] = from_lane((lane & ~3u) + 64u * j, dx);
+    quad_relax<HB, CT, NJ, true>(L, st, c, arc, d, bound, [&](uint32_t nadd, uint32_t ins, bool lost) {
+        const uint32_t back = popc(later), all = nadd + back + popc(more);
+        uint32_t f = 0;
+        if (lane == 0) f = atomicAdd(&now->fill, (ins << 16) | all);
+        f = uni(f);
+        const uint32_t base = st.tail + (f & 0xFFFFu);
+        const uint32_t used = st.nins + ((f >> 16) & 0x7FFFu) + ins;
+        // (entries from head on may still be unread by other waves)
+        if (lost || used > (3u * Table<HB, CT>::H) / 4u || base + all - head > M + 1u) {
+            st.ovf = true;
+        } else {
+            if (lane_in(later)) L.ring[mbcnt_from(later, base) & M] = e;
+            push_further(L, more, base + back, e, nq);
+        }
+        return base + all - nadd;
+    });
+    if (c.slack != kInf) {
+        // least distance queued: over each row of 16 lanes, then one LDS atomic
+        uint32_t mn = st.imin;
+        mn = min(mn, dpp<0x111>(mn, kInf));
+        mn = min(mn, dpp<0x112>(mn, kInf));
+        mn = min(mn, dpp<0x114>(mn, kInf));
+        mn = min(mn, dpp<0x118>(mn, kInf));
+        if (lane_in(0x8000800080008000ull)) atomicMin(&now->dmin, mn);
+    }
+    if (st.ovf && lane == 0) atomicOr(&now->fill, kQuadOvf);
+    keep_apart<NJ>();
+}
+
+// The search over quads by a block of NW waves sharing one table (tables of
+// 2^12 entries and more, which leave room for few searches per CU): each step
+// the waves take 16 NR ring entries at most each, dealt row by row, with one
+// block barrier per step: entries leave their pending state as they are read,
+// the deferral measures from the least distance queued for the step, and the
+// ring keeps a step's entries until its end.  Every loop that crosses the
+// barrier decides on values read from LDS after it, so the waves always agree.
+template <int HB, bool CT>
+__device__ void search_quads_block(QuadLds<HB, CT> &L, QuadBlock &B, const JoinArgs &a, const SrcCtx &c, int32_t u,
+                                   unsigned long long &tseen) {
+    using T = QTier<HB, CT>;
+    constexpr uint32_t NW = T::NW;
+    const uint32_t wv = uni(wave_in_block());
+    if (threadIdx.x == 0) {
+        const uint32_t ul = static_cast<uint32_t>(u - c.voff);
+        L.ring[0] = source_entry(a, c, put_quad_source(L, ul), ul);
+        B.step[0] = QuadStep{0u, kInf};
+        B.step[1] = QuadStep{0u, kInf};
+        B.step[2] = QuadStep{(1u << 16) | 1u, 0u};   // (left by the step before the first)
+    }
+    __syncthreads();
+    QuadState st;
+    st.tail = 0;
+    st.nins = 0;
+    st.imin = kInf;
+    st.pnew = 0;
+    st.ovf = false;
+    st.probing = false;
+    uint32_t seen = 0, phase = 0, head = 0, s0 = 0;
+    uint32_t bound = uni(current_bound(c)), nbound = bound, ncount = 0;
+    if (c.hist != nullptr) ncount = __hip_atomic_load(probe_count(c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bool ovf = false;
+    while (true) {
+        const uint32_t s1 = s0 == 2 ? 0u : s0 + 1u, s2 = s1 == 2 ? 0u : s1 + 1u;
+        // what the last step left: every wave reads the same
+        const QuadStep last = B.step[s2];
+        const uint32_t f = uni(last.fill);
+        st.tail += f & 0xFFFFu;
+        st.nins += (f >> 16) & 0x7FFFu;
+        ovf = (f & kQuadOvf) != 0u;
+        if (ovf || st.tail == head) break;
+        const uint32_t lim = sat_add(uni(last.dmin), c.slack);
+        if (c.hist != nullptr) poll_bound(c, phase, nbound, ncount, bound, st.pnew, st.probing, seen);
+        if (threadIdx.x == 0) B.step[s1] = QuadStep{0u, kInf};   // read in the last step, used in the next one
+        const uint32_t m = min(16u * T::NR * NW, st.tail - head);
+        const uint32_t rows = (m + 15u) / 16u;
+        const uint32_t nj = rows > wv ? (rows - wv + NW - 1u) / NW : 0u;
+        switch (nj) {
+            case 0: break;
+            case 1: quad_block_step<HB, CT, 1>(L, &B.step[s0], st, c, head, m, wv, lim, bound); break;
+            case 2: quad_block_step<HB, CT, 2>(L, &B.step[s0], st, c, head, m, wv, lim, bound); break;
+            case 3:
+                if constexpr (T::NR >= 3)
+                    quad_block_step<HB, CT, 3>(L, &B.step[s0], st, c, head, m, wv, lim, bound);
+                break;
+            default:
+                if constexpr (T::NR >= 4)
+                    quad_block_step<HB, CT, 4>(L, &B.step[s0], st, c, head, m, wv, lim, bound);
+                break;
+        }
+        head += m;
+        s0 = s1;
+        __syncthreads();   // every append of the step is done
+    }
+    static_assert(T::RC / NW >= 64, "a wave's staging slice holds a table row's pairs");
+    emit_and_clear<HB, CT, true>(L, a, c, u, current_bound(c), ovf, L.ring + wv * (T::RC / NW), T::RC / NW,
+                                 wv * 64u * table_rows<HB>(), NW * 64u * table_rows<HB>(), tseen);
+    if (ovf && threadIdx.x == 0) queue_next_tier(a, c, u);
     __syncthreads();   // the table is clear and B is free before the next source
 }
 
@@ -1253,11 +1948,15 @@ __device__ __forceinline__ void launch_range(const JoinArgs &a, uint32_t &b, uin
 // thousands of blocks contend for the counters at a launch's start and end.)
 // GEN = false: every source belongs to a theta-join, and the k-closest-pairs
 // code is compiled out.
-template <int HB, bool GEN, bool CT>
-__global__ __launch_bounds__((64 * Tier<HB, CT>::NW)) void k_join(JoinArgs a) {
-    __shared__ SearchLds<HB, CT> L;
-    constexpr int H = Tier<HB, CT>::H;
-    constexpr int NW = Tier<HB, CT>::NW;
+// Q: over quads (graphs that keep them, queries without buckets).
+template <int HB, bool CT, bool Q>
+constexpr int join_waves() { return Q ? QTier<HB, CT>::NW : Tier<HB, CT>::NW; }
+
+template <int HB, bool GEN, bool CT, bool Q>
+__global__ __launch_bounds__((64 * join_waves<HB, CT, Q>())) void k_join(JoinArgs a) {
+    __shared__ std::conditional_t<Q, QuadLds<HB, CT>, SearchLds<HB, CT>> L;
+    constexpr int H = 1 << HB;
+    constexpr int NW = join_waves<HB, CT, Q>();
     uint32_t b, n;
     launch_range(a, b, n);
     const uint32_t per = (n + 7u) / 8u;
@@ -1265,50 +1964,53 @@ __global__ __launch_bounds__((64 * Tier<HB, CT>::NW)) void k_join(JoinArgs a) {
     // one k-query answered by k_kcp_direct: nothing to search
     if (GEN && a.srcq[b] == a.srcq[b + n - 1] && a.qs[a.srcq[b]].direct) return;
     for (uint32_t i = threadIdx.x; i < static_cast<uint32_t>(H); i += 64 * NW) clear_slot(L, i);
-    if constexpr (NW > 1) {
-        __shared__ BlockRing B;
-        __syncthreads();
-        unsigned long long tseen = 0;
-        uint32_t tq = kInf;
-        for (uint32_t t = blockIdx.x; t < 8u * per; t += gridDim.x) {
-            const uint32_t si = (t & 7u) * per + (t >> 3);
-            if (si >= n) continue;
-            if (GEN && a.qs[a.srcq[b + si]].direct) continue;   // answered by k_kcp_direct
-            SrcCtx c = load_ctx(a, a.srcq[b + si]);
-            if (!GEN) {
-                c.k = 0;
-                c.hist = nullptr;
-            }
-            if (c.q != tq) {
-                tq = c.q;
-                tseen = 0;
-            }
-            search_source_block<HB, CT>(L, B, a, c, a.src[b + si], tseen);
+    if constexpr (Q)
+        for (uint32_t i = threadIdx.x; i < QTier<HB, CT>::RC; i += 64 * NW) L.ring[i] = make_uint2(0u, 0u);
+    __shared__ std::conditional_t<Q, QuadBlock, BlockRing> B;   // (NW > 1)
+    if constexpr (NW > 1) __syncthreads();
+    else wave_sync();
+    uint32_t tq = kInf;              // query of tseen
+    unsigned long long tseen = 0;    // its emitted count at this wave's last bound update
+    uint32_t nst = 0;                // pairs staged (quad_stages), of the last source's query
+    SrcCtx c;
+    for (uint32_t t = blockIdx.x; t < 8u * per; t += gridDim.x) {
+        const uint32_t si = (t & 7u) * per + (t >> 3);
+        if (si >= n) continue;
+        const uint32_t q = a.srcq[b + si];
+        if (GEN && a.qs[q].direct) continue;   // answered by k_kcp_direct
+        if constexpr (Q && quad_stages<HB>()) {
+            if (nst != 0 && uni(q) != c.q) flush_stage(a, c, nst, L.stg, L.stu);
         }
-    } else {
-        wave_sync();
-        uint32_t tq = kInf;              // query of tseen
-        unsigned long long tseen = 0;    // its emitted count at this wave's last bound update
-        for (uint32_t t = blockIdx.x; t < 8u * per; t += gridDim.x) {
-            const uint32_t si = (t & 7u) * per + (t >> 3);
-            if (si >= n) continue;
-            if (GEN && a.qs[a.srcq[b + si]].direct) continue;   // answered by k_kcp_direct
-            SrcCtx c = load_ctx(a, a.srcq[b + si]);
-            if (!GEN) {
-                c.k = 0;
-                c.hist = nullptr;
-            }
-            if (c.q != tq) {
-                tq = c.q;
-                tseen = 0;
-            }
+        c = load_ctx<Q>(a, q);
+        if (!GEN) {
+            c.k = 0;
+            c.hist = nullptr;
+        }
+        if (c.q != tq) {
+            tq = c.q;
+            tseen = 0;
+        }
+        const int32_t u = a.src[b + si];
+        if constexpr (NW > 1) {
+            if constexpr (Q) search_quads_block<HB, CT>(L, B, a, c, u, tseen);
+            else search_source_block<HB, CT>(L, B, a, c, u, tseen);
+        } else {
             if (GEN && c.k != 0 && !a.count_work &&
-                static_cast<uint64_t>(current_bound(c)) < 2ull * static_cast<uint64_t>(c.wmin))
-                direct_pairs<HB, CT>(L, a, c, a.src[b + si], tseen);
-            else
-                search_source<HB, CT>(L, a, c, a.src[b + si], tseen);
+                static_cast<uint64_t>(current_bound(c)) < 2ull * static_cast<uint64_t>(c.wmin)) {
+                if constexpr (Q) {
+                    direct_pairs(a, c, u, L.ring, QTier<HB, CT>::RC, tseen);
+                    for (uint32_t i = threadIdx.x; i < QTier<HB, CT>::RC; i += 64) L.ring[i] = make_uint2(0u, 0u);
+                    wave_sync();
+                }
+                else direct_pairs(a, c, u, &L.lst[0][0], 2u * Tier<HB, CT>::PC, tseen);
+            } else if constexpr (Q) {
+                search_quads<HB, CT>(L, a, c, u, nst, tseen);
+            } else {
+                search_source<HB, CT>(L, a, c, u, tseen);
+            }
         }
     }
+    if constexpr (Q && quad_stages<HB>()) flush_stage(a, c, nst, L.stg, L.stu);
 }
 
 // ------------------------------------------------------------------ global-memory tier
@@ -1667,7 +2369,7 @@ __global__ __launch_bounds__(1024) void k_join_global(JoinArgs a, uint32_t *slot
                 unsigned long long base = 0;
                 if (lane == 0) {
                     base = atomicAdd(&a.ctl->npairs, static_cast<unsigned long long>(popc(mm)));
-                    atomicAdd(&c.qs->npairs, static_cast<unsigned long long>(popc(mm)));
+                    if (!a.one) atomicAdd(&c.qs->npairs, static_cast<unsigned long long>(popc(mm)));
                 }
                 const uint32_t lo = static_cast<uint32_t>(__shfl(static_cast<int>(base & 0xFFFFFFFFull), 0));
                 const uint32_t hi = static_cast<uint32_t>(__shfl(static_cast<int>(base >> 32), 0));
@@ -1979,7 +2681,7 @@ __global__ __launch_bounds__(256) void k_kcp_direct(JoinArgs a) {
         uint32_t lo = 0, hi = 0;
         if (static_cast<int>(lane) == first) {
             const unsigned long long w = atomicAdd(&a.ctl->npairs, static_cast<unsigned long long>(tot));
-            atomicAdd(&a.qs[q0].npairs, static_cast<unsigned long long>(tot));
+            if (!a.one) atomicAdd(&a.qs[q0].npairs, static_cast<unsigned long long>(tot));
             lo = static_cast<uint32_t>(w);
             hi = static_cast<uint32_t>(w >> 32);
         }
@@ -1989,7 +2691,7 @@ __global__ __launch_bounds__(256) void k_kcp_direct(JoinArgs a) {
     }
     if (act && !same && cnt != 0) {
         base = atomicAdd(&a.ctl->npairs, static_cast<unsigned long long>(cnt));
-        atomicAdd(&c.qs->npairs, static_cast<unsigned long long>(cnt));
+        if (!a.one) atomicAdd(&c.qs->npairs, static_cast<unsigned long long>(cnt));
     }
     if (!act || cnt == 0) return;
     unsigned long long idx = base;
@@ -2129,7 +2831,8 @@ __device__ __forceinline__ void layout_block(const CallBuffers &b, int selected,
         unsigned long long nsel = 0, nout = 0;
         if (valid) {
             const QueryDesc &d = b.qd[q];
-            const QueryState &st = b.qs[q];
+            QueryState &st = b.qs[q];
+            if (b.nq == 1) st.npairs = b.ctl->npairs;   // (counted for the call only)
             nsel = (selected && d.k) ? st.nsel : st.npairs;   // a theta-join keeps every record
             nout = st.err ? 0ull : (d.k ? min(nsel, static_cast<unsigned long long>(d.k)) : nsel);
             if (nsel) atomicMax(&s_dmax, d.k ? st.bound : d.theta);
@@ -2549,7 +3252,7 @@ int lds_resident_blocks(size_t lds, size_t lds_per_cu) {
     return static_cast<int>(lds_per_cu / ((lds + gran - 1) / gran * gran));
 }
 
-template <int HB, bool GEN, bool CT>
+template <int HB, bool GEN, bool CT, bool Q>
 hipError_t launch_join_tier(const JoinArgs &a, uint32_t max_sources, bool persistent, hipStream_t s) {
     static int resident = 0;  // blocks per CU, per device this process uses first
     static int cus = 0;
@@ -2561,10 +3264,10 @@ hipError_t launch_join_tier(const JoinArgs &a, uint32_t max_sources, bool persis
         e = hipGetDeviceProperties(&prop, dev);
         if (e != hipSuccess) return e;
         int occ = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_join<HB, GEN, CT>, 64 * Tier<HB, CT>::NW, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_join<HB, GEN, CT, Q>, 64 * join_waves<HB, CT, Q>(), 0);
         if (e != hipSuccess) return e;
         hipFuncAttributes fa;
-        e = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_join<HB, GEN, CT>));
+        e = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_join<HB, GEN, CT, Q>));
         if (e != hipSuccess) return e;
         cus = prop.multiProcessorCount;
         const int fit = lds_resident_blocks(fa.sharedSizeBytes, prop.maxSharedMemoryPerMultiProcessor);
@@ -2579,7 +3282,7 @@ hipError_t launch_join_tier(const JoinArgs &a, uint32_t max_sources, bool persis
     const uint64_t want = (static_cast<uint64_t>(max_sources) + 7) / 8 * 8;
     if (want < grid || !persistent) grid = want;
     if (grid == 0) grid = 8;
-    hipLaunchKernelGGL((k_join<HB, GEN, CT>), dim3(static_cast<uint32_t>(grid)), dim3(64 * Tier<HB, CT>::NW), 0, s, a);
+    hipLaunchKernelGGL((k_join<HB, GEN, CT, Q>), dim3(static_cast<uint32_t>(grid)), dim3(64 * join_waves<HB, CT, Q>()), 0, s, a);
     return hipGetLastError();
 }
 
@@ -2616,17 +3319,23 @@ hipError_t launch_stage(const CallBuffers &b, unsigned long long max_elems, cons
 int join_tier_supported(int hash_log2) { return hash_log2 >= kMinHB && hash_log2 <= kMaxHB; }
 
 
-hipError_t launch_join(const JoinArgs &a, int hash_log2, bool generic, bool compact, uint32_t max_sources,
+template <int HB, bool CT>
+static hipError_t launch_join_kind(const JoinArgs &a, bool generic, bool quads, uint32_t max_sources, bool persistent,
+                                   hipStream_t s) {
+    if (quads)
+        return generic ? launch_join_tier<HB, true, CT, true>(a, max_sources, persistent, s)
+                       : launch_join_tier<HB, false, CT, true>(a, max_sources, persistent, s);
+    if constexpr (CT && HB < kCompactMinHB) return hipErrorInvalidValue;
+    else return generic ? launch_join_tier<HB, true, CT, false>(a, max_sources, persistent, s)
+                   : launch_join_tier<HB, false, CT, false>(a, max_sources, persistent, s);
+}
+
+hipError_t launch_join(const JoinArgs &a, int hash_log2, bool generic, bool compact, bool quads, uint32_t max_sources,
                        bool persistent, hipStream_t s) {
 #define RN_TIER(HB)                                                                                   \
     case HB:                                                                                          \
-        if constexpr (HB >= kCompactMinHB) {                                                          \
-            if (compact)                                                                              \
-                return generic ? launch_join_tier<HB, true, true>(a, max_sources, persistent, s)      \
-                               : launch_join_tier<HB, false, true>(a, max_sources, persistent, s);    \
-        }                                                                                             \
-        return generic ? launch_join_tier<HB, true, false>(a, max_sources, persistent, s)             \
-                       : launch_join_tier<HB, false, false>(a, max_sources, persistent, s);
+        if (compact) return launch_join_kind<HB, true>(a, generic, quads, max_sources, persistent, s); \
+        return launch_join_kind<HB, false>(a, generic, quads, max_sources, persistent, s);
     switch (hash_log2) {
         RN_TIER(8)
         RN_TIER(9)
@@ -2638,6 +3347,59 @@ hipError_t launch_join(const JoinArgs &a, int hash_log2, bool generic, bool comp
         default: return hipErrorInvalidValue;
     }
 #undef RN_TIER
+}
+
+// The arc quads of every row (vertex, then the reversed ones, whose row pointers
+// follow one entry on), from the arc records: first every quad is filled with
+// padding (a target of its own, so that idle lanes address distinct slots, at
+// infinite weight), then with arcs.  A vertex of more than 4 arcs takes its
+// further quads from its graph's counter (their order does not matter) and
+// chains them.  voff and qbase: first vertex and first quad of each graph
+// (targets and chains are local).
+__global__ __launch_bounds__(256) void k_fill_quads(uint32_t nquads, uint2 *quads) {
+    const uint64_t i = blockIdx.x * 256ull + threadIdx.x;
+    if (i < 4ull * nquads) quads[i] = make_uint2(static_cast<uint32_t>(i >> 2) & (kCompactVertices - 1), kInf);
+}
+
+__global__ __launch_bounds__(256) void k_build_quads(const int32_t *row_ptr, const ArcRec *arcs, uint32_t *further,
+                                                     const int32_t *voff, const uint32_t *qbase, uint32_t *next,
+                                                     uint32_t ngr, uint32_t V, uint32_t rows, uint2 *quads) {
+    const uint32_t r = blockIdx.x * 256u + threadIdx.x;
+    if (r >= rows) return;
+    const uint32_t rev = r >= V ? 1u : 0u;
+    const int32_t v = static_cast<int32_t>(r - rev * V);
+    const int32_t b = row_ptr[r + rev], e = row_ptr[r + rev + 1];
+    const uint32_t gi = seg_of(voff, ngr, v);
+    const int32_t v0 = voff[gi];
+    const uint64_t q0 = qbase[rev * ngr + gi];
+    const uint32_t extra = static_cast<uint32_t>(row_quads(e - b)) - 1u;
+    const uint32_t first = extra ? static_cast<uint32_t>(voff[gi + 1] - v0) + atomicAdd(&next[rev * ngr + gi], extra) : 0u;
+    uint64_t q = q0 + static_cast<uint32_t>(v - v0);
+    for (int32_t x = b; x < e; ++x) {
+        const uint32_t i = static_cast<uint32_t>(x - b);
+        if (i != 0 && (i & 3u) == 0u) {
+            further[q] = first + i / 4u - 1u;
+            q = q0 + first + i / 4u - 1u;
+        }
+        const ArcRec t = arcs[x];
+        quads[4ull * q + (i & 3u)] = make_uint2(
+            static_cast<uint32_t>(t.y - v0) + (static_cast<uint32_t>(row_quads(t.yend - t.ybeg)) - 1u) * (kQuadId + 1u),
+            t.w);
+    }
+}
+
+hipError_t launch_build_quads(const int32_t *row_ptr, const ArcRec *arcs, uint32_t *further, const int32_t *voff,
+                              const uint32_t *qbase, uint32_t *next, uint32_t ngr, uint32_t dirs, uint32_t V,
+                              uint32_t nquads, uint2 *quads, hipStream_t s) {
+    const uint32_t rows = dirs * V;
+    if (rows == 0) return hipSuccess;
+    const hipError_t e = launch_fill_u32(next, dirs * ngr, 0u, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_fill_quads, dim3(static_cast<uint32_t>((4ull * nquads + 255u) / 256u)), dim3(256), 0, s, nquads,
+                       quads);
+    hipLaunchKernelGGL(k_build_quads, dim3((rows + 255u) / 256u), dim3(256), 0, s, row_ptr, arcs, further, voff, qbase,
+                       next, ngr, V, rows, quads);
+    return hipGetLastError();
 }
 
 hipError_t launch_join_global(const JoinArgs &a, uint32_t *slots, uint32_t nslots, int32_t Vmax,
