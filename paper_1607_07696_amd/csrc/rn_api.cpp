@@ -9,8 +9,12 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <string>
 #include <thread>
 #include <vector>
@@ -82,20 +86,101 @@ rn_status check_queries(const rn_graph *g, const rn_query *q, int32_t nq, int32_
     return RN_OK;
 }
 
+// A bound within which a k-closest-pairs query very likely has its k pairs (kInf:
+// none worth trying): with R and S spread over the same region, a ball of b
+// vertices around each u holds |R| |S| b / V pairs in all, and the radius of the
+// ball that holds half as many again as wanted (and a few standard deviations)
+// comes from radii measured when the graph was loaded.  The searches then stop
+// at it, where they would run on until the others' discoveries bound them; a
+// query that has fewer than k pairs within it is run again without a guess.
+// ball: the vertices expected within it.
+uint32_t guess_bound(const rn_graph *g, const rn_query &x, double *ball) {
+    const double V = static_cast<double>(g->voff[x.graph + 1] - g->voff[x.graph]);
+    const double k = static_cast<double>(x.k);
+    const double want = std::max(1.5 * k, k + 4.0 * std::sqrt(k)) + 8.0;
+    const double b = std::max(want * V / (static_cast<double>(x.nR) * x.nS), static_cast<double>(1 << kBallMinLog2));
+    if (!(8.0 * b <= V)) return kInf;
+    const double *r = g->radius.data() + static_cast<size_t>(x.graph) * kBalls;
+    const double l = std::log2(b) - kBallMinLog2;
+    const int i = std::min(static_cast<int>(l), kBalls - 1);
+    // between measured radii linear in the logarithm of the size, beyond the
+    // largest as the square root of the size
+    if (!(r[i] > 0)) return kInf;
+    double d;
+    if (i == kBalls - 1) {
+        d = r[i] * std::sqrt(std::exp2(l - i));
+    } else {
+        if (!(r[i + 1] > 0)) return kInf;
+        d = r[i] * std::pow(r[i + 1] / r[i], l - i);
+    }
+    if (!(d < 1e9)) return kInf;
+    if (ball) *ball = b;
+    return static_cast<uint32_t>(d) + 1u;
+}
+
+// Mean distances within which 2^3 .. 2^9 vertices lie, over a few vertices of
+// graph i spread over its numbering (0: not reached).
+// dist: per vertex 1 + tentative distance, all 0 before and after.
+void measure_radii(rn_graph *g, int32_t i, uint64_t *dist) {
+    constexpr int kSamples = 4;
+    const int32_t vo = g->voff[i], V = g->voff[i + 1] - vo;
+    double *r = g->radius.data() + static_cast<size_t>(i) * kBalls;
+    int reached[kBalls] = {};
+    std::vector<std::pair<uint64_t, int32_t>> heap;
+    std::vector<int32_t> touched;
+    for (int smp = 0; smp < kSamples; ++smp) {
+        const int32_t s = vo + static_cast<int32_t>((2 * smp + 1) * static_cast<int64_t>(V) / (2 * kSamples));
+        heap.assign(1, {0, s});
+        touched.assign(1, s);
+        dist[s] = 1;
+        int32_t settled = 0;
+        const auto later = [](const std::pair<uint64_t, int32_t> &a, const std::pair<uint64_t, int32_t> &b) { return a > b; };
+        while (!heap.empty() && settled < (1 << (kBallMinLog2 + kBalls - 1))) {
+            std::pop_heap(heap.begin(), heap.end(), later);
+            const auto [d, x] = heap.back();
+            heap.pop_back();
+            if (d + 1 != dist[x]) continue;
+            ++settled;
+            for (int b = 0; b < kBalls; ++b)
+                if (settled == (1 << (kBallMinLog2 + b))) {
+                    r[b] += static_cast<double>(d);
+                    ++reached[b];
+                }
+            for (int32_t a = g->row_ptr[x]; a < g->row_ptr[x + 1]; ++a) {
+                const int32_t y = g->col[a];
+                const uint64_t nd = d + g->w[a];
+                if (dist[y] != 0 && nd + 1 >= dist[y]) continue;
+                if (dist[y] == 0) touched.push_back(y);
+                dist[y] = nd + 1;
+                heap.push_back({nd, y});
+                std::push_heap(heap.begin(), heap.end(), later);
+            }
+        }
+        for (int32_t x : touched) dist[x] = 0;
+    }
+    for (int b = 0; b < kBalls; ++b) r[b] = reached[b] == kSamples ? r[b] / kSamples : 0.0;
+}
+
 // First on-chip table of a query when the caller set none: for a theta-join the
 // smallest whose fill limit (3/4) holds the expected ball (about
 // 2 (theta / mean arc weight)^2 vertices on a planar road graph) with a margin of
 // 1.3; balls of less than 2^11 slots vary more and take 1.8.  (Over quads only:
 // the window search keeps 2^11 as its smallest.  32 768 searches of 66 vertices:
 // 153 us with 2^8 slots, 384 with 2^11.)  A larger ball overflows the table and
-// is searched again.
-int first_table(const rn_graph *g, const rn_query &x) {
+// is searched again.  A k-closest-pairs query whose searches start from a guess
+// takes the ball expected within it.
+int first_table(const rn_graph *g, const rn_query &x, bool guesses) {
     if (x.k == 0 && !g->hash_auto) return g->hash_log2;
     const bool quads = g->quads && (x.delta == RN_DELTA_DEFAULT ? g->delta : x.delta) == 0;
     const double r = static_cast<double>(x.theta) / std::max(1.0, g->wmean[x.graph]);
     auto fits = [&](int hb, double ball) { return static_cast<double>(1u << hb) >= ball / 0.75; };
     int hb = kMinHB;
-    if (x.k > 0) return hb;
+    if (x.k > 0) {
+        double ball = 0;
+        if (!quads || !guesses || guess_bound(g, x, &ball) == kInf) return hb;
+        while (hb < kMaxHB && !fits(hb, 1.8 * ball)) ++hb;
+        return hb;
+    }
     if (quads)
         while (hb < 11 && !fits(hb, 1.8 * 2.0 * r * r)) ++hb;
     else
@@ -132,7 +217,7 @@ uint32_t ring_slack(double wmean) {
     return s >= 2147483647.0 ? 0x7FFFFFFFu : static_cast<uint32_t>(s + 0.5);
 }
 
-rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p) {
+rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p, bool guesses) {
     // reset in place: the vectors keep their capacity, so a Prepared reused for
     // calls of the same shape allocates nothing after its first call
     auto qd = std::move(p.qd);
@@ -150,6 +235,7 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p)
     p.binbase = std::move(binbase);
     p.groups.clear();
     p.nq = nq;
+    p.guesses = guesses;
     p.qd.resize(nq);
     p.ebase.assign(nq + 1, 0);
     p.rbase.assign(nq + 1, 0);
@@ -159,7 +245,7 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p)
     for (int32_t i = 0; i < nq; ++i) {
         const rn_query &x = q[i];
         hb[i] = x.hash_log2 ? x.hash_log2
-                            : (sure_global(g, x) ? kGlobalHB : first_table(g, x));
+                            : (sure_global(g, x) ? kGlobalHB : first_table(g, x, guesses));
         p.any_kcp |= x.k > 0;
         dmax = std::max(dmax, x.theta);
         p.total_R += static_cast<uint64_t>(std::max(x.nR, 0));
@@ -223,6 +309,7 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p)
         d.gdelta = g->gdelta[x.graph];
         d.wmin = g->w_min[x.graph];
         d.slack = ring_slack(g->wmean[x.graph]);
+        d.guess = x.k > 0 && guesses && hb[i] != kGlobalHB ? guess_bound(g, x, nullptr) : kInf;
         d.sbits = static_cast<uint32_t>(sw);
         d.rbits = static_cast<uint32_t>(rw);
         d.hist = x.k ? nkcp * kHistWords : 0;
@@ -238,20 +325,22 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p)
         Group &gr = p.groups.back();
         gr.kcp = gr.kcp || x.k > 0;
         gr.end = s + 1;
-        gr.ring = gr.ring && d.delta == 0;
-        gr.sized = gr.sized && x.k == 0 && x.hash_log2 == 0 && g->hash_auto;
-        p.all_ring = p.all_ring && d.delta == 0;
+        // k-closest pairs search over quads where a guess bounds them from the start
+        const bool quads = g->quads && d.delta == 0 && (x.k == 0 || d.guess != kInf);
+        gr.quads = gr.quads && quads;
+        p.all_quads = p.all_quads && quads;
+        gr.sized = gr.sized && x.hash_log2 == 0 && (x.k > 0 ? d.guess != kInf : g->hash_auto);
         gr.sources += static_cast<uint64_t>(d.nR);
         // compact tables: local ids below 2^24, and (theta-joins) every
         // distance within theta fits the compact word; a k-closest-pairs
         // search whose bound is larger moves on if it meets such a distance
         // (the compact 2^11 search's lists hold 64 entries: with buckets, delta
         // > 0, too few for its pending sets, so such groups keep wide tables)
-        const bool quads = g->quads && d.delta == 0 && x.k == 0;
         gr.compact = gr.compact && (quads || hb[i] >= kCompactMinHB) && hb[i] <= kMaxHB && g->Vmax < kCompactVertices &&
                      (hb[i] != kCompactSmallRingHB || d.delta == 0) &&
                      (quads || g->A * (g->rev_rpo ? 2 : 1) < static_cast<int64_t>(kCompactArcs)) &&
-                     ((x.k > 0 && hb[i] >= kCompactMinHB) || x.theta <= compact_max_dist(hb[i]));
+                     ((x.k > 0 && hb[i] >= kCompactMinHB) ||
+                      (x.k > 0 ? std::min(x.theta, d.guess) : x.theta) <= compact_max_dist(hb[i]));
     }
     p.rbase[nq] = static_cast<uint32_t>(rw);
     p.total_elems = p.ebase[nq];
@@ -538,7 +627,7 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
             t.novf = &b.ctl->nlist[li];
             t.first_tier = 1;
             t.tier = 0;
-            RN_HIP(launch_join(t, hbt, gr.kcp, gr.compact, g->quads && gr.ring && !gr.kcp, static_cast<uint32_t>(gr.sources),
+            RN_HIP(launch_join(t, hbt, gr.kcp, gr.compact, gr.quads, static_cast<uint32_t>(gr.sources),
                                !shared, on_chip_stream(gi)),
                    "launching the relaxation");
         }
@@ -566,7 +655,7 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
         // the re-run tiers take wide tables: they must hold any search the
         // first tiers sent on, whatever its distances (a compact 2^14 re-run
         // could only send those on to the global tier)
-        RN_HIP(launch_join(t, li == 0 ? kRetryHB1 : kMaxHB, true, false, g->quads && p.all_ring && !p.any_kcp, maxs, !shared, s),
+        RN_HIP(launch_join(t, li == 0 ? kRetryHB1 : kMaxHB, true, false, p.all_quads, maxs, !shared, s),
                "launching the relaxation");
     }
     if (gside) RN_HIP(hipStreamWaitEvent(s, ws.join[0], 0), "joining streams");   // the early global launch
@@ -637,12 +726,14 @@ float elapsed(const rn_graph *g, const Workspace &ws, int a, int b) {
 // Turn the read-back state into offsets / status / the return code (after
 // the radix sort of a bucket-sorted call that found an oversized bin).
 // Sets *regrow when the call must run again (records outgrew the buffer, or
-// a search needed global-tier slots that did not exist yet).
+// a search needed global-tier slots that did not exist yet), and *unmet with it
+// when that is to be without guessed bounds.
 rn_status finish(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, int64_t *offsets,
-                 int32_t *status, bool timed, bool *regrow, hipStream_t s) {
+                 int32_t *status, bool timed, bool *regrow, bool *unmet, hipStream_t s) {
     const CallCtl &c = *reinterpret_cast<const CallCtl *>(ws.h_state);
     const QueryState *qs = reinterpret_cast<const QueryState *>(ws.h_state + sizeof(CallCtl));
     *regrow = false;
+    *unmet = false;
     if (c.nlist[2] > 0 && !ws.d_gslots) {
         // some search needed the global tier, which had no slots yet
         *regrow = true;
@@ -653,6 +744,11 @@ rn_status finish(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, in
         RN_TRY(grow_recs(ws, c.npairs));
     }
     if (*regrow) return RN_OK;
+    if (c.unmet) {
+        *regrow = true;
+        *unmet = true;
+        return RN_OK;
+    }
     if (c.resort) {
         RN_TRY(enqueue_sort_fallback(ws, p, out, cap, s));
         RN_HIP(hipStreamSynchronize(s), "waiting for the sort");
@@ -694,19 +790,20 @@ rn_status finish(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, in
     return RN_OK;
 }
 
-// One eager call on workspace ws (prepared p); retries when the record buffer
-// was too small.
-rn_status run_eager(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, int64_t *offsets,
-                    int32_t *status, hipStream_t s, bool timed) {
-    RN_TRY(ensure_buffers(ws, p));
-    for (int attempt = 0; attempt < 4; ++attempt) {
+// One eager call on workspace ws (prepared p, from the queries q); retries when
+// the record buffer was too small, and without guesses when one was not met.
+rn_status run_eager(rn_graph *g, Workspace &ws, Prepared &p, const rn_query *q, rn_pair *out, int64_t cap,
+                    int64_t *offsets, int32_t *status, hipStream_t s, bool timed) {
+    for (int attempt = 0; attempt < 5; ++attempt) {
+        RN_TRY(ensure_buffers(ws, p));
         fill_host_desc(p, ws.h_desc);
         RN_HIP(hipMemcpyAsync(ws.d_desc, ws.h_desc, p.desc_bytes, hipMemcpyHostToDevice, s), "uploading queries");
         RN_TRY(enqueue_call(g, ws, p, out, cap, s, timed));
         RN_TRY(read_back(ws, p, s));
-        bool regrow = false;
-        const rn_status st = finish(g, ws, p, out, cap, offsets, status, timed, &regrow, s);
+        bool regrow = false, unmet = false;
+        const rn_status st = finish(g, ws, p, out, cap, offsets, status, timed, &regrow, &unmet, s);
         if (!regrow) return st;
+        if (st == RN_OK && unmet) RN_TRY(prepare(g, q, p.nq, p, false));
     }
     return fail(RN_ERR_NOMEM, "record buffer did not settle");
 }
@@ -718,7 +815,7 @@ rn_status run_batch(rn_graph *g, const rn_query *q, int32_t nq, rn_pair *out, in
     RN_HIP(hipSetDevice(g->device), "selecting the device");
     Prepared p;
     RN_TRY(prepare(g, q, nq, p));
-    return run_eager(g, g->ws, p, out, cap, offsets, status, s, true);
+    return run_eager(g, g->ws, p, q, out, cap, offsets, status, s, true);
 }
 
 rn_status run_single(rn_graph *g, const int32_t *R, int32_t nR, const int32_t *S, int32_t nS, uint32_t theta,
@@ -949,6 +1046,8 @@ rn_status rn_graph_load_many(int32_t n, const int32_t *V, const int64_t *A, cons
         delete g;
         return hip_fail(e, "no HIP device");
     }
+    // scratch of measure_radii, which touches little of it (calloc gives pages on first use)
+    std::unique_ptr<uint64_t, decltype(&std::free)> dist(nullptr, &std::free);
     g->ngraphs = n;
     g->V = static_cast<int32_t>(totV);
     g->A = totA;
@@ -959,6 +1058,9 @@ rn_status rn_graph_load_many(int32_t n, const int32_t *V, const int64_t *A, cons
         g->gdelta.assign(n, 1);
         g->wmean.assign(n, 1.0);
         g->varied.assign(n, 0);
+        g->radius.assign(static_cast<size_t>(n) * kBalls, 0.0);
+        dist.reset(static_cast<uint64_t *>(std::calloc(static_cast<size_t>(totV), sizeof(uint64_t))));
+        if (!dist) throw std::bad_alloc();
         g->row_ptr.resize(static_cast<size_t>(totV) + 1);
         g->col.resize(static_cast<size_t>(totA));
         g->w.resize(static_cast<size_t>(totA));
@@ -972,7 +1074,7 @@ rn_status rn_graph_load_many(int32_t n, const int32_t *V, const int64_t *A, cons
         g->voff[i + 1] = vo + V[i];
         g->aoff[i + 1] = ao + A[i];
         g->Vmax = std::max(g->Vmax, V[i]);
-        for (int32_t x = 0; x < V[i]; ++x) g->row_ptr[vo + x] = static_cast<int32_t>(ao + row_ptr[i][x]);
+        for (int32_t x = 0; x <= V[i]; ++x) g->row_ptr[vo + x] = static_cast<int32_t>(ao + row_ptr[i][x]);
         uint32_t wm = A[i] ? 0xFFFFFFFFu : 0u;
         for (int64_t a = 0; a < A[i]; ++a) {
             g->col[ao + a] = vo + col[i][a];
@@ -990,6 +1092,12 @@ rn_status rn_graph_load_many(int32_t n, const int32_t *V, const int64_t *A, cons
             for (int64_t a = 0; a < A[i] && seen.size() < 16; ++a)
                 if (std::find(seen.begin(), seen.end(), w[i][a]) == seen.end()) seen.push_back(w[i][a]);
             g->varied[i] = seen.size() >= 16 ? 1 : 0;
+        }
+        try {
+            measure_radii(g, i, dist.get());
+        } catch (...) {
+            delete g;
+            return fail(RN_ERR_NOMEM, "measuring the graph");
         }
         const double gd = 8.0 * g->wmean[i];
         g->gdelta[i] = static_cast<uint32_t>(std::min(std::max(gd, 1.0), 2147483648.0));
@@ -1414,11 +1522,11 @@ rn_status rn_autotune(rn_graph *g, rn_query *q, int32_t nq, int32_t sample, void
                 t.delta = di < 3 ? deltas[di] : g->delta;
                 t.hash_log2 = di < 3 ? hbs[hi] : kGlobalHB;
                 Prepared p;
-                result = prepare(g, &t, 1, p);
+                result = prepare(g, &t, 1, p, false);   // (a guess would hide what the setting costs)
                 if (result != RN_OK) break;
                 float ms = 3.4e38f;
                 for (int rep = 0; rep < 3 && result == RN_OK; ++rep) {
-                    result = run_eager(g, g->ws, p, nullptr, 0, nullptr, nullptr, s, true);
+                    result = run_eager(g, g->ws, p, &t, nullptr, 0, nullptr, nullptr, s, true);
                     if (result == RN_ERR_CAPACITY) result = RN_OK;   // counts only: no output wanted
                     if (result == RN_ERR_ARG) {
                         result = RN_OK;   // invalid node sets: keep the defaults for this query
@@ -1476,8 +1584,8 @@ rn_status capture_plan(rn_plan *pl, const Prepared &p) {
 }
 
 // Eager run to size the buffers, then capture.
-rn_status plan_build(rn_plan *pl, const Prepared &p, hipStream_t s, int64_t *offsets, int32_t *status) {
-    const rn_status st = run_eager(pl->g, pl->ws, p, pl->out, pl->cap, offsets, status, s, false);
+rn_status plan_build(rn_plan *pl, Prepared &p, hipStream_t s, int64_t *offsets, int32_t *status) {
+    const rn_status st = run_eager(pl->g, pl->ws, p, pl->q.data(), pl->out, pl->cap, offsets, status, s, false);
     if (st != RN_OK && st != RN_ERR_CAPACITY && st != RN_ERR_ARG) return st;
     RN_TRY(capture_plan(pl, p));
     return st;
@@ -1528,12 +1636,13 @@ rn_status rn_plan_run(rn_plan *pl, int64_t *offsets, int32_t *status, void *stre
     if (!guard.ok) return fail(RN_ERR_BUSY, "handle in use by another call");
     RN_HIP(hipSetDevice(g->device), "selecting the device");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const Prepared &p = pl->prep;
+    Prepared &p = pl->prep;
     RN_HIP(hipGraphLaunch(pl->exec, s), "launching the graph");
     RN_TRY(read_back(pl->ws, p, s));
-    bool regrow = false;
-    const rn_status st = finish(g, pl->ws, p, pl->out, pl->cap, offsets, status, false, &regrow, s);
+    bool regrow = false, unmet = false;
+    const rn_status st = finish(g, pl->ws, p, pl->out, pl->cap, offsets, status, false, &regrow, &unmet, s);
     if (!regrow) return st;
+    if (st == RN_OK && unmet) RN_TRY(prepare(g, pl->q.data(), p.nq, p, false));   // (from now on)
     // the records outgrew the buffer (grown by finish): run eagerly, re-capture
     return plan_build(pl, p, s, offsets, status);
 }

@@ -58,6 +58,10 @@ enum { EV_START, EV_STAGED, EV_TIER0, EV_RELAXED, EV_SELECTED, EV_DONE, EV_COUNT
 constexpr int kSide = 2 * (kMaxHB - kMinHB + 1) - 1;   // side streams: one per first-tier launch beyond the first
 constexpr unsigned long long kRecCapMax = 1ull << 31;
 
+// Ball sizes whose radii are measured when a graph is loaded (2^3 .. 2^9 vertices).
+constexpr int kBallMinLog2 = 3;
+constexpr int kBalls = 7;
+
 inline size_t round_up(size_t x, size_t m) { return (x + m - 1) / m * m; }
 
 inline uint32_t bitlen(uint64_t x) {
@@ -129,8 +133,8 @@ struct Group {
     int hb;
     bool kcp;               // some query of the group asks for k closest pairs
     bool compact;           // its launch uses compact on-chip tables
-    bool ring;              // no query of the group has buckets (delta = 0)
-    bool sized;             // theta-joins whose table was chosen for their balls: the few searches
+    bool quads;             // its launch searches over arc quads
+    bool sized;             // queries whose table was chosen for their balls: the few searches
                             // that outgrow it go on to the largest table at once
     int32_t first;          // staging positions [first, end)
     int32_t end;
@@ -148,7 +152,8 @@ struct Prepared {
     bool any_kcp = false;
     bool need_list0 = false;
     bool need_list1 = false;
-    bool all_ring = true;           // no query of the call has buckets (delta = 0)
+    bool all_quads = true;          // every query's first searches are over arc quads
+    bool guesses = true;            // k-closest-pairs queries may start from a guessed bound
     bool any_global = false;        // a first-tier group runs in the global tier
     uint32_t qb = 0, vb = 1, max_passes = 1;
     uint64_t total_R = 0;
@@ -168,7 +173,10 @@ struct Prepared {
 std::string describe_err(uint32_t err);
 // Host-side checks of a batch (status[i] marks the malformed queries).
 rn_status check_queries(const rn_graph *g, const rn_query *q, int32_t nq, int32_t *status);
-rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p);
+// guesses: k-closest-pairs searches may start from a guessed bound; a call whose
+// state then reports an unmet guess (ctl.unmet) is prepared again without them
+// and run again.
+rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p, bool guesses = true);
 // Global-tier slots are allocated on demand: a call enqueued while a
 // workspace has none skips the global tier, and if any of its searches needed
 // it (ctl.nlist[2] > 0) the call is run again once slots exist.  Allocate (once)
@@ -234,6 +242,7 @@ struct rn_graph {
     int hash_log2 = 11;
     bool hash_auto = true;          // no first table size set: theta-joins size it from theta
     std::vector<double> wmean;      // per graph: mean arc weight
+    std::vector<double> radius;     // per graph: mean distance within which kBalls vertices lie
     std::vector<char> varied;       // per graph: at least 16 distinct arc weights
 
     rn::host::Workspace ws;

@@ -72,7 +72,7 @@ struct QueryDesc {
     uint32_t slack;             // delta = 0: a step of the on-chip search puts back the vertices
                                 // more than this above its least distance (kInf: none)
     uint32_t quads;             // first arc quad of the (reversed) graph searched
-    uint32_t pad;
+    uint32_t guess;             // k > 0: bound the searches start from (kInf: none), see guess_bound
 };
 static_assert(sizeof(QueryDesc) == 80, "QueryDesc is 80 bytes");
 constexpr uint32_t kOrientSwap = 1u << 31;
@@ -90,7 +90,8 @@ struct QueryState {
     unsigned long long start;   // first kept record of the query in the sorted order
     unsigned long long nout;    // pairs written for the query
     unsigned long long off;     // first output position of the query
-    unsigned long long pad2;
+    uint32_t guessed;           // k > 0: the searches started from the query's guess
+    uint32_t pad2;
 };
 static_assert(sizeof(QueryState) == 64, "QueryState is 64 bytes");
 
@@ -110,8 +111,11 @@ struct CallCtl {
     uint32_t nchunks;           // bucket sort: 64-record chunks over all bins
     uint32_t resort;            // the call's sort left the output to the radix sort (a bucket-sort bin
                                 //   above kBucketRankMax records, or more than kSmallSort candidates)
+    uint32_t unmet;             // a k-query found fewer than k pairs within its guess: the call is to be
+                                //   run again without guesses
+    uint32_t pad;
 };
-static_assert(sizeof(CallCtl) == 80, "CallCtl is 80 bytes");
+static_assert(sizeof(CallCtl) == 88, "CallCtl is 88 bytes");
 
 // One emitted (u, v, dist) of query q, ids local to the query's graph.
 struct alignas(16) Rec {

@@ -396,6 +396,7 @@ struct SrcCtx {
     uint32_t *hist;                 // k > 0: the query's histogram region (else null)
     QueryState *qs;                 // the query's state
     const unsigned long long *npairs;   // records the query has emitted
+    bool guessed;                   // the searches start from a guessed bound
 };
 
 __device__ __forceinline__ uint32_t uni(uint32_t v) {
@@ -430,6 +431,7 @@ __device__ __forceinline__ SrcCtx load_ctx(const JoinArgs &a, uint32_t q0) {
     c.sbits = a.sbits + same(d.sbits);
     c.hist = c.k ? a.hists + same(d.hist) : nullptr;
     c.qs = a.qs + q;
+    c.guessed = c.k != 0 && c.qs->guessed != 0;
     c.npairs = a.one ? &a.ctl->npairs : &a.qs[q].npairs;
     return c;
 }
@@ -1325,16 +1327,17 @@ constexpr uint32_t quad_dist_shift() {
     else return 1u;
 }
 
-// Write the n <= 64 staged pairs of query c.  Whole wave.
-__device__ __forceinline__ void flush_stage(const JoinArgs &a, const SrcCtx &c, uint32_t &n, const uint2 *stg,
-                                            const int32_t *stu) {
-    if (n == 0) return;
+// Write the n <= 64 staged pairs of query c.  Whole wave.  Returns the call's
+// records so far.
+__device__ __forceinline__ unsigned long long flush_stage(const JoinArgs &a, const SrcCtx &c, uint32_t &n,
+                                                          const uint2 *stg, const int32_t *stu) {
+    if (n == 0) return 0;
     const uint32_t i = min(lane_id(), n - 1u);
     wave_sync();
     const uint2 e = stg[i];
     const int32_t us = stu[i];
     const int32_t from = caller_id(a, us, c.voff), to = caller_id(a, static_cast<int32_t>(e.y), c.voff);
-    const unsigned long long idx = reserve_recs(a, c, n) + lane_id();
+    const unsigned long long base = reserve_recs(a, c, n), idx = base + lane_id(), total = base + n;
     if (lane_id() < n && idx < a.rec_cap) {
         Rec r;
         r.u = c.swapped ? to : from;
@@ -1346,6 +1349,7 @@ __device__ __forceinline__ void flush_stage(const JoinArgs &a, const SrcCtx &c, 
     }
     wave_sync();
     n = 0;
+    return total;
 }
 
 // The end of a search over quads from u: stage the table entries in S (none when
@@ -1393,9 +1397,11 @@ __device__ __forceinline__ void quad_emit(QuadLds<HB, CT, true> &L, const JoinAr
     }
     if (c.k) {
         // k-closest pairs: counted at once, for the bound
+        // (within a guess there is little to lower until far more than k are
+        // there: then the count that the flush returns spares reading it)
         emitted += nst - before;
-        flush_stage(a, c, nst, L.stg, L.stu);
-        if (emitted != 0) tighten_bound(c, tseen);
+        const unsigned long long total = flush_stage(a, c, nst, L.stg, L.stu);
+        if (emitted != 0 && !(c.guessed && a.one && total < 2ull * c.k)) tighten_bound(c, tseen);
     }
     if (a.count_work && !ovf) {
         for (int o = 32; o > 0; o >>= 1) {
@@ -1701,15 +1707,18 @@ __device__ __forceinline__ void probe_step(const SrcCtx &c, uint32_t n, uint32_t
 // The bound and the count are read every kPoll steps, and used a step later, so
 // that no step waits for them.
 constexpr uint32_t kPoll = 2;
+constexpr uint32_t kPollGuessed = 8;
 __device__ __forceinline__ void poll_bound(const SrcCtx &c, uint32_t &phase, uint32_t &nbound, uint32_t &ncount,
                                            uint32_t &bound, uint32_t &pnew, bool &probing, uint32_t &seen) {
-    // small searches (the first two steps) never count discoveries
-    if (phase >= 2 && phase % kPoll == 0) {
+    // small searches (the first two steps) never count discoveries, and those
+    // that start from a guess hardly gain from it
+    const uint32_t first = c.guessed ? kPollGuessed : 2u;
+    if (phase >= first && phase % kPoll == 0) {
         bound = min(uni(nbound), c.theta);
         probe_step(c, uni(ncount), pnew, probing, seen);
     }
     ++phase;
-    if (phase >= 2 && phase % kPoll == 0) {
+    if (phase >= first && phase % kPoll == 0) {
         nbound = __hip_atomic_load(&c.qs->bound, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         ncount = __hip_atomic_load(probe_count(c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -1747,7 +1756,8 @@ __device__ void search_quads(QuadLds<HB, CT> &L, const JoinArgs &a, const SrcCtx
     st.probing = false;
     uint32_t head = 0, seen = 0, phase = 0;
     uint32_t bound = uni(current_bound(c)), nbound = bound, ncount = 0;
-    if (c.hist != nullptr) ncount = __hip_atomic_load(probe_count(c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (c.hist != nullptr && !c.guessed)
+        ncount = __hip_atomic_load(probe_count(c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     while (true) {
         head = uni(head);
         const uint32_t np = st.tail - head;
@@ -1893,7 +1903,8 @@ __device__ void search_quads_block(QuadLds<HB, CT> &L, QuadBlock &B, const JoinA
     st.probing = false;
     uint32_t seen = 0, phase = 0, head = 0, s0 = 0;
     uint32_t bound = uni(current_bound(c)), nbound = bound, ncount = 0;
-    if (c.hist != nullptr) ncount = __hip_atomic_load(probe_count(c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (c.hist != nullptr && !c.guessed)
+        ncount = __hip_atomic_load(probe_count(c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     bool ovf = false;
     while (true) {
         const uint32_t s1 = s0 == 2 ? 0u : s0 + 1u, s2 = s1 == 2 ? 0u : s1 + 1u;
@@ -2600,9 +2611,11 @@ __global__ __launch_bounds__(64) void k_kcp_seed_bound(const QueryDesc *qd, Quer
                                                        int allow_direct) {
     const QueryDesc &d = qd[blockIdx.x];
     if (d.k == 0) return;
-    const uint32_t b = min(wave_bound_from_hist(hists + d.hist + kHistSeed, d.k), d.theta);
+    const uint32_t sure = min(wave_bound_from_hist(hists + d.hist + kHistSeed, d.k), d.theta);
+    const uint32_t b = min(sure, d.guess);
     if (threadIdx.x == 0) {
         qs[blockIdx.x].bound = b;
+        qs[blockIdx.x].guessed = b < sure ? 1u : 0u;
         qs[blockIdx.x].direct =
             allow_direct && static_cast<uint64_t>(b) < 2ull * static_cast<uint64_t>(d.wmin) ? 1u : 0u;
     }
@@ -2834,6 +2847,8 @@ __device__ __forceinline__ void layout_block(const CallBuffers &b, int selected,
             QueryState &st = b.qs[q];
             if (b.nq == 1) st.npairs = b.ctl->npairs;   // (counted for the call only)
             nsel = (selected && d.k) ? st.nsel : st.npairs;   // a theta-join keeps every record
+            // every pair within the guess was found, but not k of them
+            if (d.k && st.guessed && !st.err && nsel < d.k) b.ctl->unmet = 1u;
             nout = st.err ? 0ull : (d.k ? min(nsel, static_cast<unsigned long long>(d.k)) : nsel);
             if (nsel) atomicMax(&s_dmax, d.k ? st.bound : d.theta);
         }

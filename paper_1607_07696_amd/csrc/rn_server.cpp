@@ -253,7 +253,19 @@ bool progress_lane(rn_server *s, Lane &L) {
             else L.out_cap = cap;
             rerun = true;
         }
-        if (rerun && st == RN_OK && ++L.reruns <= 3) {
+        if (!rerun && c.unmet) {
+            // a k-query had fewer than k pairs within its guess: again without guesses
+            st = prepare(s->g, L.q.data(), static_cast<int32_t>(L.q.size()), L.prep, false);
+            if (st == RN_OK) st = ensure_buffers(L.ws, L.prep);
+            if (st == RN_OK) {
+                fill_host_desc(L.prep, L.ws.h_desc);
+                const hipError_t ec = hipMemcpyAsync(L.ws.d_desc, L.ws.h_desc, L.prep.desc_bytes, hipMemcpyHostToDevice,
+                                                     L.stream);
+                if (ec != hipSuccess) st = hip_fail(ec, "uploading queries");
+            }
+            rerun = true;
+        }
+        if (rerun && st == RN_OK && ++L.reruns <= 4) {
             {
                 std::lock_guard<std::mutex> lk(s->mu);
                 s->stats.reruns += 1;
