@@ -573,6 +573,7 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
     a.count_work = g->count_work ? 1 : 0;
     a.big_deg = g->big_deg ? 1 : 0;
     a.order = g->d_order;
+    a.rank = g->d_rank;
     a.first = g->d_first;
     a.quads = g->d_quads;
     a.further = g->d_further;
@@ -615,7 +616,11 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
             hipStream_t st = gside ? ws.side[0] : s;
             t.tier = 3;
             t.work = ws.d_block + p.off_work + 32;
-            RN_HIP(launch_join_global(t, ws.d_gslots, ws.n_gslots, g->Vmax, static_cast<uint32_t>(gr.sources), st),
+            t.ovf = b.list[3];
+            t.ovfq = b.listq[3];
+            t.novf = &b.ctl->nlist[3];
+            RN_HIP((g->dense ? launch_join_dense : launch_join_global)(t, ws.d_gslots, ws.n_gslots, g->Vmax,
+                                                                        static_cast<uint32_t>(gr.sources), st),
                    "launching the global relaxation");
         } else {
             // (without global-tier slots yet, a global group takes the largest
@@ -667,6 +672,17 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
         t.send = &b.ctl->nlist[2];
         t.tier = 3;
         t.work = ws.d_block + p.off_work;
+        if (g->dense) {
+            t.ovf = b.list[3];
+            t.ovfq = b.listq[3];
+            t.novf = &b.ctl->nlist[3];
+            RN_HIP(launch_join_dense(t, ws.d_gslots, ws.n_gslots, g->Vmax, maxs, s), "launching the global relaxation");
+            t.src = b.list[3];
+            t.srcq = b.listq[3];
+            t.send = &b.ctl->nlist[3];
+            t.work = ws.d_block + p.off_work + 16;
+            t.tier = 4;   // (each tier's discoveries are counted apart: a re-run would count a pair twice)
+        }
         RN_HIP(launch_join_global(t, ws.d_gslots, ws.n_gslots, g->Vmax, maxs, s), "launching the global relaxation");
     }
     record(g, ws, timed, EV_RELAXED, s);
@@ -896,6 +912,13 @@ void choose_quads(rn_graph *g, const std::vector<int32_t> &rrow) {
     }
     g->qbase[static_cast<size_t>(dirs) * g->ngraphs] = static_cast<uint32_t>(n);
     g->quads = n < 0x7FFFFFFFLL && 8 * n <= 3 * g->A * dirs;
+    g->dense = g->quads;
+    for (int32_t i = 0; i < g->ngraphs; ++i) {
+        // a shortest path has at most V - 1 arcs
+        uint32_t wmax = 0;
+        for (int64_t a = g->aoff[i]; a < g->aoff[i + 1]; ++a) wmax = std::max(wmax, g->w[a]);
+        g->dense = g->dense && static_cast<uint64_t>(wmax) * (g->voff[i + 1] - g->voff[i]) < 0x7FFFFFFEull;
+    }
 }
 
 // Lay out the device copy's arcs as quads.

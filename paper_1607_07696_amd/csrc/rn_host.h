@@ -226,6 +226,7 @@ struct rn_graph {
     rn::ArcRec *d_arcs = nullptr;
     // Arc quads (graphs whose degrees suit them):
     bool quads = false;
+    bool dense = false;             // quads, and no shortest path is longer than 31 bits hold
     std::vector<uint32_t> qbase;    // first quad of each graph, then of each reversed graph, then their number
     uint2 *d_quads = nullptr;
     uint32_t *d_further = nullptr;  // per quad: the next quad of its vertex (of more than 4 arcs)

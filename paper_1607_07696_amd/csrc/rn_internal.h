@@ -23,14 +23,15 @@ enum : uint32_t {
 // the two fixed re-run sizes: a search that outgrows its first table is re-run
 // with a 2^11-slot table when it started below that, else with 2^14 slots; one
 // that outgrows 2^14 slots moves to the global-memory tier, which takes any
-// search.  Re-run lists: 0 -> 2^11, 1 -> 2^14, 2 -> global.
+// search.  Re-run lists: 0 -> 2^11, 1 -> 2^14, 2 -> global, 3 -> global after the
+// global tier over quads.
 constexpr int kMinHB = 8;
 constexpr int kMaxHB = 14;
 constexpr int kRetryHB1 = 11;
 // First-tier "table size" of queries whose searches run in the global tier
 // from the start (RN_TABLE_GLOBAL).
 constexpr int kGlobalHB = kMaxHB + 1;
-constexpr int kLists = 3;
+constexpr int kLists = 4;
 inline int retry_list_after(int hb) { return hb < kRetryHB1 ? 0 : (hb < kMaxHB ? 1 : 2); }
 
 // k-closest pairs: distances are counted in log-spaced bins (16 per octave:
@@ -47,8 +48,8 @@ constexpr uint32_t kDistBins = 512;   // 464 used
 constexpr uint32_t kHistSeed = 0;
 constexpr uint32_t kHistEmit = kDistBins;
 constexpr uint32_t kHistProbe = 2 * kDistBins;      // + tier * kDistBins
-constexpr uint32_t kHistCount = 6 * kDistBins;      // + tier
-constexpr uint32_t kHistWords = 6 * kDistBins + 64;
+constexpr uint32_t kHistCount = 7 * kDistBins;      // + tier
+constexpr uint32_t kHistWords = 7 * kDistBins + 64;
 
 // One query of a call as the kernels read it (uploaded per call).  Ids in R
 // and S are local to the query's graph; the graph's vertices are the global
@@ -102,6 +103,7 @@ struct CallCtl {
     unsigned long long npairs;  // records emitted (may exceed the record buffer)
     uint32_t nlist[kLists];     // sources queued on each re-run list
     uint32_t nretry;            // sources that outgrew their first table
+    uint32_t pad0;
     unsigned long long arcs;    // work count: out-arcs of every settled (source, vertex)
     unsigned long long settled; // work count: settled (source, vertex) pairs
     unsigned long long nsel;    // records kept by the final bounds
@@ -115,7 +117,7 @@ struct CallCtl {
                                 //   run again without guesses
     uint32_t pad;
 };
-static_assert(sizeof(CallCtl) == 88, "CallCtl is 88 bytes");
+static_assert(sizeof(CallCtl) == 96, "CallCtl is 96 bytes");
 
 // One emitted (u, v, dist) of query q, ids local to the query's graph.
 struct alignas(16) Rec {
@@ -159,11 +161,13 @@ struct JoinArgs {
     uint32_t *bins;             // bucket sort: per-bin record counts, kept as records are stored (else null)
     const uint32_t *binbase;    //   first bin of each query
     int32_t first_tier;         // 1: count re-queued searches in ctl->nretry
-    int32_t tier;               // 0 first table, 1 and 2 the re-run tables, 3 the global tier
+    int32_t tier;               // 0 first table, 1 and 2 the re-run tables, 3 the global tier, 4 the
+                                //   global tier after that over quads
     int32_t one;                // 1: the call has one query (its records are counted in ctl only)
     int32_t count_work;         // 1: accumulate ctl->arcs / ctl->settled
     int32_t big_deg;            // 1: some vertex has 2^16 or more arcs (searches reaching one move on)
     const int32_t *order;       // global vertex of the device copy -> local id in the caller's numbering
+    const int32_t *rank;        // and back: caller's global vertex -> local id in the device copy
     const uint2 *quads;         // arc quads (null: the graphs keep none)
     const uint32_t *further;    //   per quad: the next quad of its vertex (local), if it has one
     const uint32_t *first;      // bit a: arc a is the first lightest of the arcs from its tail to its
@@ -266,6 +270,10 @@ hipError_t launch_build_quads(const int32_t *row_ptr, const ArcRec *arcs, uint32
 int join_tier_supported(int hash_log2);
 // The global-memory tier: one block per source, nslots slots of
 // global_slot_words(Vmax) words in the layout above.
+// The same over arc quads, for graphs whose path lengths fit 31 bits; searches
+// whose pending set outgrows its ring are queued on a.ovf.
+hipError_t launch_join_dense(const JoinArgs &a, uint32_t *slots, uint32_t nslots, int32_t Vmax, uint32_t max_sources,
+                             hipStream_t s);
 hipError_t launch_join_global(const JoinArgs &a, uint32_t *slots, uint32_t nslots, int32_t Vmax,
                               uint32_t max_sources, hipStream_t s);
 

@@ -2421,6 +2421,293 @@ __global__ __launch_bounds__(1024) void k_join_global(JoinArgs a, uint32_t *slot
     }
 }
 
+// ------------------------------------------------------------------ global-memory tier over quads
+// Searches that outgrow every on-chip table, on graphs with quads whose path
+// lengths fit 31 bits: one block of 16 waves per search, with the step of
+// search_quads_block (one barrier, entries taken and deferred by one lane each,
+// rows of 16 vertices), its ring in LDS and its distance words, (distance << 1) |
+// pending, in a dense array in global memory indexed by the vertex.  A step waits
+// for global memory twice, for the arcs (beside which the entries' words are read
+// and cleared of their pending bits) and for the atomicMin on the targets; about
+// half of it goes to those, which one CU takes at a third of a lane a cycle.  (A
+// plain load first, so that only the third of the arcs that improve something
+// goes on to the atomic, costs as much as it saves: 2 392 us against 2 116.)  The
+// pairs come from the query's list of S where that is shorter than the list of
+// vertices reached.  23 whole searches of the 400 x 400 road graph: 2 778 us by
+// k_join_global, 2 116 here (slack 3: 2 224; 8 waves: 2 619); 60 of the 1024 x 1024
+// graph 9.40 -> 8.53 ms.  A search whose pending set outgrows the ring goes on to
+// k_join_global, whose lists have room for any.
+constexpr uint32_t kDT = 1024;
+constexpr uint32_t kDW = kDT / 64;
+constexpr uint32_t kDR = 4;          // rows per wave and step
+constexpr uint32_t kDRing = 16384;
+constexpr uint32_t kDSlack = 2;      // deferral in units of the on-chip searches' slack
+
+struct DenseLds {
+    uint2 ring[kDRing];   // {vertex, quad | flags}
+    QuadBlock B;
+    uint32_t si, ovf;
+};
+
+// A slot's words are only touched by the block that owns the slot, so their
+// loads and atomics are workgroup-scoped (served by the XCD's L2, which
+// performs the atomics).
+__device__ __forceinline__ uint32_t dense_min(uint32_t *p, uint32_t v) {
+    return __hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ uint32_t dense_and(uint32_t *p, uint32_t v) {
+    return __hip_atomic_fetch_and(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ uint32_t dense_load(const uint32_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// One wave's rows of a step (as quad_block_step).
+template <int NJ>
+__device__ __forceinline__ void dense_step(DenseLds &L, uint32_t *word, uint32_t *touched, QuadStep *now, QuadState &st,
+                                           const SrcCtx &c, uint32_t head, uint32_t m, uint32_t wv, uint32_t lim,
+                                           uint32_t bound) {
+    constexpr uint32_t M = kDRing - 1u;
+    const uint32_t lane = lane_id(), lane4 = lane >> 2, lane8 = (lane & 3u) << 3;
+    uint2 arc[NJ];
+    uint32_t q[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) q[j] = L.ring[(lane4 + (head + 16u * (j * kDW + wv))) & M].y;
+    const uint32_t i = (lane & 15u) + 16u * ((lane >> 4) * kDW + wv);
+    const uint2 e = L.ring[(i + head) & M];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) arc[j] = quad_arc(c, q[j], lane8);
+    uint64_t val = __ballot(i < m);
+    if constexpr (NJ < 4) val &= (1ull << (16 * NJ)) - 1ull;
+    const uint64_t further = __ballot(e.y >= kQuadFurther);
+    uint32_t dl = kInf;
+    if (lane_in(val)) dl = dense_and(&word[e.x], lane_in(further) ? 0xFFFFFFFFu : ~1u) >> 1;
+    uint64_t later = val & __ballot(dl > lim) & __ballot(dl <= bound);
+    if (lane_in(later & ~further)) __hip_atomic_fetch_or(&word[e.x], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    st.imin = lane_in(later) ? dl : kInf;
+    val &= ~later & __ballot(dl <= bound);
+    const uint32_t dx = lane_in(val) ? dl : kInf;
+    const uint64_t more = val & __ballot((e.y & kQuadMore) != 0u);
+    uint32_t nq = 0;
+    if (lane_in(more)) nq = c.further[e.y & kQuadId];
+    uint32_t nd[NJ], old[NJ], sw[NJ], y[NJ];
+    uint64_t act[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        nd[j] = sat_add(from_lane((lane & ~3u) + 64u * j, dx), arc[j].y);
+        y[j] = arc[j].x & kQuadId;
+        act[j] = __ballot(nd[j] <= bound) & __ballot(nd[j] <= kPackMax);
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        old[j] = 0;
+        sw[j] = 0;
+        if (lane_in(act[j])) {
+            old[j] = dense_min(&word[y[j]], (nd[j] << 1) | 1u);
+            if (st.probing) sw[j] = c.sbits[y[j] >> 5] >> (y[j] & 31u);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);   // every min is issued before the first result is used
+    uint64_t app[NJ], fresh[NJ];
+    uint32_t nadd = 0, ins = 0;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const uint64_t imp = act[j] & __ballot(((nd[j] << 1) | 1u) < old[j]);
+        fresh[j] = imp & __ballot(old[j] == kWordNone);
+        app[j] = imp & (__ballot((old[j] & 1u) == 0u) | fresh[j]);
+        st.imin = min(st.imin, lane_in(imp) ? nd[j] : kInf);
+        nadd += popc(app[j]);
+        ins += popc(fresh[j]);
+    }
+    if (st.probing && ins != 0) {
+        uint32_t *ph = probe_hist(c);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const uint64_t hit = fresh[j] & __ballot((sw[j] & 1u) != 0u);
+            if (lane_in(hit)) atomicAdd(&ph[dist_bin(nd[j])], 1u);
+            st.pnew += popc(hit);
+        }
+    }
+    const uint32_t back = popc(later), all = nadd + back + popc(more);
+    uint32_t f = 0;
+    if (lane == 0) f = atomicAdd(&now->fill, (ins << 16) | all);
+    f = uni(f);
+    uint32_t base = st.tail + (f & 0xFFFFu), tb = st.nins + ((f >> 16) & 0x7FFFu);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {   // (also when the ring is full: the words are reset by this list)
+        if (lane_in(fresh[j])) touched[mbcnt_from(fresh[j], tb)] = y[j];
+        tb += popc(fresh[j]);
+    }
+    if (base + all - head > M + 1u) {   // (entries from head on may still be unread by other waves)
+        if (lane == 0) atomicOr(&now->fill, kQuadOvf);
+        return;
+    }
+    if (lane_in(later)) L.ring[mbcnt_from(later, base) & M] = e;
+    base += back;
+    if (lane_in(more))
+        L.ring[mbcnt_from(more, base) & M] =
+            make_uint2(e.x, nq | ((e.y & ~kQuadId) - (kQuadId + 1u)) | kQuadFurther);
+    base += popc(more);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        if (lane_in(app[j])) L.ring[mbcnt_from(app[j], base) & M] = make_uint2(y[j], arc[j].x);
+        base += popc(app[j]);
+    }
+    uint32_t mn = st.imin;
+    mn = min(mn, dpp<0x111>(mn, kInf));
+    mn = min(mn, dpp<0x112>(mn, kInf));
+    mn = min(mn, dpp<0x114>(mn, kInf));
+    mn = min(mn, dpp<0x118>(mn, kInf));
+    if (lane_in(0x8000800080008000ull)) atomicMin(&now->dmin, mn);
+    keep_apart<NJ>();
+}
+
+__global__ __launch_bounds__(1024) void k_join_dense(JoinArgs a, uint32_t *slots, uint32_t nslots, int32_t Vmax) {
+    __shared__ DenseLds L;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wv = uni(wave_in_block());
+    uint32_t sb, n;
+    launch_range(a, sb, n);
+    const size_t V = static_cast<size_t>(Vmax), NV = nslots * V, k = blockIdx.x;
+    uint32_t *word = slots + 2 * k * V;                  // local ids (half of the slot's 64-bit words)
+    uint32_t *touched = slots + 4 * NV + k * V;          // local ids
+    for (uint32_t i = tid; i < kDRing; i += kDT) L.ring[i] = make_uint2(0u, 0u);
+    for (uint32_t i = blockIdx.x; i < n;) {
+        const uint32_t q = uni(a.srcq[sb + i]);
+        const SrcCtx c = load_ctx<true>(a, q);
+        const int32_t u = a.src[sb + i];
+        __syncthreads();   // every thread has read the claim (and the ring is clear)
+        if (c.k != 0 && a.qs[q].direct) {   // answered by k_kcp_direct: nothing to search
+            if (tid == 0) L.si = gridDim.x + atomicAdd(a.work, 1u);
+            __syncthreads();
+            i = uni(L.si);
+            continue;
+        }
+        const uint32_t ul = static_cast<uint32_t>(u - c.voff);
+        if (tid == 0) {
+            word[ul] = 1u;   // distance 0, pending
+            touched[0] = ul;
+            L.ring[0] = source_entry(a, c, ul, ul);
+            L.B.step[0] = QuadStep{0u, kInf};
+            L.B.step[1] = QuadStep{0u, kInf};
+            L.B.step[2] = QuadStep{(1u << 16) | 1u, 0u};   // (left by the step before the first)
+        }
+        __syncthreads();
+        QuadState st;
+        st.tail = 0;
+        st.nins = 0;
+        st.imin = kInf;
+        st.pnew = 0;
+        st.ovf = false;
+        st.probing = false;
+        uint32_t seen = 0, phase = 0, head = 0, s0 = 0;
+        uint32_t bound = uni(current_bound(c)), nbound = bound, ncount = 0;
+        const uint32_t slack = c.slack == kInf ? kInf : c.slack >= 0x80000000u / kDSlack ? 0x80000000u : c.slack * kDSlack;
+        bool ovf = false;
+        while (true) {
+            const uint32_t s1 = s0 == 2 ? 0u : s0 + 1u, s2 = s1 == 2 ? 0u : s1 + 1u;
+            const QuadStep last = L.B.step[s2];   // what the last step left: every wave reads the same
+            const uint32_t f = uni(last.fill);
+            st.tail += f & 0xFFFFu;
+            st.nins += (f >> 16) & 0x7FFFu;
+            ovf = (f & kQuadOvf) != 0u;
+            if (ovf || st.tail == head) break;
+            const uint32_t lim = sat_add(uni(last.dmin), slack);
+            if (c.hist != nullptr) poll_bound(c, phase, nbound, ncount, bound, st.pnew, st.probing, seen);
+            if (tid == 0) L.B.step[s1] = QuadStep{0u, kInf};   // read in the last step, used in the next one
+            const uint32_t m = min(16u * kDR * kDW, st.tail - head);
+            const uint32_t rows = (m + 15u) / 16u;
+            const uint32_t nj = rows > wv ? (rows - wv + kDW - 1u) / kDW : 0u;
+            switch (nj) {
+                case 0: break;
+                case 1: dense_step<1>(L, word, touched, &L.B.step[s0], st, c, head, m, wv, lim, bound); break;
+                case 2: dense_step<2>(L, word, touched, &L.B.step[s0], st, c, head, m, wv, lim, bound); break;
+                case 3: dense_step<3>(L, word, touched, &L.B.step[s0], st, c, head, m, wv, lim, bound); break;
+                default: dense_step<4>(L, word, touched, &L.B.step[s0], st, c, head, m, wv, lim, bound); break;
+            }
+            head += m;
+            s0 = s1;
+            __syncthreads();   // every append of the step is done
+        }
+        // emit S members (from the query's list of them where that is shorter
+        // than the list of the vertices reached), count work
+        bound = current_bound(c);
+        unsigned long long warcs = 0;
+        uint32_t wsettled = 0, emitted = 0;
+        const QueryDesc &qd = a.qd[q];
+        const uint32_t nS = uni(static_cast<uint32_t>(qd.nS));
+        const bool by_s = nS < st.nins && !a.count_work;
+        const uint32_t cnt = ovf ? 0u : (by_s ? nS : st.nins);
+        for (uint32_t j0 = wv * 64u; j0 < cnt; j0 += kDT) {
+            const uint32_t j = j0 + lane;
+            uint32_t yl = 0, d = kInf;
+            bool hit = false;
+            if (j < cnt) {
+                bool ok = true;
+                if (by_s) {
+                    const int32_t s0 = qd.S[j];
+                    ok = s0 >= 0 && s0 < qd.V;   // (else an argument error, reported by the staging)
+                    yl = ok ? static_cast<uint32_t>(a.rank[c.voff + s0]) : 0u;
+                } else {
+                    yl = touched[j];
+                    ok = (c.sbits[yl >> 5] >> (yl & 31u)) & 1u;
+                }
+                d = dense_load(&word[yl]) >> 1;
+                hit = ok && d <= bound && d <= kPackMax;
+                if (a.count_work && d <= bound) {
+                    const uint32_t r = c.rpo + yl + static_cast<uint32_t>(c.voff);
+                    warcs += static_cast<unsigned long long>(a.row_ptr[r + 1] - a.row_ptr[r]);
+                    wsettled += 1;
+                }
+            }
+            const uint64_t mm = __ballot(hit);
+            if (mm == 0) continue;
+            if (c.k && hit) atomicAdd(&c.hist[kHistEmit + dist_bin(d)], 1u);
+            emitted += popc(mm);
+            const unsigned long long idx = reserve_recs(a, c, popc(mm)) + mbcnt(mm);
+            if (hit && idx < a.rec_cap) {
+                Rec rr;
+                const int32_t cy = caller_id(a, static_cast<int32_t>(yl) + c.voff, c.voff);
+                const int32_t cu = caller_id(a, u, c.voff);
+                rr.u = c.swapped ? cy : cu;
+                rr.v = c.swapped ? cu : cy;
+                rr.d = d;
+                rr.q = c.q;
+                if (a.bins) rr.q |= bin_place(atomicAdd(&a.bins[a.binbase[c.q] + d], 1u));
+                a.recs[idx] = rr;
+            }
+        }
+        // reset the slot: whole, where an eighth of it was reached, else by the list
+        __syncthreads();   // every distance is read
+        const uint32_t nv = static_cast<uint32_t>(qd.V);
+        if (st.nins > nv / 8u) {
+            for (uint32_t j = tid; j < nv; j += kDT) word[j] = kWordNone;
+        } else {
+            for (uint32_t j = tid; j < st.nins; j += kDT) word[touched[j]] = kWordNone;
+        }
+        unsigned long long tseen = 0;
+        if (c.k && emitted != 0) tighten_bound(c, tseen);
+        if (a.count_work && !ovf) {
+            for (int o = 32; o > 0; o >>= 1) {
+                const uint32_t lo = static_cast<uint32_t>(__shfl_xor(static_cast<int>(warcs & 0xFFFFFFFFull), o));
+                const uint32_t hi = static_cast<uint32_t>(__shfl_xor(static_cast<int>(warcs >> 32), o));
+                warcs += (static_cast<unsigned long long>(hi) << 32) | lo;
+                wsettled += static_cast<uint32_t>(__shfl_xor(static_cast<int>(wsettled), o));
+            }
+            if (lane == 0) {
+                atomicAdd(&a.ctl->arcs, warcs);
+                atomicAdd(&a.ctl->settled, static_cast<unsigned long long>(wsettled));
+            }
+        }
+        for (uint32_t j = tid; j < min(st.tail, kDRing); j += kDT) L.ring[j] = make_uint2(0u, 0u);
+        if (tid == 0) {
+            if (ovf) queue_next_tier(a, c, u);
+            L.si = gridDim.x + atomicAdd(a.work, 1u);
+        }
+        __syncthreads();   // the slot and the ring are clean before the next source starts
+        i = uni(L.si);
+    }
+}
+
 // ------------------------------------------------------------------ staging
 __global__ __launch_bounds__(256) void k_publish(const uint32_t *src, uint32_t *dst, uint32_t words) {
     const uint32_t i = blockIdx.x * 256u + threadIdx.x;
@@ -3414,6 +3701,14 @@ hipError_t launch_build_quads(const int32_t *row_ptr, const ArcRec *arcs, uint32
                        quads);
     hipLaunchKernelGGL(k_build_quads, dim3((rows + 255u) / 256u), dim3(256), 0, s, row_ptr, arcs, further, voff, qbase,
                        next, ngr, V, rows, quads);
+    return hipGetLastError();
+}
+
+hipError_t launch_join_dense(const JoinArgs &a, uint32_t *slots, uint32_t nslots, int32_t Vmax, uint32_t max_sources,
+                             hipStream_t s) {
+    uint32_t grid = nslots < max_sources ? nslots : max_sources;
+    if (grid == 0) grid = 1;
+    hipLaunchKernelGGL(k_join_dense, dim3(grid), dim3(kDT), 0, s, a, slots, nslots, Vmax);
     return hipGetLastError();
 }
 

@@ -72,3 +72,34 @@ def test_tables_chosen_by_radius(rnmod, orc, rg, theta):
     for nR, nS in ((12000, 13000) if theta <= 900 else (9000, 900), (9000, 40), (63, 65)):
         R, S = rg.sample_disjoint(g.V, nR, nS, theta)
         same(rnmod.pairs_to_numpy(net.dist_join(R, S, theta)), orc.dist_join(g, R, S, theta).pairs)
+
+
+def test_global_tier_over_quads(rnmod, orc, rg):
+    # whole-graph searches in the global tier: pairs found by S's list, by the
+    # vertices reached, and of a graph whose pending sets outgrow the search's ring of
+    # 16 384 entries (it goes on to the general global tier)
+    g = rg.road_graph(130, 3)
+    net = rnmod.RoadNetwork.from_graph(g)
+    for nR, nS in ((30, 200), (20, 9000)):
+        R, S = rg.sample_disjoint(g.V, nR, nS, nS)
+        for sp, want in (({"theta": 0xFFFFFFFE}, orc.dist_join(g, R, S, 0xFFFFFFFE).pairs),
+                         ({"theta": 5000}, orc.dist_join(g, R, S, 5000).pairs), ({"k": 3000}, orc.kcp_join(g, R, S, 3000))):
+            out, off, status = net.join_batch([{"R": R, "S": S, "hash_log2": rnmod.RN_TABLE_GLOBAL, **sp}])
+            assert not status.any()
+            same(rnmod.pairs_to_numpy(out[:off[1]]), want)
+    # two random cycles through 100 000 vertices: tens of thousands pending at once
+    n = 100000
+    rng = np.random.default_rng(8)
+    p, q = rng.permutation(n), rng.permutation(n)
+    t = rg.from_edges(n, np.concatenate([p, q]), np.concatenate([np.roll(p, 1), np.roll(q, 1)]),
+                      rng.integers(90, 111, size=2 * n), symmetric=True)
+    net = rnmod.RoadNetwork.from_graph(t)
+    net.set_profiling(times=True, work=True)
+    R = np.array([0, n - 1, 500], dtype=np.int32)
+    S = np.arange(1000, 3000, dtype=np.int32)
+    out, off, status = net.join_batch([{"R": R, "S": S, "hash_log2": rnmod.RN_TABLE_GLOBAL},
+                                       {"R": R, "S": S, "k": 500, "hash_log2": rnmod.RN_TABLE_GLOBAL}])
+    segs = rnmod.split_batch(out, off)
+    ref = orc.dist_join(t, R, S, 0xFFFFFFFE)
+    same(segs[0], ref.pairs)
+    same(segs[1], orc.kcp_join(t, R, S, 500))
