@@ -217,7 +217,7 @@ uint32_t ring_slack(double wmean) {
     return s >= 2147483647.0 ? 0x7FFFFFFFu : static_cast<uint32_t>(s + 0.5);
 }
 
-rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p, bool guesses) {
+rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p, bool guesses, bool short_form) {
     // reset in place: the vectors keep their capacity, so a Prepared reused for
     // calls of the same shape allocates nothing after its first call
     auto qd = std::move(p.qd);
@@ -351,11 +351,28 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
         p.need_list1 |= gr.hb < kMaxHB;
         p.any_global |= gr.hb == kGlobalHB;
     }
+    // the short form: one query whose table was chosen for its ball, with few
+    // searches (so that one which outgrows its table, and sends the whole call
+    // round again, is rare) and few records expected
+    if (short_form && nq == 1 && p.groups[0].sized && p.groups[0].quads && !g->count_work && p.groups[0].hb <= kMaxHB &&
+        p.groups[0].sources <= 4096) {
+        const rn_query &x = q[0];
+        const double V = static_cast<double>(g->voff[x.graph + 1] - g->voff[x.graph]);
+        const double r = static_cast<double>(x.theta) / std::max(1.0, g->wmean[x.graph]);
+        const double pairs = static_cast<double>(x.nR) * x.nS;
+        const double expect = x.k > 0 ? 1.5 * x.k : pairs * std::min(1.0, 2.5 * r * r / V);
+        const uint32_t dbits = bitlen(x.k > 0 ? std::min(x.theta, p.qd[0].guess) : x.theta);
+        const uint32_t vbits = std::max<uint32_t>(1u, bitlen(static_cast<uint64_t>(std::max(g->Vmax - 1, 0))));
+        const bool roomy = x.k > 0 || 0.75 * static_cast<double>(1u << p.groups[0].hb) >= 1.8 * 2.0 * r * r;
+        p.tail_one = roomy && (pairs <= kSmallSort || expect <= kSmallSort / 2) && dbits + 2 * vbits <= 63u;
+        p.stage_one = p.tail_one && g->voff[x.graph + 1] - g->voff[x.graph] <= kStage1Vertices &&
+                      p.total_elems <= kStage1Elems;
+    }
     // the bucket sort: theta-joins only, on graphs with varied weights, with
     // at most kMaxBins (query, dist) bins in all
     {
         uint64_t nb = 0;
-        bool ok = !p.any_kcp;
+        bool ok = !p.any_kcp && !p.tail_one;
         p.binbase.assign(static_cast<size_t>(nq) + 1, 0);
         for (int32_t i = 0; i < nq && ok; ++i) {
             p.binbase[i] = static_cast<uint32_t>(nb);
@@ -373,7 +390,7 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
             all_kcp = all_kcp && q[i].k > 0;
             ksum += static_cast<uint64_t>(std::max(q[i].k, 0));
         }
-        p.small_sort = all_kcp && ksum <= kSmallSort / 2;
+        p.small_sort = all_kcp && ksum <= kSmallSort / 2 && !p.tail_one;
     }
     p.qb = nq > 1 ? bitlen(static_cast<uint64_t>(nq - 1)) : 0u;
     p.vb = std::max<uint32_t>(1u, bitlen(static_cast<uint64_t>(std::max(g->Vmax - 1, 0))));
@@ -552,10 +569,6 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
                        bool timed, bool shared) {
     const CallBuffers b = call_buffers(ws, p);
     record(g, ws, timed, EV_START, s);
-    RN_HIP(launch_fill_u32(ws.d_block, p.zero_words, 0u, s), "clearing call state");
-    RN_HIP(launch_stage(b, p.total_elems, g->d_rank, s), "staging the queries");
-    record(g, ws, timed, EV_STAGED, s);
-
     JoinArgs a;
     std::memset(&a, 0, sizeof(a));
     a.row_ptr = g->d_row_ptr;
@@ -577,7 +590,27 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
     a.first = g->d_first;
     a.quads = g->d_quads;
     a.further = g->d_further;
-    if (p.any_kcp) {
+    if (p.nq == 1) {
+        DescWords desc;
+        uint8_t raw[sizeof(desc.w)];
+        if (p.desc_bytes > sizeof(raw)) return fail(RN_ERR_DEVICE, "query descriptors too large");
+        std::memset(raw, 0, sizeof(raw));
+        fill_host_desc(p, raw);
+        std::memcpy(desc.w, raw, sizeof(raw));
+        const uint32_t dn = static_cast<uint32_t>((p.desc_bytes + 3) / 4);
+        uint32_t *dd = reinterpret_cast<uint32_t *>(ws.d_desc);
+        if (p.stage_one)
+            RN_HIP(launch_stage_one(a, b, static_cast<uint32_t>(p.off_sbits), static_cast<uint32_t>(p.off_bins - p.off_hists),
+                                    g->d_rank, desc, dn, dd, s),
+                   "staging the query");
+        else
+            RN_HIP(launch_begin(ws.d_block, p.zero_words, desc, dn, dd, s), "clearing call state");
+    } else {
+        RN_HIP(launch_fill_u32(ws.d_block, p.zero_words, 0u, s), "clearing call state");
+    }
+    if (!p.stage_one) RN_HIP(launch_stage(b, p.total_elems, g->d_rank, s), "staging the queries");
+    record(g, ws, timed, EV_STAGED, s);
+    if (p.any_kcp && !p.stage_one) {
         JoinArgs k = a;
         k.src = b.src;
         k.srcq = b.srcq;
@@ -642,6 +675,17 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
         for (size_t i = gside; i < gside + ons - 1; ++i) RN_HIP(hipStreamWaitEvent(s, ws.join[i], 0), "joining streams");
     }
     record(g, ws, timed, EV_TIER0, s);
+    const size_t state_bytes = sizeof(CallCtl) + static_cast<size_t>(p.nq) * sizeof(QueryState);
+    const uint32_t *state = reinterpret_cast<const uint32_t *>(ws.d_block);
+    const uint32_t state_words = static_cast<uint32_t>(state_bytes / 4);
+    if (p.tail_one) {
+        record(g, ws, timed, EV_RELAXED, s);
+        record(g, ws, timed, EV_SELECTED, s);
+        RN_HIP(launch_tail_one(b, p.vb, out, static_cast<unsigned long long>(cap), state, ws.d_state_map, state_words, s),
+               "sorting pairs");
+        record(g, ws, timed, EV_DONE, s);
+        return RN_OK;
+    }
     // re-runs: 2^11-slot tables, 2^14-slot tables, then the global tier
     const uint32_t maxs = static_cast<uint32_t>(p.total_R);
     for (int li = 0; li < 2; ++li) {
@@ -690,9 +734,6 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
     const bool small = p.small_sort && p.nbins == 0;   // the small sort lays out the output itself
     if (!small) RN_HIP(launch_layout(b, p.any_kcp ? 1 : 0, p.qb, p.vb, p.nbins != 0, s), "laying out the output");
     record(g, ws, timed, EV_SELECTED, s);
-    const size_t state_bytes = sizeof(CallCtl) + static_cast<size_t>(p.nq) * sizeof(QueryState);
-    const uint32_t *state = reinterpret_cast<const uint32_t *>(ws.d_block);
-    const uint32_t state_words = static_cast<uint32_t>(state_bytes / 4);
     bool published = false;   // the sort's kernel published the call state itself
     if (p.nbins) {
         RN_HIP(launch_bucket_sort(b, out, static_cast<unsigned long long>(cap), state, ws.d_state_map, state_words, s),
@@ -743,13 +784,19 @@ float elapsed(const rn_graph *g, const Workspace &ws, int a, int b) {
 // the radix sort of a bucket-sorted call that found an oversized bin).
 // Sets *regrow when the call must run again (records outgrew the buffer, or
 // a search needed global-tier slots that did not exist yet), and *unmet with it
-// when that is to be without guessed bounds.
+// (kUnmet* bits) when that is to be without guessed bounds or the short form.
 rn_status finish(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, int64_t *offsets,
-                 int32_t *status, bool timed, bool *regrow, bool *unmet, hipStream_t s) {
+                 int32_t *status, bool timed, bool *regrow, uint32_t *unmet, hipStream_t s) {
     const CallCtl &c = *reinterpret_cast<const CallCtl *>(ws.h_state);
     const QueryState *qs = reinterpret_cast<const QueryState *>(ws.h_state + sizeof(CallCtl));
     *regrow = false;
-    *unmet = false;
+    *unmet = 0;
+    if (p.tail_one && (c.nlist[0] | c.nlist[1] | c.nlist[2]) != 0) {
+        // a search outgrew its table: the short form has no tier for it
+        *regrow = true;
+        *unmet = kUnmetTail;
+        return RN_OK;
+    }
     if (c.nlist[2] > 0 && !ws.d_gslots) {
         // some search needed the global tier, which had no slots yet
         *regrow = true;
@@ -762,7 +809,7 @@ rn_status finish(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, in
     if (*regrow) return RN_OK;
     if (c.unmet) {
         *regrow = true;
-        *unmet = true;
+        *unmet = c.unmet;
         return RN_OK;
     }
     if (c.resort) {
@@ -783,7 +830,9 @@ rn_status finish(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, in
         st.settled = static_cast<int64_t>(c.settled);
         st.retried = static_cast<int32_t>(c.nretry);
         st.global_searches = static_cast<int32_t>(c.nlist[2]);
-        st.relax_launches = static_cast<int32_t>(p.groups.size()) + (p.need_list0 ? 1 : 0) + (p.need_list1 ? 1 : 0) + 1;
+        st.relax_launches = p.tail_one ? 1
+                                       : static_cast<int32_t>(p.groups.size()) + (p.need_list0 ? 1 : 0) +
+                                             (p.need_list1 ? 1 : 0) + 1;
     }
     int bad = -1;
     uint32_t bad_err = 0;
@@ -806,20 +855,29 @@ rn_status finish(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, in
     return RN_OK;
 }
 
+// Prepare a call again after its state reported unmet (kUnmet* bits).
+rn_status prepare_again(const rn_graph *g, const rn_query *q, Prepared &p, uint32_t unmet) {
+    const bool guesses = p.guesses && !(unmet & kUnmetGuess);
+    return prepare(g, q, p.nq, p, guesses, p.tail_one && !(unmet & kUnmetTail));
+}
+
 // One eager call on workspace ws (prepared p, from the queries q); retries when
 // the record buffer was too small, and without guesses when one was not met.
 rn_status run_eager(rn_graph *g, Workspace &ws, Prepared &p, const rn_query *q, rn_pair *out, int64_t cap,
                     int64_t *offsets, int32_t *status, hipStream_t s, bool timed) {
-    for (int attempt = 0; attempt < 5; ++attempt) {
+    for (int attempt = 0; attempt < 6; ++attempt) {
         RN_TRY(ensure_buffers(ws, p));
-        fill_host_desc(p, ws.h_desc);
-        RN_HIP(hipMemcpyAsync(ws.d_desc, ws.h_desc, p.desc_bytes, hipMemcpyHostToDevice, s), "uploading queries");
+        if (p.nq > 1) {   // (one query's descriptors go with the first kernel)
+            fill_host_desc(p, ws.h_desc);
+            RN_HIP(hipMemcpyAsync(ws.d_desc, ws.h_desc, p.desc_bytes, hipMemcpyHostToDevice, s), "uploading queries");
+        }
         RN_TRY(enqueue_call(g, ws, p, out, cap, s, timed));
         RN_TRY(read_back(ws, p, s));
-        bool regrow = false, unmet = false;
+        bool regrow = false;
+        uint32_t unmet = 0;
         const rn_status st = finish(g, ws, p, out, cap, offsets, status, timed, &regrow, &unmet, s);
         if (!regrow) return st;
-        if (st == RN_OK && unmet) RN_TRY(prepare(g, q, p.nq, p, false));
+        if (st == RN_OK && unmet) RN_TRY(prepare_again(g, q, p, unmet));
     }
     return fail(RN_ERR_NOMEM, "record buffer did not settle");
 }
@@ -830,7 +888,7 @@ rn_status run_batch(rn_graph *g, const rn_query *q, int32_t nq, rn_pair *out, in
     RN_TRY(check_queries(g, q, nq, status));
     RN_HIP(hipSetDevice(g->device), "selecting the device");
     Prepared p;
-    RN_TRY(prepare(g, q, nq, p));
+    RN_TRY(prepare(g, q, nq, p, true, true));
     return run_eager(g, g->ws, p, q, out, cap, offsets, status, s, true);
 }
 
@@ -1634,7 +1692,7 @@ rn_status rn_plan_create(rn_graph *g, const rn_query *q, int32_t nq, rn_pair *ou
     pl->cap = cap;
     pl->q.assign(q, q + nq);
     Prepared &p = pl->prep;
-    rn_status st = prepare(g, q, nq, p);
+    rn_status st = prepare(g, q, nq, p, true, true);
     hipError_t e = hipSuccess;
     if (st == RN_OK && (e = hipStreamCreateWithFlags(&pl->cap_stream, hipStreamNonBlocking)) != hipSuccess)
         st = hip_fail(e, "creating the capture stream");
@@ -1662,10 +1720,11 @@ rn_status rn_plan_run(rn_plan *pl, int64_t *offsets, int32_t *status, void *stre
     Prepared &p = pl->prep;
     RN_HIP(hipGraphLaunch(pl->exec, s), "launching the graph");
     RN_TRY(read_back(pl->ws, p, s));
-    bool regrow = false, unmet = false;
+    bool regrow = false;
+    uint32_t unmet = 0;
     const rn_status st = finish(g, pl->ws, p, pl->out, pl->cap, offsets, status, false, &regrow, &unmet, s);
     if (!regrow) return st;
-    if (st == RN_OK && unmet) RN_TRY(prepare(g, pl->q.data(), p.nq, p, false));   // (from now on)
+    if (st == RN_OK && unmet) RN_TRY(prepare_again(g, pl->q.data(), p, unmet));   // (from now on)
     // the records outgrew the buffer (grown by finish): run eagerly, re-capture
     return plan_build(pl, p, s, offsets, status);
 }

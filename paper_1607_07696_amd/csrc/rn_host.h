@@ -154,6 +154,8 @@ struct Prepared {
     bool need_list1 = false;
     bool all_quads = true;          // every query's first searches are over arc quads
     bool guesses = true;            // k-closest-pairs queries may start from a guessed bound
+    bool stage_one = false;         // one-block staging (launch_stage_one)
+    bool tail_one = false;          // one-block tail (launch_tail_one), no re-run tiers
     bool any_global = false;        // a first-tier group runs in the global tier
     uint32_t qb = 0, vb = 1, max_passes = 1;
     uint64_t total_R = 0;
@@ -175,8 +177,11 @@ std::string describe_err(uint32_t err);
 rn_status check_queries(const rn_graph *g, const rn_query *q, int32_t nq, int32_t *status);
 // guesses: k-closest-pairs searches may start from a guessed bound; a call whose
 // state then reports an unmet guess (ctl.unmet) is prepared again without them
-// and run again.
-rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p, bool guesses = true);
+// and run again.  short_form: small one-query calls may take the one-block
+// staging and tail, without the re-run tiers; a call that needs those after all
+// (ctl.unmet, or searches queued on a re-run list) is prepared again without it.
+rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p, bool guesses = true,
+                  bool short_form = false);
 // Global-tier slots are allocated on demand: a call enqueued while a
 // workspace has none skips the global tier, and if any of its searches needed
 // it (ctl.nlist[2] > 0) the call is run again once slots exist.  Allocate (once)

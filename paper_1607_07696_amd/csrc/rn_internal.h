@@ -78,6 +78,11 @@ struct QueryDesc {
 static_assert(sizeof(QueryDesc) == 80, "QueryDesc is 80 bytes");
 constexpr uint32_t kOrientSwap = 1u << 31;
 
+// CallCtl::unmet: a k-query found fewer than k pairs within its guess (run again
+// without guesses); the call has more candidates than its one-block tail sorts
+// (run again without it).
+constexpr uint32_t kUnmetGuess = 1u, kUnmetTail = 2u;
+
 // Per-query device state of one call.  Zeroed first.
 struct QueryState {
     uint32_t err;               // kErr* bits
@@ -113,8 +118,7 @@ struct CallCtl {
     uint32_t nchunks;           // bucket sort: 64-record chunks over all bins
     uint32_t resort;            // the call's sort left the output to the radix sort (a bucket-sort bin
                                 //   above kBucketRankMax records, or more than kSmallSort candidates)
-    uint32_t unmet;             // a k-query found fewer than k pairs within its guess: the call is to be
-                                //   run again without guesses
+    uint32_t unmet;             // kUnmet* bits: the call is to be run again in another form
     uint32_t pad;
 };
 static_assert(sizeof(CallCtl) == 96, "CallCtl is 96 bytes");
@@ -223,6 +227,31 @@ hipError_t launch_publish(const uint32_t *src, uint32_t *dst, uint32_t words, hi
 // device copy (nullptr: identity).  max_elems: sum of nS + nR over the queries.
 hipError_t launch_stage(const CallBuffers &b, unsigned long long max_elems, const int32_t *rank, hipStream_t s);
 size_t stage_scratch_words(size_t rwords);
+
+// Descriptors of a one-query call (CallBuffers' qd .. binbase, as uploaded),
+// passed by value: the kernel that clears the call state writes them to their
+// place, so no copy goes ahead of the call.
+struct alignas(16) DescWords {
+    uint32_t w[40];
+};
+// Clear words [0, n) of p and write the descriptors' dn words to d.
+hipError_t launch_begin(uint32_t *p, uint64_t n, const DescWords &desc, uint32_t dn, uint32_t *d, hipStream_t s);
+
+// Staging of a one-query call in one block (instead of launch_begin, launch_stage
+// and, for k closest pairs, launch_kcp_seed): graphs of at most kStage1Vertices
+// vertices and sets of at most kStage1Elems in all.  hist_words: words to clear
+// from b.hists on (the histograms and the counters after them).
+constexpr int32_t kStage1Vertices = 32768;
+constexpr uint32_t kStage1Elems = 8192;
+hipError_t launch_stage_one(const JoinArgs &a, const CallBuffers &b, uint32_t head_words, uint32_t hist_words,
+                            const int32_t *rank, const DescWords &desc, uint32_t dn, uint32_t *d, hipStream_t s);
+
+// Tail of a one-query call with few records in one block (instead of
+// launch_select, launch_layout and a sort): keeps the records within the bound,
+// sorts them in LDS, lays out and writes the output, and publishes the call
+// state.  More than kSmallSort kept: ctl->unmet (kUnmetTail).
+hipError_t launch_tail_one(const CallBuffers &b, uint32_t vb, rn_pair *out, unsigned long long user_cap,
+                           const uint32_t *state, uint32_t *state_map, uint32_t state_words, hipStream_t s);
 
 // Relaxation at the on-chip tier with table size 2^hash_log2.  generic =
 // false: every source belongs to a theta-join (the kernel variant without the

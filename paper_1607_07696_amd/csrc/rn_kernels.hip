@@ -2720,6 +2720,11 @@ __global__ void k_fill_u32(uint32_t *p, uint64_t n, uint32_t v) {
         p[i] = v;
 }
 
+__global__ __launch_bounds__(256) void k_begin(uint32_t *p, uint64_t n, DescWords desc, uint32_t dn, uint32_t *d) {
+    if (blockIdx.x == 0 && threadIdx.x < dn) d[threadIdx.x] = desc.w[threadIdx.x];
+    for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < n; i += gridDim.x * 256ull) p[i] = 0u;
+}
+
 // Largest p in [0, n) with a[p] <= x (a non-decreasing, a[0] <= x).
 template <typename T>
 __device__ __forceinline__ uint32_t seg_of(const T *a, uint32_t n, T x) {
@@ -3017,6 +3022,94 @@ __global__ __launch_bounds__(256) void k_kcp_direct(JoinArgs a) {
     }
 }
 
+// Staging of a one-query call on a small graph in one block: clear the call state,
+// write the descriptors, check the sets and list the sources with both bitmaps in
+// LDS, and (k closest pairs) seed the bound.  As k_begin, k_mark, k_overlap_count,
+// k_rank_emit, k_kcp_seed_hist and k_kcp_seed_bound, whose launches and gaps cost
+// such a call more than their work does (64 x 64 sets on 4 060 vertices: 2 to 4 us
+// of work in each of 5 launches, 8 with the seeds, in a call of 80 us).  Queries
+// that direct arcs answer are searched one wave per source (direct_pairs).
+template <bool KCP>
+__global__ __launch_bounds__(1024) void k_stage_one(JoinArgs a, CallBuffers b, uint32_t head_words, uint32_t hist_words,
+                                                    const int32_t *rank, DescWords desc, uint32_t dn, uint32_t *dd) {
+    __shared__ uint32_t sb[kStage1Vertices / 32], rb[kStage1Vertices / 32];
+    alignas(16) __shared__ uint32_t h[KCP ? kDistBins : 4];
+    __shared__ uint32_t wsum[16];
+    __shared__ uint32_t s_err;
+    const uint32_t tid = threadIdx.x;
+    const QueryDesc &d = *reinterpret_cast<const QueryDesc *>(desc.w);
+    const uint32_t words = b.rwords;
+    if (tid < dn) dd[tid] = desc.w[tid];
+    uint32_t *head = reinterpret_cast<uint32_t *>(b.ctl);
+    for (uint32_t i = tid; i < head_words; i += 1024) head[i] = 0u;
+    for (uint32_t i = tid; i < hist_words; i += 1024) b.hists[i] = 0u;
+    if (tid < words) sb[tid] = rb[tid] = 0u;
+    if (KCP && tid < kDistBins) h[tid] = 0u;
+    if (tid == 0) s_err = 0u;
+    __syncthreads();
+    uint32_t err = 0;
+    const uint32_t nS = static_cast<uint32_t>(d.nS), nE = nS + static_cast<uint32_t>(d.nR);
+    for (uint32_t i = tid; i < nE; i += 1024) {
+        const bool in_r = i >= nS;
+        const int32_t x = in_r ? d.R[i - nS] : d.S[i];
+        if (x < 0 || x >= d.V) {
+            err |= kErrRange;
+            continue;
+        }
+        const int32_t y = rank ? rank[d.voff + x] : x;
+        const uint32_t bit = 1u << (y & 31);
+        if (atomicOr(in_r ? &rb[y >> 5] : &sb[y >> 5], bit) & bit) err |= in_r ? kErrDupR : kErrDupS;
+    }
+    __syncthreads();
+    uint32_t bits = 0;
+    if (tid < words) {
+        bits = rb[tid];
+        if (bits & sb[tid]) err |= kErrOverlap;
+        b.sbits[d.sbits + tid] = sb[tid];
+    }
+    if (err) atomicOr(&s_err, err);
+    uint32_t nsrc;
+    uint32_t pos = block_excl_scan_1024(__popc(bits), wsum, &nsrc);
+    while (bits) {
+        const uint32_t bt = __ffs(bits) - 1u;
+        b.src[pos] = d.voff + static_cast<int32_t>(tid * 32u + bt);
+        b.srcq[pos] = 0u;
+        ++pos;
+        bits &= bits - 1u;
+    }
+    __syncthreads();   // the cleared state and the sources are written
+    if (tid == 0) {
+        b.ctl->nsrc = nsrc;
+        if (s_err) {
+            b.ctl->err = s_err;
+            b.qs[0].err = s_err;
+        }
+    }
+    if constexpr (KCP) {
+        const uint32_t rpo = d.orient & ~kOrientSwap;
+        for (uint32_t i = tid; i < nsrc; i += 1024) {
+            const int32_t u = b.src[i];
+            const int32_t x1 = a.row_ptr[rpo + u + 1];
+            for (int32_t x = a.row_ptr[rpo + u]; x < x1; ++x) {
+                const ArcRec r = a.arcs[x];
+                const uint32_t yl = static_cast<uint32_t>(r.y - d.voff);
+                if (first_of_pair(a, x) && ((sb[yl >> 5] >> (yl & 31u)) & 1u)) atomicAdd(&h[dist_bin(r.w)], 1u);
+            }
+        }
+        __syncthreads();
+        if (tid < 64) {
+            uint32_t *seed = b.hists + d.hist + kHistSeed;
+            for (uint32_t j = tid; j < kDistBins; j += 64) seed[j] = h[j];
+            const uint32_t sure = min(wave_bound_from_hist(h, d.k), d.theta);
+            const uint32_t bd = min(sure, d.guess);
+            if (tid == 0) {
+                b.qs[0].bound = bd;
+                b.qs[0].guessed = bd < sure ? 1u : 0u;
+            }
+        }
+    }
+}
+
 // Keep the records within their query's final bound (order is restored by the
 // sort).  Each block takes a contiguous tile: it counts the records it keeps,
 // reserves their places with one global atomic, then writes them; only
@@ -3135,7 +3228,7 @@ __device__ __forceinline__ void layout_block(const CallBuffers &b, int selected,
             if (b.nq == 1) st.npairs = b.ctl->npairs;   // (counted for the call only)
             nsel = (selected && d.k) ? st.nsel : st.npairs;   // a theta-join keeps every record
             // every pair within the guess was found, but not k of them
-            if (d.k && st.guessed && !st.err && nsel < d.k) b.ctl->unmet = 1u;
+            if (d.k && st.guessed && !st.err && nsel < d.k) b.ctl->unmet = kUnmetGuess;
             nout = st.err ? 0ull : (d.k ? min(nsel, static_cast<unsigned long long>(d.k)) : nsel);
             if (nsel) atomicMax(&s_dmax, d.k ? st.bound : d.theta);
         }
@@ -3468,6 +3561,25 @@ __device__ __forceinline__ void bitonic_stages(unsigned long long *s, uint32_t P
     }
 }
 
+// Sort P (a power of two) keys in LDS.  Whole block, after a barrier; ends with one.
+__device__ __forceinline__ void bitonic_sort(unsigned long long *s_k, uint32_t P, uint32_t tid) {
+    for (uint32_t k = 2; k <= P; k <<= 1) {
+        for (uint32_t j = k >> 1; j > 0;) {
+            if (j >= 4) {
+                bitonic_stages<3>(s_k, P, k, j, tid);
+                j >>= 3;
+            } else if (j == 2) {
+                bitonic_stages<2>(s_k, P, k, j, tid);
+                j >>= 2;
+            } else {
+                bitonic_stages<1>(s_k, P, k, j, tid);
+                j >>= 1;
+            }
+            __syncthreads();
+        }
+    }
+}
+
 __device__ __forceinline__ void sort_small(const CallBuffers &b, uint32_t qb, uint32_t vb, rn_pair *out,
                                            unsigned long long user_cap, unsigned long long *s_k) {
     CallCtl *ctl = b.ctl;
@@ -3493,21 +3605,7 @@ __device__ __forceinline__ void sort_small(const CallBuffers &b, uint32_t qb, ui
         s_k[i] = key;
     }
     __syncthreads();
-    for (uint32_t k = 2; k <= P; k <<= 1) {
-        for (uint32_t j = k >> 1; j > 0;) {
-            if (j >= 4) {
-                bitonic_stages<3>(s_k, P, k, j, tid);
-                j >>= 3;
-            } else if (j == 2) {
-                bitonic_stages<2>(s_k, P, k, j, tid);
-                j >>= 2;
-            } else {
-                bitonic_stages<1>(s_k, P, k, j, tid);
-                j >>= 1;
-            }
-            __syncthreads();
-        }
-    }
+    bitonic_sort(s_k, P, tid);
     const unsigned long long vm = (1ull << vb) - 1ull, dm = (1ull << db) - 1ull;
     for (uint32_t i = tid; i < n; i += 1024) {
         const unsigned long long key = s_k[i];
@@ -3538,6 +3636,74 @@ __global__ __launch_bounds__(1024) void k_sort_small(CallBuffers b, uint32_t qb,
     sort_small(b, qb, vb, out, user_cap, s_k);
     __syncthreads();   // the state's last writes (ctl->resort) are seen by the whole block
     for (uint32_t i = threadIdx.x; i < state_words; i += 1024) state_map[i] = state[i];
+}
+
+// One block: the tail of a one-query call with few records.  The records within
+// the bound become (dist, u, v) keys in LDS, are sorted there and written out; the
+// call's counts come from the same block, which publishes them.  One launch
+// where the bucket sort takes three and k closest pairs two, at 3 to 7 us each
+// and as much again between them.
+__global__ __launch_bounds__(1024) void k_tail_one(CallBuffers b, uint32_t vb, rn_pair *out, unsigned long long user_cap,
+                                                   const uint32_t *state, uint32_t *state_map, uint32_t state_words) {
+    __shared__ unsigned long long s_k[kSmallSort];
+    __shared__ uint32_t s_n;
+    const uint32_t tid = threadIdx.x;
+    if (tid == 0) s_n = 0;
+    const QueryDesc &d = b.qd[0];
+    QueryState &st = b.qs[0];
+    CallCtl *ctl = b.ctl;
+    const unsigned long long n64 = ctl->npairs;
+    const uint32_t bound = d.k ? st.bound : d.theta;
+    const uint32_t db = max(bitlen32(bound), 1u);
+    const bool fits = n64 <= b.rec_cap;          // (else the host runs the call again)
+    const uint32_t n = fits && n64 <= 4u * kSmallSort ? static_cast<uint32_t>(n64) : 0u;
+    __syncthreads();
+    for (uint32_t i0 = 0; i0 < n; i0 += 1024) {
+        const uint32_t i = i0 + tid;
+        Rec r{0, 0, 0, 0};
+        if (i < n) r = b.recs[0][i];
+        const uint64_t m = __ballot(i < n && r.d <= bound);
+        uint32_t base = 0;
+        if (lane_id() == 0 && m != 0) base = atomicAdd(&s_n, popc(m));
+        base = readlane(base, 0);
+        const uint32_t at = base + mbcnt(m);
+        if (i < n && r.d <= bound && at < kSmallSort)
+            s_k[at] = (static_cast<unsigned long long>(r.d) << (2u * vb)) |
+                      (static_cast<unsigned long long>(static_cast<uint32_t>(r.u)) << vb) | static_cast<uint32_t>(r.v);
+    }
+    __syncthreads();
+    const uint32_t kept = s_n;
+    const bool small = fits && n64 <= 4u * kSmallSort && kept <= kSmallSort;
+    const uint32_t nout = st.err || !small ? 0u : (d.k ? min(kept, d.k) : kept);
+    if (small) {
+        uint32_t P = 2;
+        while (P < kept) P <<= 1;
+        for (uint32_t i = kept + tid; i < P; i += 1024) s_k[i] = ~0ull;
+        __syncthreads();
+        bitonic_sort(s_k, P, tid);
+        if (nout <= user_cap) {
+            const unsigned long long vm = (1ull << vb) - 1ull, dm = (1ull << db) - 1ull;
+            for (uint32_t i = tid; i < nout; i += 1024) {
+                const unsigned long long key = s_k[i];
+                rn_pair p;
+                p.u = static_cast<int32_t>((key >> vb) & vm);
+                p.v = static_cast<int32_t>(key & vm);
+                p.dist = static_cast<uint32_t>((key >> (2u * vb)) & dm);
+                out[i] = p;
+            }
+        }
+    }
+    if (tid == 0) {
+        if (fits && !small) ctl->unmet = kUnmetTail;
+        else if (small && d.k && st.guessed && !st.err && kept < d.k) ctl->unmet = kUnmetGuess;
+        ctl->nsel = kept;
+        ctl->nout = nout;
+        st.npairs = n64;
+        st.nsel = kept;
+        st.nout = nout;
+    }
+    __syncthreads();   // the state's last writes are seen by the whole block
+    for (uint32_t i = tid; i < state_words; i += 1024) state_map[i] = state[i];
 }
 
 // Blocks of `lds` bytes of LDS that one CU holds at once.  A CU's LDS is
@@ -3603,6 +3769,30 @@ hipError_t launch_fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s) {
     uint64_t blocks = (n + 255) / 256;
     if (blocks > 4096) blocks = 4096;
     hipLaunchKernelGGL(k_fill_u32, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s, p, n, v);
+    return hipGetLastError();
+}
+
+hipError_t launch_begin(uint32_t *p, uint64_t n, const DescWords &desc, uint32_t dn, uint32_t *d, hipStream_t s) {
+    uint64_t blocks = (n + 255) / 256;
+    if (blocks > 4096) blocks = 4096;
+    if (blocks == 0) blocks = 1;
+    hipLaunchKernelGGL(k_begin, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s, p, n, desc, dn, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_stage_one(const JoinArgs &a, const CallBuffers &b, uint32_t head_words, uint32_t hist_words,
+                            const int32_t *rank, const DescWords &desc, uint32_t dn, uint32_t *d, hipStream_t s) {
+    const bool kcp = reinterpret_cast<const QueryDesc *>(desc.w)->k != 0;
+    if (kcp)
+        hipLaunchKernelGGL((k_stage_one<true>), dim3(1), dim3(1024), 0, s, a, b, head_words, hist_words, rank, desc, dn, d);
+    else
+        hipLaunchKernelGGL((k_stage_one<false>), dim3(1), dim3(1024), 0, s, a, b, head_words, hist_words, rank, desc, dn, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_tail_one(const CallBuffers &b, uint32_t vb, rn_pair *out, unsigned long long user_cap,
+                           const uint32_t *state, uint32_t *state_map, uint32_t state_words, hipStream_t s) {
+    hipLaunchKernelGGL(k_tail_one, dim3(1), dim3(1024), 0, s, b, vb, out, user_cap, state, state_map, state_words);
     return hipGetLastError();
 }
 

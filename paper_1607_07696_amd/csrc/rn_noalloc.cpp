@@ -125,8 +125,6 @@ rn_status rn_dist_join_noalloc(rn_graph *g, const int32_t *R, int32_t nR, const 
     // first call its vectors are reused in place
     static thread_local Prepared p;
     RN_TRY(prepare(g, &q, 1, p));
-    alignas(16) uint8_t h_desc[512];
-    if (p.desc_bytes > sizeof(h_desc)) return fail(RN_ERR_DEVICE, "query descriptors too large");
     const size_t state_bytes = sizeof(CallCtl) + sizeof(QueryState);
     alignas(16) uint8_t h_state[sizeof(CallCtl) + sizeof(QueryState)];
     uint32_t nslots = 0;
@@ -140,8 +138,6 @@ rn_status rn_dist_join_noalloc(rn_graph *g, const int32_t *R, int32_t nR, const 
             RN_HIP(launch_fill_u32(ws.d_gslots, global_clear_words(nslots, g->Vmax), 0xFFFFFFFFu, s),
                    "clearing search slots");
         }
-        fill_host_desc(p, h_desc);
-        RN_HIP(hipMemcpyAsync(ws.d_desc, h_desc, p.desc_bytes, hipMemcpyHostToDevice, s), "uploading the query");
         RN_TRY(enqueue_call(g, ws, p, out, cap, s, false));
         RN_HIP(hipMemcpyAsync(h_state, ws.d_state_map, state_bytes, hipMemcpyDeviceToHost, s), "reading the call state");
         RN_HIP(hipStreamSynchronize(s), "waiting for the call");

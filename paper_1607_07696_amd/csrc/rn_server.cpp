@@ -219,8 +219,8 @@ rn_status launch_lane(rn_server *s, Lane &L) {
         L.out_cap = 1u << 16;
         RN_HIP(dev_alloc(&L.d_out, L.out_cap), "allocating the output");
     }
-    fill_host_desc(L.prep, L.ws.h_desc);
-    RN_HIP(hipMemcpyAsync(L.ws.d_desc, L.ws.h_desc, L.prep.desc_bytes, hipMemcpyHostToDevice, L.stream),
+    if (L.prep.nq > 1) fill_host_desc(L.prep, L.ws.h_desc);   // (one query's go with the first kernel)
+    if (L.prep.nq > 1) RN_HIP(hipMemcpyAsync(L.ws.d_desc, L.ws.h_desc, L.prep.desc_bytes, hipMemcpyHostToDevice, L.stream),
            "uploading queries");
     L.reruns = 0;
     return enqueue_lane(s, L);
@@ -257,7 +257,7 @@ bool progress_lane(rn_server *s, Lane &L) {
             // a k-query had fewer than k pairs within its guess: again without guesses
             st = prepare(s->g, L.q.data(), static_cast<int32_t>(L.q.size()), L.prep, false);
             if (st == RN_OK) st = ensure_buffers(L.ws, L.prep);
-            if (st == RN_OK) {
+            if (st == RN_OK && L.prep.nq > 1) {
                 fill_host_desc(L.prep, L.ws.h_desc);
                 const hipError_t ec = hipMemcpyAsync(L.ws.d_desc, L.ws.h_desc, L.prep.desc_bytes, hipMemcpyHostToDevice,
                                                      L.stream);
