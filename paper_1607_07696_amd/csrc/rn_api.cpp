@@ -395,6 +395,20 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
     p.qb = nq > 1 ? bitlen(static_cast<uint64_t>(nq - 1)) : 0u;
     p.vb = std::max<uint32_t>(1u, bitlen(static_cast<uint64_t>(std::max(g->Vmax - 1, 0))));
     p.max_passes = std::max<uint32_t>(1u, (p.qb + std::max<uint32_t>(bitlen(dmax), 1u) + 2u * p.vb + 7u) / 8u);
+    // other calls with k closest pairs: bins of equal width up to each query's
+    // final bound, as many as kMixedBins allows.  (32 mixed queries, 10 digit
+    // passes: the radix sort's 30 launches took 115 us.)
+    p.bin_log2 = 0;
+    if (p.any_kcp && !p.small_sort && !p.tail_one && nq <= static_cast<int32_t>(kMixedBins / 16)) {
+        bool varied = true;
+        for (int32_t i = 0; i < nq; ++i) varied = varied && g->varied[q[i].graph];
+        if (varied) {
+            p.bin_log2 = 4;
+            while (p.bin_log2 < 12 && (2u << p.bin_log2) * static_cast<uint32_t>(nq) <= kMixedBins) ++p.bin_log2;
+            for (int32_t i = 0; i <= nq; ++i) p.binbase[i] = static_cast<uint32_t>(i) << p.bin_log2;
+            p.nbins = p.binbase[nq];
+        }
+    }
     // call block: words, every region 64-word (256-byte) aligned
     p.off_qs = sizeof(CallCtl) / 4;
     p.off_sbits = round_up(p.off_qs + static_cast<size_t>(nq) * (sizeof(QueryState) / 4), 64);
@@ -408,7 +422,7 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
     // the bucket sort needs its bin counts cleared (either way the clearing
     // covers the call state, histograms and the global tier's counter before
     // them)
-    p.zero_words = p.nbins ? p.off_bins + p.nbins : p.off_bins;
+    p.zero_words = p.nbins ? p.off_bins + 2 * static_cast<size_t>(bin_stride(p.nbins)) : p.off_bins;
     p.off_ebase = round_up(static_cast<size_t>(nq) * sizeof(QueryDesc), 16);
     p.off_rbase = round_up(p.off_ebase + static_cast<size_t>(nq + 1) * sizeof(unsigned long long), 16);
     p.off_perm = round_up(p.off_rbase + static_cast<size_t>(nq + 1) * sizeof(uint32_t), 16);
@@ -531,6 +545,7 @@ CallBuffers call_buffers(const Workspace &ws, const Prepared &p) {
     b.perm = reinterpret_cast<const uint32_t *>(ws.d_desc + p.off_perm);
     b.binbase = reinterpret_cast<const uint32_t *>(ws.d_desc + p.off_binbase);
     b.nbins = p.nbins;
+    b.bin_log2 = p.bin_log2;
     b.bins = ws.d_block + p.off_bins;
     b.ctl = reinterpret_cast<CallCtl *>(ws.d_block);
     b.qs = reinterpret_cast<QueryState *>(ws.d_block + p.off_qs);
@@ -580,7 +595,7 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
     a.ctl = b.ctl;
     a.recs = b.recs[0];
     a.rec_cap = b.rec_cap;
-    a.bins = p.nbins ? b.bins : nullptr;
+    a.bins = p.nbins && p.bin_log2 == 0 ? b.bins : nullptr;   // (else counted by the selection)
     a.binbase = b.binbase;
     a.one = p.nq == 1 ? 1 : 0;
     a.count_work = g->count_work ? 1 : 0;
@@ -755,7 +770,9 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
 
 rn_status enqueue_sort_fallback(const Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, hipStream_t s) {
     const CallBuffers b = call_buffers(ws, p);
-    RN_HIP(launch_sort_out(b, 1, p.max_passes, p.vb, out, static_cast<unsigned long long>(cap), s), "sorting pairs");
+    // (the scattered records: recs[0] where the selection filled recs[1])
+    RN_HIP(launch_sort_out(b, p.bin_log2 ? 0 : 1, p.max_passes, p.vb, out, static_cast<unsigned long long>(cap), s),
+           "sorting pairs");
     return RN_OK;
 }
 

@@ -203,8 +203,10 @@ struct CallBuffers {
     uint32_t *hists;            // histogram pool
     uint32_t *sort_hist;        // sort_hist_words() words
     const uint32_t *binbase;    // bucket sort: [nq+1] first bin of each query (query order)
-    uint32_t nbins;             //   bins (query, dist); 0 when the call uses the radix sort
-    uint32_t *bins;             //   count[nbins] (zeroed) | start[nbins] | cursor[nbins] | chunk start[nbins+1]
+    uint32_t nbins;             //   bins (query, dist >> shift); 0 when the call uses another sort
+    uint32_t bin_log2;          //   0: shift 0, theta + 1 bins a query; else 2^bin_log2 bins a query
+    uint32_t *bins;             //   count | cursor (both zeroed) | start | chunk start, bin_stride(nbins)
+                                //   words each (one more chunk start)
     uint32_t *stage_scratch;    // stage_scratch_words(rwords) words
     int32_t *src;               // source list and its queries
     uint32_t *srcq;
@@ -333,7 +335,10 @@ constexpr uint32_t kSortPassesMax = 16;
 // record's place in its bin in the upper half of its 32-bit query field.
 constexpr int32_t kMaxQueries = 65536;
 
-// Bucket sort, for calls of theta-joins only whose bins (query, dist), theta+1
+// Bucket sort.  Calls with k-closest-pairs queries (of more candidates than the
+// small sort takes) use up to kMixedBins bins of equal width per query, 2^bin_log2
+// of them from 0 to its final bound; the selection counts the records per bin as
+// it keeps them.  Calls of theta-joins only whose bins (query, dist), theta+1
 // per query, number at most kMaxBins: the relaxation kernels count the records
 // per bin as they store them (the count's old value is the record's place in
 // its bin); the layout launch scans the counts; the scatter copies each record
@@ -346,8 +351,10 @@ constexpr int32_t kMaxQueries = 65536;
 // once, and the caller sorts the scattered records (grouped by bin in
 // recs[1]) with the radix sort instead (launch_sort_out, selected = 1).
 constexpr uint32_t kMaxBins = 65536;
+constexpr uint32_t kMixedBins = 32768;
 constexpr uint32_t kBucketRankMax = 4096;
-inline size_t bucket_words(uint32_t nbins) { return 4 * static_cast<size_t>(nbins) + 1; }
+__host__ __device__ inline uint32_t bin_stride(uint32_t nbins) { return (nbins + 3u) / 4u * 4u; }
+inline size_t bucket_words(uint32_t nbins) { return 4 * static_cast<size_t>(bin_stride(nbins)) + 1; }
 // The ranking launch also publishes the call state (state_words words from
 // state to state_map, as launch_publish does), which is final by then.
 hipError_t launch_bucket_sort(const CallBuffers &b, rn_pair *out, unsigned long long user_cap, const uint32_t *state,

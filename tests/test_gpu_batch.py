@@ -302,3 +302,27 @@ def test_config4_autotuned_plan_all_instances(rnmod, orc, instances, torch_cuda)
         net.join_batch([spec(instances[3], 3)])
         torch.cuda.synchronize()
     plan.close()
+
+
+@pytest.mark.parametrize("nq", [2, 3, 9, 40])
+def test_mixed_calls_sorted_by_bins(rnmod, orc, rg, nq):
+    # bins of several distances, for theta-joins beside k closest pairs; one
+    # query's pairs all at a few distances (a bin beyond what the ranking takes)
+    g = rg.road_graph(120, 5)
+    flat = rg.from_edges(g.V, np.repeat(np.arange(g.V), np.diff(g.row_ptr)), g.col,
+                         np.where(g.w < 120, 100, 1 + g.w % 37), symmetric=False)
+    net = rnmod.RoadNetwork.from_graphs([g, flat])
+    specs, want = [], []
+    for i in range(nq):
+        gr = i % 2
+        R, S = rg.sample_disjoint(g.V, 150 + 60 * (i % 5), 3000 if i == 1 else 200 + i, 77 + i)
+        if i % 3 == 0:
+            specs.append({"R": R, "S": S, "k": 1 + 531 * i % 2900, "graph": gr})
+            want.append(orc.kcp_join((g, flat)[gr], R, S, specs[-1]["k"]))
+        else:
+            specs.append({"R": R, "S": S, "theta": (0, 900, 2500)[i % 3] + 10 * i, "graph": gr})
+            want.append(orc.dist_join((g, flat)[gr], R, S, specs[-1]["theta"]).pairs)
+    out, off, status = net.join_batch(specs)
+    assert not status.any()
+    for seg, w in zip(rnmod.split_batch(out, off), want):
+        assert seg.shape == w.shape and np.array_equal(seg, w)
