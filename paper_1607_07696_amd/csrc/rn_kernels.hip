@@ -3,7 +3,7 @@
 // A call runs any mix of theta-joins and k-closest-pairs queries, each on one
 // of the resident graphs, as one launch sequence on one HIP stream:
 //   stage     validate every query's R and S, set its S-membership bitmap and
-//             list all sources query by query (k_mark, k_overlap_count, k_rank_emit)
+//             list all sources query by query (k_mark, k_rank_emit)
 //   seed      k-closest pairs: a first distance bound per query from the
 //             direct R-S arcs (k_kcp_seed_*); a query whose bound is below twice
 //             the lightest arc is answered here, one thread per source (k_kcp_direct)
@@ -2772,25 +2772,6 @@ __global__ void k_mark(CallBuffers b, const int32_t *rank) {
     }
 }
 
-// R and S must be disjoint: element i of the flattened lists, if it is in
-// some R, must not be in that query's S.
-__device__ __forceinline__ void check_overlap(const CallBuffers &b, const int32_t *rank, unsigned long long i) {
-    const uint32_t nq = static_cast<uint32_t>(b.nq);
-    if (i >= b.ebase[nq]) return;
-    const uint32_t p = seg_of(b.ebase, nq, i);
-    const uint32_t q = b.perm[p];
-    const QueryDesc &d = b.qd[q];
-    const unsigned long long j = i - b.ebase[p];
-    if (j < static_cast<unsigned long long>(d.nS)) return;
-    const int32_t u0 = d.R[j - d.nS];
-    if (u0 < 0 || u0 >= d.V) return;
-    const int32_t u = rank ? rank[d.voff + u0] : u0;   // local id in the device copy
-    if ((b.sbits[d.sbits + (u >> 5)] >> (u & 31)) & 1u) {
-        atomicOr(&b.qs[q].err, kErrOverlap);
-        atomicOr(&b.ctl->err, kErrOverlap);
-    }
-}
-
 // Block-wide exclusive scan of one value per thread (blockDim.x = 1024); *total
 // receives the block sum.  Uses wsum[16] in LDS.
 __device__ __forceinline__ uint32_t block_excl_scan_1024(uint32_t v, uint32_t *wsum, uint32_t *total) {
@@ -2809,27 +2790,36 @@ __device__ __forceinline__ uint32_t block_excl_scan_1024(uint32_t v, uint32_t *w
     return off + incl - v;
 }
 
-// After the marks, in one launch: the disjointness check (thread i takes
-// element i of the flattened lists) and source listing pass 1, the marked
-// ranks per 1024-word block of the rank pool (the first nblk blocks).
-__global__ __launch_bounds__(1024) void k_overlap_count(CallBuffers b, const int32_t *rank, uint32_t nblk) {
+// Source listing, pass 1 (calls of more than kListOnePass rank words): the marked
+// ranks per 1024-word block of the rank pool.
+__global__ __launch_bounds__(1024) void k_rank_count(CallBuffers b) {
     __shared__ uint32_t wsum[16];
-    check_overlap(b, rank, blockIdx.x * 1024ull + threadIdx.x);
-    if (blockIdx.x >= nblk) return;
     const uint32_t i = blockIdx.x * 1024u + threadIdx.x;
     uint32_t total;
     block_excl_scan_1024(i < b.rwords ? __popc(b.rbits[i]) : 0u, wsum, &total);
     if (threadIdx.x == 0) b.stage_scratch[blockIdx.x] = total;
 }
 
-// Source listing, pass 2: list the marked ranks in increasing pool order as
-// global vertex ids with their queries; the first word of each query records
-// where its sources start.
+// Source listing: the marked ranks in increasing pool order as global vertex ids
+// with their queries; the first word of each query records where its sources
+// start; R and S must be disjoint (a word's bits in both bitmaps).  bsum: the
+// block counts of pass 1, or null: each block counts the words before its own
+// itself (at most 256 KB from L2, which takes less than a launch and its gap).
+constexpr uint32_t kListOnePass = 65536;
 __global__ __launch_bounds__(1024) void k_rank_emit(CallBuffers b, const uint32_t *bsum) {
     __shared__ uint32_t wsum[16];
     const uint32_t tid = threadIdx.x;
     uint32_t acc = 0;
-    for (uint32_t j = tid; j < blockIdx.x; j += 1024) acc += bsum[j];
+    if (bsum) {
+        for (uint32_t j = tid; j < blockIdx.x; j += 1024) acc += bsum[j];
+    } else {
+        const uint4 *w = reinterpret_cast<const uint4 *>(b.rbits);   // (the pool starts a 256-byte line)
+#pragma unroll 4
+        for (uint32_t j = tid; j < blockIdx.x * 256u; j += 1024) {
+            const uint4 x = w[j];
+            acc += __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
+        }
+    }
     uint32_t pre;
     block_excl_scan_1024(acc, wsum, &pre);
     const uint32_t i = blockIdx.x * 1024u + tid;
@@ -2843,6 +2833,10 @@ __global__ __launch_bounds__(1024) void k_rank_emit(CallBuffers b, const uint32_
         const uint32_t lw = i - b.rbase[p];
         const int32_t voff = b.qd[q].voff;
         if (lw == 0) b.qs[q].src_start = pos;
+        if (bits && (bits & b.sbits[b.qd[q].sbits + lw])) {
+            atomicOr(&b.qs[q].err, kErrOverlap);
+            atomicOr(&b.ctl->err, kErrOverlap);
+        }
         while (bits) {
             const uint32_t bt = __ffs(bits) - 1u;
             const int32_t r = static_cast<int32_t>(lw * 32u + bt);
@@ -3024,8 +3018,8 @@ __global__ __launch_bounds__(256) void k_kcp_direct(JoinArgs a) {
 
 // Staging of a one-query call on a small graph in one block: clear the call state,
 // write the descriptors, check the sets and list the sources with both bitmaps in
-// LDS, and (k closest pairs) seed the bound.  As k_begin, k_mark, k_overlap_count,
-// k_rank_emit, k_kcp_seed_hist and k_kcp_seed_bound, whose launches and gaps cost
+// LDS, and (k closest pairs) seed the bound.  As k_begin, k_mark, k_rank_emit,
+// k_kcp_seed_hist and k_kcp_seed_bound, whose launches and gaps cost
 // such a call more than their work does (64 x 64 sets on 4 060 vertices: 2 to 4 us
 // of work in each of 5 launches, 8 with the seeds, in a call of 80 us).  Queries
 // that direct arcs answer are searched one wave per source (direct_pairs).
@@ -3628,8 +3622,60 @@ __device__ __forceinline__ void bitonic_sort(unsigned long long *s_k, uint32_t P
     }
 }
 
+// Place n <= kSmallSort distinct keys s_k in LDS in order: bins of the keys' top 10
+// of `bits` bits (from bit `low` on), counted and scanned in LDS, then each key's
+// place in its bin by counting the bin's smaller ones; put(key, place) once per
+// key.  Six barriers where the bitonic network takes 26 for 2 048 keys.  Returns
+// false, having done nothing, if some bin holds more than kSmallBin keys (many
+// equal distances): the caller then takes the network.  Whole block.
+constexpr uint32_t kSmallBin = 256;
+struct SmallLds {
+    unsigned long long k[kSmallSort];   // the keys
+    unsigned long long t[kSmallSort];   // the keys by bins
+    uint32_t start[1025];               // counts, then starts of the bins
+    uint32_t wsum[16];
+    uint32_t dmax, n;
+};
+
+template <typename Put>
+__device__ __forceinline__ bool place_small(SmallLds &L, uint32_t n, uint32_t low, uint32_t bits, Put put) {
+    const uint32_t tid = threadIdx.x, sh = low + (bits > 10u ? bits - 10u : 0u);
+    L.start[tid] = 0;
+    __syncthreads();
+    constexpr uint32_t E = kSmallSort / 1024;
+    uint32_t place[E];
+#pragma unroll
+    for (uint32_t e = 0; e < E; ++e) {
+        const uint32_t i = e * 1024u + tid;
+        place[e] = i < n ? atomicAdd(&L.start[static_cast<uint32_t>(L.k[i] >> sh)], 1u) : 0u;
+    }
+    __syncthreads();
+    const uint32_t cnt = L.start[tid];
+    if (__syncthreads_or(cnt > kSmallBin)) return false;
+    uint32_t total;
+    const uint32_t first = block_excl_scan_1024(cnt, L.wsum, &total);
+    L.start[tid] = first;
+    if (tid == 0) L.start[1024] = n;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t e = 0; e < E; ++e) {
+        const uint32_t i = e * 1024u + tid;
+        if (i < n) L.t[L.start[static_cast<uint32_t>(L.k[i] >> sh)] + place[e]] = L.k[i];
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < n; i += 1024) {
+        const unsigned long long key = L.t[i];
+        const uint32_t bin = static_cast<uint32_t>(key >> sh), s0 = L.start[bin], s1 = L.start[bin + 1];
+        uint32_t pos = s0;
+        for (uint32_t j = s0; j < s1; ++j) pos += L.t[j] < key ? 1u : 0u;
+        put(key, pos);
+    }
+    return true;
+}
+
 __device__ __forceinline__ void sort_small(const CallBuffers &b, uint32_t qb, uint32_t vb, rn_pair *out,
-                                           unsigned long long user_cap, unsigned long long *s_k) {
+                                           unsigned long long user_cap, SmallLds &L) {
+    unsigned long long *s_k = L.k;
     CallCtl *ctl = b.ctl;
     if (ctl->npairs > b.rec_cap || ctl->nout > user_cap) return;
     const uint32_t tid = threadIdx.x;
@@ -3640,25 +3686,16 @@ __device__ __forceinline__ void sort_small(const CallBuffers &b, uint32_t qb, ui
         return;
     }
     const uint32_t n = static_cast<uint32_t>(n64);
-    uint32_t P = 2;
-    while (P < n) P <<= 1;
     const uint32_t sh_d = 2u * vb, sh_q = 2u * vb + db;
-    for (uint32_t i = tid; i < P; i += 1024) {
-        unsigned long long key = ~0ull;
-        if (i < n) {
-            const Rec r = b.recs[1][i];
-            key = (static_cast<unsigned long long>(r.q) << sh_q) | (static_cast<unsigned long long>(r.d) << sh_d) |
-                  (static_cast<unsigned long long>(static_cast<uint32_t>(r.u)) << vb) | static_cast<uint32_t>(r.v);
-        }
-        s_k[i] = key;
+    for (uint32_t i = tid; i < n; i += 1024) {
+        const Rec r = b.recs[1][i];
+        s_k[i] = (static_cast<unsigned long long>(r.q) << sh_q) | (static_cast<unsigned long long>(r.d) << sh_d) |
+                 (static_cast<unsigned long long>(static_cast<uint32_t>(r.u)) << vb) | static_cast<uint32_t>(r.v);
     }
     __syncthreads();
-    bitonic_sort(s_k, P, tid);
     const unsigned long long vm = (1ull << vb) - 1ull, dm = (1ull << db) - 1ull;
-    for (uint32_t i = tid; i < n; i += 1024) {
-        const unsigned long long key = s_k[i];
-        const uint32_t q = static_cast<uint32_t>(key >> sh_q);
-        const QueryState &st = b.qs[q];
+    auto put = [&](unsigned long long key, uint32_t i) {
+        const QueryState &st = b.qs[static_cast<uint32_t>(key >> sh_q)];
         const unsigned long long rel = static_cast<unsigned long long>(i) - st.start;
         if (rel < st.nout) {
             rn_pair p;
@@ -3667,7 +3704,14 @@ __device__ __forceinline__ void sort_small(const CallBuffers &b, uint32_t qb, ui
             p.dist = static_cast<uint32_t>((key >> sh_d) & dm);
             out[st.off + rel] = p;
         }
-    }
+    };
+    if (place_small(L, n, sh_d, qb + db, put)) return;
+    uint32_t P = 2;
+    while (P < n) P <<= 1;
+    for (uint32_t i = n + tid; i < P; i += 1024) s_k[i] = ~0ull;
+    __syncthreads();
+    bitonic_sort(s_k, P, tid);
+    for (uint32_t i = tid; i < n; i += 1024) put(s_k[i], i);
 }
 
 // The output layout of the selected records (as k_layout), the small sort,
@@ -3676,25 +3720,25 @@ __device__ __forceinline__ void sort_small(const CallBuffers &b, uint32_t qb, ui
 __global__ __launch_bounds__(1024) void k_sort_small(CallBuffers b, uint32_t qb, uint32_t vb, rn_pair *out,
                                                      unsigned long long user_cap, const uint32_t *state,
                                                      uint32_t *state_map, uint32_t state_words) {
-    __shared__ unsigned long long s_k[kSmallSort];
-    __shared__ uint32_t s_dmax;
+    __shared__ SmallLds L;
     static_assert(kSmallSort >= 1024, "the layout's scan uses the sort's keys as scratch");
-    layout_block(b, 1, qb, vb, s_k, s_dmax);
+    layout_block(b, 1, qb, vb, L.k, L.dmax);
     __syncthreads();   // the layout's call state (ctl written by thread 0) is seen by the whole block
-    sort_small(b, qb, vb, out, user_cap, s_k);
+    sort_small(b, qb, vb, out, user_cap, L);
     __syncthreads();   // the state's last writes (ctl->resort) are seen by the whole block
     for (uint32_t i = threadIdx.x; i < state_words; i += 1024) state_map[i] = state[i];
 }
 
 // One block: the tail of a one-query call with few records.  The records within
-// the bound become (dist, u, v) keys in LDS, are sorted there and written out; the
+// the bound become (dist, u, v) keys in LDS, are placed there and written out; the
 // call's counts come from the same block, which publishes them.  One launch
 // where the bucket sort takes three and k closest pairs two, at 3 to 7 us each
 // and as much again between them.
 __global__ __launch_bounds__(1024) void k_tail_one(CallBuffers b, uint32_t vb, rn_pair *out, unsigned long long user_cap,
                                                    const uint32_t *state, uint32_t *state_map, uint32_t state_words) {
-    __shared__ unsigned long long s_k[kSmallSort];
-    __shared__ uint32_t s_n;
+    __shared__ SmallLds L;
+    unsigned long long *s_k = L.k;
+    uint32_t &s_n = L.n;
     const uint32_t tid = threadIdx.x;
     if (tid == 0) s_n = 0;
     const QueryDesc &d = b.qd[0];
@@ -3723,22 +3767,23 @@ __global__ __launch_bounds__(1024) void k_tail_one(CallBuffers b, uint32_t vb, r
     const uint32_t kept = s_n;
     const bool small = fits && n64 <= 4u * kSmallSort && kept <= kSmallSort;
     const uint32_t nout = st.err || !small ? 0u : (d.k ? min(kept, d.k) : kept);
-    if (small) {
-        uint32_t P = 2;
-        while (P < kept) P <<= 1;
-        for (uint32_t i = kept + tid; i < P; i += 1024) s_k[i] = ~0ull;
-        __syncthreads();
-        bitonic_sort(s_k, P, tid);
-        if (nout <= user_cap) {
-            const unsigned long long vm = (1ull << vb) - 1ull, dm = (1ull << db) - 1ull;
-            for (uint32_t i = tid; i < nout; i += 1024) {
-                const unsigned long long key = s_k[i];
-                rn_pair p;
-                p.u = static_cast<int32_t>((key >> vb) & vm);
-                p.v = static_cast<int32_t>(key & vm);
-                p.dist = static_cast<uint32_t>((key >> (2u * vb)) & dm);
-                out[i] = p;
-            }
+    if (small && nout != 0 && nout <= user_cap) {
+        const unsigned long long vm = (1ull << vb) - 1ull, dm = (1ull << db) - 1ull;
+        auto put = [&](unsigned long long key, uint32_t i) {
+            if (i >= nout) return;
+            rn_pair p;
+            p.u = static_cast<int32_t>((key >> vb) & vm);
+            p.v = static_cast<int32_t>(key & vm);
+            p.dist = static_cast<uint32_t>((key >> (2u * vb)) & dm);
+            out[i] = p;
+        };
+        if (!place_small(L, kept, 2u * vb, db, put)) {
+            uint32_t P = 2;
+            while (P < kept) P <<= 1;
+            for (uint32_t i = kept + tid; i < P; i += 1024) s_k[i] = ~0ull;
+            __syncthreads();
+            bitonic_sort(s_k, P, tid);
+            for (uint32_t i = tid; i < nout; i += 1024) put(s_k[i], i);
         }
     }
     if (tid == 0) {
@@ -3850,9 +3895,9 @@ hipError_t launch_stage(const CallBuffers &b, unsigned long long max_elems, cons
     const uint32_t eblk = static_cast<uint32_t>((max_elems + 255) / 256);
     hipLaunchKernelGGL(k_mark, dim3(eblk), dim3(256), 0, s, b, rank);
     const uint32_t nblk = (b.rwords + 1023u) / 1024u;
-    const uint32_t oblk = static_cast<uint32_t>((max_elems + 1023) / 1024);
-    hipLaunchKernelGGL(k_overlap_count, dim3(max(nblk, oblk)), dim3(1024), 0, s, b, rank, nblk);
-    hipLaunchKernelGGL(k_rank_emit, dim3(nblk), dim3(1024), 0, s, b, b.stage_scratch);
+    const bool one = b.rwords <= kListOnePass;
+    if (!one) hipLaunchKernelGGL(k_rank_count, dim3(nblk), dim3(1024), 0, s, b);
+    hipLaunchKernelGGL(k_rank_emit, dim3(nblk), dim3(1024), 0, s, b, one ? nullptr : b.stage_scratch);
     return hipGetLastError();
 }
 
