@@ -640,6 +640,9 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
     // stream of its own that the re-run tiers do not wait for: only the later
     // global launch, which takes the same slots, waits for it.
     const size_t ng = p.groups.size();
+    uint64_t searches = 0;
+    for (const Group &gr : p.groups) searches += gr.sources;
+    const bool dense = g->dense && searches <= kDenseSources;
     if (ng > static_cast<size_t>(kSide) + 1) return fail(RN_ERR_DEVICE, "too many first-tier groups");
     const bool early_global = ng > 0 && p.groups[ng - 1].hb == kGlobalHB && ws.d_gslots != nullptr;
     const size_t non = ng - (early_global ? 1 : 0);                  // on-chip groups
@@ -667,7 +670,7 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
             t.ovf = b.list[3];
             t.ovfq = b.listq[3];
             t.novf = &b.ctl->nlist[3];
-            RN_HIP((g->dense ? launch_join_dense : launch_join_global)(t, ws.d_gslots, ws.n_gslots, g->Vmax,
+            RN_HIP((dense ? launch_join_dense : launch_join_global)(t, ws.d_gslots, ws.n_gslots, g->Vmax,
                                                                         static_cast<uint32_t>(gr.sources), st),
                    "launching the global relaxation");
         } else {
@@ -731,7 +734,7 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
         t.send = &b.ctl->nlist[2];
         t.tier = 3;
         t.work = ws.d_block + p.off_work;
-        if (g->dense) {
+        if (dense) {
             t.ovf = b.list[3];
             t.ovfq = b.listq[3];
             t.novf = &b.ctl->nlist[3];

@@ -80,7 +80,7 @@ def test_global_tier_over_quads(rnmod, orc, rg):
     # 16 384 entries (it goes on to the general global tier)
     g = rg.road_graph(130, 3)
     net = rnmod.RoadNetwork.from_graph(g)
-    for nR, nS in ((30, 200), (20, 9000)):
+    for nR, nS in ((30, 200), (20, 9000), (65, 300)):   # (the last: more searches than it takes)
         R, S = rg.sample_disjoint(g.V, nR, nS, nS)
         for sp, want in (({"theta": 0xFFFFFFFE}, orc.dist_join(g, R, S, 0xFFFFFFFE).pairs),
                          ({"theta": 5000}, orc.dist_join(g, R, S, 5000).pairs), ({"k": 3000}, orc.kcp_join(g, R, S, 3000))):
