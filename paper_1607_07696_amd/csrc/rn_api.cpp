@@ -118,7 +118,7 @@ uint32_t guess_bound(const rn_graph *g, const rn_query &x, double *ball) {
     return static_cast<uint32_t>(d) + 1u;
 }
 
-// Mean distances within which 2^3 .. 2^9 vertices lie, over a few vertices of
+// Mean distances within which 2^3 .. 2^8 vertices lie, over a few vertices of
 // graph i spread over its numbering (0: not reached).
 // dist: per vertex 1 + tentative distance, all 0 before and after.
 void measure_radii(rn_graph *g, int32_t i, uint64_t *dist) {

@@ -58,9 +58,9 @@ enum { EV_START, EV_STAGED, EV_TIER0, EV_RELAXED, EV_SELECTED, EV_DONE, EV_COUNT
 constexpr int kSide = 2 * (kMaxHB - kMinHB + 1) - 1;   // side streams: one per first-tier launch beyond the first
 constexpr unsigned long long kRecCapMax = 1ull << 31;
 
-// Ball sizes whose radii are measured when a graph is loaded (2^3 .. 2^9 vertices).
+// Ball sizes whose radii are measured when a graph is loaded (2^3 .. 2^8 vertices).
 constexpr int kBallMinLog2 = 3;
-constexpr int kBalls = 7;
+constexpr int kBalls = 6;
 
 inline size_t round_up(size_t x, size_t m) { return (x + m - 1) / m * m; }
 

@@ -1901,6 +1901,11 @@ __device__ void search_quads_block(QuadLds<HB, CT> &L, QuadBlock &B, const JoinA
     st.pnew = 0;
     st.ovf = false;
     st.probing = false;
+    // half as much again as one wave's searches: the least distance queued lies
+    // below the least one taken, and wider steps lose less by an early expansion
+    // (theta = 8 000: 1 683 us with 1.5 mean weights, 1 602 with 2.2, 1 600 with 2.8;
+    // 4 000: 344, 340, 347)
+    const uint32_t slack = c.slack == kInf ? kInf : c.slack + c.slack / 2u;   // (at most 2^31)
     uint32_t seen = 0, phase = 0, head = 0, s0 = 0;
     uint32_t bound = uni(current_bound(c)), nbound = bound, ncount = 0;
     if (c.hist != nullptr && !c.guessed)
@@ -1915,7 +1920,7 @@ __device__ void search_quads_block(QuadLds<HB, CT> &L, QuadBlock &B, const JoinA
         st.nins += (f >> 16) & 0x7FFFu;
         ovf = (f & kQuadOvf) != 0u;
         if (ovf || st.tail == head) break;
-        const uint32_t lim = sat_add(uni(last.dmin), c.slack);
+        const uint32_t lim = sat_add(uni(last.dmin), slack);
         if (c.hist != nullptr) poll_bound(c, phase, nbound, ncount, bound, st.pnew, st.probing, seen);
         if (threadIdx.x == 0) B.step[s1] = QuadStep{0u, kInf};   // read in the last step, used in the next one
         const uint32_t m = min(16u * T::NR * NW, st.tail - head);
