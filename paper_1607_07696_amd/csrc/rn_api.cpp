@@ -99,7 +99,9 @@ uint32_t guess_bound(const rn_graph *g, const rn_query &x, double *ball) {
     const double k = static_cast<double>(x.k);
     const double want = std::max(1.5 * k, k + 4.0 * std::sqrt(k)) + 8.0;
     const double b = std::max(want * V / (static_cast<double>(x.nR) * x.nS), static_cast<double>(1 << kBallMinLog2));
-    if (!(8.0 * b <= V)) return kInf;
+    // (balls that are a large part of the graph are cut off at its edges: at V / 8
+    // by a quarter, which used the margin up and sent such queries round again)
+    if (!(64.0 * b <= V)) return kInf;
     const double *r = g->radius.data() + static_cast<size_t>(x.graph) * kBalls;
     const double l = std::log2(b) - kBallMinLog2;
     const int i = std::min(static_cast<int>(l), kBalls - 1);
@@ -398,14 +400,31 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
     // other calls with k closest pairs: bins of equal width up to each query's
     // final bound, as many as kMixedBins allows.  (32 mixed queries, 10 digit
     // passes: the radix sort's 30 launches took 115 us.)
-    p.bin_log2 = 0;
+    p.mixed_bins = false;
     if (p.any_kcp && !p.small_sort && !p.tail_one && nq <= static_cast<int32_t>(kMixedBins / 16)) {
         bool varied = true;
         for (int32_t i = 0; i < nq; ++i) varied = varied && g->varied[q[i].graph];
         if (varied) {
-            p.bin_log2 = 4;
-            while (p.bin_log2 < 12 && (2u << p.bin_log2) * static_cast<uint32_t>(nq) <= kMixedBins) ++p.bin_log2;
-            for (int32_t i = 0; i <= nq; ++i) p.binbase[i] = static_cast<uint32_t>(i) << p.bin_log2;
+            // a power of two for each query's expected records, 8 a bin where
+            // that fits (equal shares left some bins hundreds long: 297 us to
+            // rank 825 000 pairs of 128 queries)
+            p.mixed_bins = true;
+            for (double per = 8.0;; per *= 2.0) {
+                uint64_t nb = 0;
+                for (int32_t i = 0; i < nq; ++i) {
+                    const rn_query &x = q[i];
+                    const double V = static_cast<double>(g->voff[x.graph + 1] - g->voff[x.graph]);
+                    const double r = static_cast<double>(x.theta) / std::max(1.0, g->wmean[x.graph]);
+                    const double pairs = static_cast<double>(x.nR) * x.nS;
+                    const double expect = x.k > 0 ? 1.5 * x.k : pairs * std::min(1.0, 2.5 * r * r / V);
+                    uint32_t n = 16;
+                    while (n < 8192u && n * per < expect) n *= 2;
+                    p.binbase[i] = static_cast<uint32_t>(nb);
+                    nb += n;
+                }
+                p.binbase[nq] = static_cast<uint32_t>(nb);
+                if (nb <= kMixedBins) break;
+            }
             p.nbins = p.binbase[nq];
         }
     }
@@ -545,7 +564,7 @@ CallBuffers call_buffers(const Workspace &ws, const Prepared &p) {
     b.perm = reinterpret_cast<const uint32_t *>(ws.d_desc + p.off_perm);
     b.binbase = reinterpret_cast<const uint32_t *>(ws.d_desc + p.off_binbase);
     b.nbins = p.nbins;
-    b.bin_log2 = p.bin_log2;
+    b.mixed_bins = p.mixed_bins ? 1 : 0;
     b.bins = ws.d_block + p.off_bins;
     b.ctl = reinterpret_cast<CallCtl *>(ws.d_block);
     b.qs = reinterpret_cast<QueryState *>(ws.d_block + p.off_qs);
@@ -595,7 +614,7 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
     a.ctl = b.ctl;
     a.recs = b.recs[0];
     a.rec_cap = b.rec_cap;
-    a.bins = p.nbins && p.bin_log2 == 0 ? b.bins : nullptr;   // (else counted by the selection)
+    a.bins = p.nbins && !p.mixed_bins ? b.bins : nullptr;   // (else counted by the selection)
     a.binbase = b.binbase;
     a.one = p.nq == 1 ? 1 : 0;
     a.count_work = g->count_work ? 1 : 0;
@@ -670,7 +689,7 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
             t.ovf = b.list[3];
             t.ovfq = b.listq[3];
             t.novf = &b.ctl->nlist[3];
-            RN_HIP((dense ? launch_join_dense : launch_join_global)(t, ws.d_gslots, ws.n_gslots, g->Vmax,
+            RN_HIP((g->dense && gr.sources <= kDenseSources ? launch_join_dense : launch_join_global)(t, ws.d_gslots, ws.n_gslots, g->Vmax,
                                                                         static_cast<uint32_t>(gr.sources), st),
                    "launching the global relaxation");
         } else {
@@ -774,7 +793,7 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
 rn_status enqueue_sort_fallback(const Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, hipStream_t s) {
     const CallBuffers b = call_buffers(ws, p);
     // (the scattered records: recs[0] where the selection filled recs[1])
-    RN_HIP(launch_sort_out(b, p.bin_log2 ? 0 : 1, p.max_passes, p.vb, out, static_cast<unsigned long long>(cap), s),
+    RN_HIP(launch_sort_out(b, p.mixed_bins ? 0 : 1, p.max_passes, p.vb, out, static_cast<unsigned long long>(cap), s),
            "sorting pairs");
     return RN_OK;
 }

@@ -167,7 +167,8 @@ struct Prepared {
     size_t desc_bytes = 0, off_ebase = 0, off_rbase = 0, off_perm = 0;
     // bucket sort (theta-join calls with few bins); nbins = 0: radix sort
     uint32_t nbins = 0;
-    uint32_t bin_log2 = 0;          // 2^bin_log2 bins a query (calls with k closest pairs), 0: theta + 1
+    bool mixed_bins = false;        // bins of several distances (calls with k closest pairs), else theta + 1
+                                    // bins a query
     bool small_sort = false;        // k-closest-pairs calls with few candidates: launch_sort_small
     std::vector<uint32_t> binbase;
     size_t off_bins = 0, off_binbase = 0;

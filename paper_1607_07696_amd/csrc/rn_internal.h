@@ -204,7 +204,7 @@ struct CallBuffers {
     uint32_t *sort_hist;        // sort_hist_words() words
     const uint32_t *binbase;    // bucket sort: [nq+1] first bin of each query (query order)
     uint32_t nbins;             //   bins (query, dist >> shift); 0 when the call uses another sort
-    uint32_t bin_log2;          //   0: shift 0, theta + 1 bins a query; else 2^bin_log2 bins a query
+    uint32_t mixed_bins;        //   0: shift 0, theta + 1 bins a query; 1: a power of two of them a query
     uint32_t *bins;             //   count | cursor (both zeroed) | start | chunk start, bin_stride(nbins)
                                 //   words each (one more chunk start)
     uint32_t *stage_scratch;    // stage_scratch_words(rwords) words
@@ -342,9 +342,9 @@ constexpr uint32_t kSortPassesMax = 16;
 constexpr int32_t kMaxQueries = 65536;
 
 // Bucket sort.  Calls with k-closest-pairs queries (of more candidates than the
-// small sort takes) use up to kMixedBins bins of equal width per query, 2^bin_log2
-// of them from 0 to its final bound; the selection counts the records per bin as
-// it keeps them.  Calls of theta-joins only whose bins (query, dist), theta+1
+// small sort takes) use up to kMixedBins bins, a power of two of equal width for
+// each query from 0 to its final bound; the selection counts the records per bin
+// as it keeps them.  Calls of theta-joins only whose bins (query, dist), theta+1
 // per query, number at most kMaxBins: the relaxation kernels count the records
 // per bin as they store them (the count's old value is the record's place in
 // its bin); the layout launch scans the counts; the scatter copies each record

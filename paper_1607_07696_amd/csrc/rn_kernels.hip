@@ -3122,12 +3122,14 @@ __device__ __forceinline__ uint32_t bitlen32(uint32_t x) { return x ? 32u - stat
 
 // Bin of a kept record (q: its query).
 __device__ __forceinline__ uint32_t rec_bin(const CallBuffers &b, uint32_t q, uint32_t d) {
+    const uint32_t first = b.binbase[q];
     uint32_t shift = 0;
-    if (b.bin_log2 != 0) {
+    if (b.mixed_bins) {
         const uint32_t bits = bitlen32(b.qd[q].k ? b.qs[q].bound : b.qd[q].theta);
-        shift = bits > b.bin_log2 ? bits - b.bin_log2 : 0u;
+        const uint32_t have = bitlen32(b.binbase[q + 1] - first) - 1u;   // (a power of two)
+        shift = bits > have ? bits - have : 0u;
     }
-    return b.binbase[q] + (d >> shift);
+    return first + (d >> shift);
 }
 
 __global__ __launch_bounds__(256) void k_select(CallBuffers b) {
@@ -3189,7 +3191,7 @@ __global__ __launch_bounds__(256) void k_select(CallBuffers b) {
         if (lane_id() == 0) base = atomicAdd(&s_cnt, popc(mk));
         base = readlane(base, 0);
         if (keep) {
-            if (b.bin_log2 != 0) r.q |= bin_place(atomicAdd(&b.bins[rec_bin(b, r.q, r.d)], 1u));
+            if (b.mixed_bins) r.q |= bin_place(atomicAdd(&b.bins[rec_bin(b, r.q, r.d)], 1u));
             kept[s_base + base + mbcnt(mk)] = r;
         }
     }
@@ -4074,9 +4076,9 @@ hipError_t launch_sort_small(const CallBuffers &b, uint32_t qb, uint32_t vb, rn_
 hipError_t launch_bucket_sort(const CallBuffers &b, rn_pair *out, unsigned long long user_cap, const uint32_t *state,
                               uint32_t *state_map, uint32_t state_words, hipStream_t s) {
     // (the selection, where one counts the bins, has moved the records to recs[1])
-    Rec *in = b.recs[b.bin_log2 ? 1 : 0], *mid = b.recs[b.bin_log2 ? 0 : 1];
+    Rec *in = b.recs[b.mixed_bins ? 1 : 0], *mid = b.recs[b.mixed_bins ? 0 : 1];
     hipLaunchKernelGGL(k_bucket_scatter, dim3(1024), dim3(256), 0, s, b, in, mid);
-    if (b.bin_log2)
+    if (b.mixed_bins)
         hipLaunchKernelGGL((k_bucket_rank<true>), dim3(1024), dim3(256), 0, s, b, mid, out, user_cap, state, state_map,
                            state_words);
     else
