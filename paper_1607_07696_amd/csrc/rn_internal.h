@@ -273,7 +273,8 @@ constexpr uint32_t compact_disp_bits(int hash_log2) { return hash_log2 >= 14 ? 5
 constexpr uint32_t compact_max_dist(int hash_log2) {
     return (1u << (7u + static_cast<uint32_t>(hash_log2) - compact_disp_bits(hash_log2))) - 2u;
 }
-// Compact tables are used from this size on.  Their 12 KiB (2^11) and 8 KiB
+// Compact tables are used from this size on (by window searches; over quads from
+// 2^8 on, where the distances fit).  Their 12 KiB (2^11) and 8 KiB
 // (2^10) per search hold 12 and 18 searches per CU against the wide tables' 8
 // and 12, which outweighs their longer arithmetic (2^11 at theta = 3000:
 // 0.224 against 0.268 ms); at 2^9 both hold 18 or more, and the wide table's

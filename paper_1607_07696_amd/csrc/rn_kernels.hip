@@ -5,16 +5,18 @@
 //   stage     validate every query's R and S, set its S-membership bitmap and
 //             list all sources query by query (k_mark, k_rank_emit)
 //   seed      k-closest pairs: a first distance bound per query from the
-//             direct R-S arcs (k_kcp_seed_*); a query whose bound is below twice
-//             the lightest arc is answered here, one thread per source (k_kcp_direct)
+//             direct R-S arcs (k_kcp_seed_*) or a guess; a query whose bound is below
+//             twice the lightest arc is answered here, one thread per source (k_kcp_direct)
 //   relax     one wavefront per source: a bounded, bucketed label-correcting
 //             search whose whole state (distance table, pending set, frontier)
-//             lives in LDS; emits (u, v, dist, query) for v in S (k_join), with
-//             larger tables and a global-memory tier for searches that outgrow
-//             the first
+//             lives in LDS; emits (u, v, dist, query) for v in S (k_join, over arc
+//             quads or windows of arcs), with larger tables, several waves per
+//             search, and a global-memory tier for searches that outgrow the first
 //   select    k-closest pairs: keep the records within the final bounds
-//   sort      LSD radix sort of the records on the (query, dist, u, v) key;
-//             the last digit pass writes each query's segment of the output
+//   sort      by bins (query, distance range) and rank within a bin, or an LSD
+//             radix sort, on the (query, dist, u, v) key; few records in one block
+// A small call of one query takes its staging and everything behind its searches
+// in one block each (k_stage_one, k_tail_one).
 //
 // The queries are the paper's theta-join and k-closest pairs (Abstract;
 // Section 1; Section 4).  The per-source search plays the role of the paper's
