@@ -683,14 +683,20 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
         t.send = gr.end < p.nq ? &b.qs[p.perm[gr.end]].src_start : &b.ctl->nsrc;
         if (early_global && gi == ng - 1) {
             // searches sure to outgrow every table: the global tier at once
+            // over quads, what outgrows the ring goes to a list that a later
+            // launch of the general tier takes: list 3 where the re-queued
+            // searches run over quads too, else list 2 with theirs.  (Each
+            // launch that may search a source again counts its discoveries apart.)
             hipStream_t st = gside ? ws.side[0] : s;
-            t.tier = 3;
+            const bool early_dense = g->dense && gr.sources <= kDenseSources;
+            const int li = dense ? 3 : 2;
+            t.tier = early_dense && !dense ? 4 : 3;
             t.work = ws.d_block + p.off_work + 32;
-            t.ovf = b.list[3];
-            t.ovfq = b.listq[3];
-            t.novf = &b.ctl->nlist[3];
-            RN_HIP((g->dense && gr.sources <= kDenseSources ? launch_join_dense : launch_join_global)(t, ws.d_gslots, ws.n_gslots, g->Vmax,
-                                                                        static_cast<uint32_t>(gr.sources), st),
+            t.ovf = b.list[li];
+            t.ovfq = b.listq[li];
+            t.novf = &b.ctl->nlist[li];
+            RN_HIP((early_dense ? launch_join_dense : launch_join_global)(t, ws.d_gslots, ws.n_gslots, g->Vmax,
+                                                                         static_cast<uint32_t>(gr.sources), st),
                    "launching the global relaxation");
         } else {
             // (without global-tier slots yet, a global group takes the largest

@@ -166,7 +166,8 @@ struct JoinArgs {
     const uint32_t *binbase;    //   first bin of each query
     int32_t first_tier;         // 1: count re-queued searches in ctl->nretry
     int32_t tier;               // 0 first table, 1 and 2 the re-run tables, 3 the global tier, 4 the
-                                //   global tier after that over quads
+                                //   global tier after that over quads (or, before it, the early
+                                //   one over quads of a call whose re-queued searches do not run so)
     int32_t one;                // 1: the call has one query (its records are counted in ctl only)
     int32_t count_work;         // 1: accumulate ctl->arcs / ctl->settled
     int32_t big_deg;            // 1: some vertex has 2^16 or more arcs (searches reaching one move on)
