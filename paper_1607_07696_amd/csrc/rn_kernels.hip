@@ -1945,9 +1945,13 @@ __device__ void search_quads_block(QuadLds<HB, CT> &L, QuadBlock &B, const JoinA
         s0 = s1;
         __syncthreads();   // every append of the step is done
     }
-    static_assert(T::RC / NW >= 64, "a wave's staging slice holds a table row's pairs");
-    emit_and_clear<HB, CT, true>(L, a, c, u, current_bound(c), ovf, L.ring + wv * (T::RC / NW), T::RC / NW,
-                                 wv * 64u * table_rows<HB>(), NW * 64u * table_rows<HB>(), tseen);
+    constexpr uint32_t SL = T::RC / NW;   // each wave's slice of the ring, for staging
+    static_assert(SL >= 64, "a wave's staging slice holds a table row's pairs");
+    emit_and_clear<HB, CT, true>(L, a, c, u, current_bound(c), ovf, L.ring + wv * SL, SL, wv * 64u * table_rows<HB>(),
+                                 NW * 64u * table_rows<HB>(), tseen);
+    // (each wave has cleared its slice; three do not divide 2^12's ring)
+    static_assert(T::RC - NW * SL <= 64u * NW, "the entries behind the slices are cleared at once");
+    if (threadIdx.x < T::RC - NW * SL) L.ring[NW * SL + threadIdx.x] = make_uint2(0u, 0u);
     if (ovf && threadIdx.x == 0) queue_next_tier(a, c, u);
     __syncthreads();   // the table is clear and B is free before the next source
 }
