@@ -662,10 +662,9 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
     uint64_t searches = 0;
     for (const Group &gr : p.groups) searches += gr.sources;
     const bool dense = g->dense && searches <= kDenseSources;
-    if (ng > static_cast<size_t>(kSide) + 1) return fail(RN_ERR_DEVICE, "too many first-tier groups");
     const bool early_global = ng > 0 && p.groups[ng - 1].hb == kGlobalHB && ws.d_gslots != nullptr;
     const size_t non = ng - (early_global ? 1 : 0);                  // on-chip groups
-    const size_t ons = shared ? 1 : std::max<size_t>(1, std::min<size_t>(non, 3));   // their streams
+    const size_t ons = shared ? 1 : std::max<size_t>(1, std::min<size_t>(non, kOnChipStreams));   // their streams
     const size_t gside = early_global && !shared ? 1 : 0;             // side stream 0: the global group
     const bool fork = ons > 1 || gside > 0;
     if (fork) {

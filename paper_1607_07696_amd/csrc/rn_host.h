@@ -55,7 +55,8 @@ void host_free(T *&p) {
 // Stage timing events (used when profiling is on).
 enum { EV_START, EV_STAGED, EV_TIER0, EV_RELAXED, EV_SELECTED, EV_DONE, EV_COUNT };
 
-constexpr int kSide = 2 * (kMaxHB - kMinHB + 1) - 1;   // side streams: one per first-tier launch beyond the first
+constexpr int kOnChipStreams = 3;          // the on-chip groups share at most so many streams, the call's among them
+constexpr int kSide = kOnChipStreams;       // side streams: two of those, and one for a global group
 constexpr unsigned long long kRecCapMax = 1ull << 31;
 
 // Ball sizes whose radii are measured when a graph is loaded (2^3 .. 2^8 vertices).
