@@ -65,7 +65,7 @@ rn_status carve(uint32_t *base, const Prepared &p, int32_t Vmax, uint32_t nslots
     const size_t nsrc = std::max<size_t>(p.total_R, 1);
     const size_t fixed = round_up(p.block_words, 64) + round_up((p.desc_bytes + 3) / 4, 64) +
                          round_up(stage_scratch_words(p.rbits_words), 64) + round_up(state_words, 64) +
-                         (2 + 2 * kLists) * round_up(nsrc, 64);
+                         (2 + 2 * (kLists - 1)) * round_up(nsrc, 64);
     const size_t sw = nslots ? global_slot_words(Vmax) : 0;
     if (fixed + nslots * sw + 64 * 8 > kScratchWords) return fail(RN_ERR_NOMEM, "the call does not fit the scratch array");
     ws.d_block = take(p.block_words);
@@ -77,10 +77,16 @@ rn_status carve(uint32_t *base, const Prepared &p, int32_t Vmax, uint32_t nslots
     ws.d_state_map = take(state_words);
     ws.d_src = reinterpret_cast<int32_t *>(take(nsrc));
     ws.d_srcq = take(nsrc);
-    for (int i = 0; i < kLists; ++i) {
+    // (list 3 takes the place of list 0: one query's searches all start in one
+    // tier, so list 0 is empty or has been searched again by the time a launch
+    // over quads queues what outgrows its ring)
+    static_assert(kLists == 4, "re-run lists 0 to 3");
+    for (int i = 0; i < 3; ++i) {
         ws.d_list[i] = reinterpret_cast<int32_t *>(take(nsrc));
         ws.d_listq[i] = take(nsrc);
     }
+    ws.d_list[3] = ws.d_list[0];
+    ws.d_listq[3] = ws.d_listq[0];
     ws.src_cap = nsrc;
     if (nslots) {
         ws.d_gslots = take(nslots * sw);

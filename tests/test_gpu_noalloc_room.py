@@ -1,0 +1,39 @@
+"""rn_dist_join_noalloc: the largest source list its scratch array takes."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rnmod():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_1607_07696_amd import rn
+    rn.load_library()
+    return rn
+
+
+def noalloc(rnmod, net, R, S, theta, cap):
+    import torch
+    lib, n = rnmod.load_library(), C.c_int64(-1)
+    Rd, Sd = torch.from_numpy(R).cuda(), torch.from_numpy(S).cuda()
+    out = torch.zeros((max(cap, 1), 3), dtype=torch.int32, device="cuda")
+    st = lib.rn_dist_join_noalloc(net._h, C.c_void_p(Rd.data_ptr()), len(R), C.c_void_p(Sd.data_ptr()), len(S),
+                                  C.c_uint32(theta), C.c_void_p(out.data_ptr()), cap, C.byref(n),
+                                  C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == rnmod.RN_OK, lib.rn_last_error()
+    return rnmod.pairs_to_numpy(out[:n.value])
+
+
+def test_source_list_near_the_limit(rnmod):
+    # 8 words a source (the list, three re-run lists and their queries) of the
+    # array's 2^25, beside 2^20 and a few of sorting scratch and the bitmaps
+    V, nR = 4_000_000, 3_900_000
+    net = rnmod.RoadNetwork(np.zeros(V + 1, dtype=np.int32), np.zeros(0, dtype=np.int32), np.zeros(0, dtype=np.uint32))
+    R, S = np.arange(nR, dtype=np.int32), np.arange(V - 10, V, dtype=np.int32)
+    assert len(noalloc(rnmod, net, R, S, 0, 0)) == 0
+
