@@ -665,7 +665,9 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
     const bool early_global = ng > 0 && p.groups[ng - 1].hb == kGlobalHB && ws.d_gslots != nullptr;
     const size_t non = ng - (early_global ? 1 : 0);                  // on-chip groups
     const size_t ons = shared ? 1 : std::max<size_t>(1, std::min<size_t>(non, kOnChipStreams));   // their streams
-    const size_t gside = early_global && !shared ? 1 : 0;             // side stream 0: the global group
+    // side stream 0: the global group (with nothing beside it, it stays on this
+    // one: a workspace carved from the static array has no events to fork with)
+    const size_t gside = early_global && !shared && ng > 1 ? 1 : 0;
     const bool fork = ons > 1 || gside > 0;
     if (fork) {
         RN_TRY(ensure_side_streams(ws, gside + ons - 1));

@@ -1,4 +1,6 @@
-"""rn_dist_join_noalloc: the largest source list its scratch array takes."""
+"""rn_dist_join_noalloc: the largest source list its scratch array takes, and
+whole-graph searches that outgrow the ring of the quad form (re-run lists share
+places there)."""
 import ctypes as C
 
 import numpy as np
@@ -37,3 +39,16 @@ def test_source_list_near_the_limit(rnmod):
     R, S = np.arange(nR, dtype=np.int32), np.arange(V - 10, V, dtype=np.int32)
     assert len(noalloc(rnmod, net, R, S, 0, 0)) == 0
 
+
+@pytest.mark.parametrize("nR", [3, 70])
+def test_whole_graph_searches(rnmod, orc, rg, nR):
+    n = 100000
+    rng = np.random.default_rng(8)
+    p, q = rng.permutation(n), rng.permutation(n)
+    g = rg.from_edges(n, np.concatenate([p, q]), np.concatenate([np.roll(p, 1), np.roll(q, 1)]),
+                      rng.integers(90, 111, size=2 * n), symmetric=True)
+    net = rnmod.RoadNetwork.from_graph(g)
+    R, S = np.arange(nR, dtype=np.int32), np.arange(1000, 3000, dtype=np.int32)
+    want = orc.dist_join(g, R, S, 0xFFFFFFFE).pairs
+    got = noalloc(rnmod, net, R, S, 0xFFFFFFFE, len(want))
+    assert got.shape == want.shape and np.array_equal(got, want)
