@@ -1691,11 +1691,15 @@ void rn_plan_free(rn_plan *p) {
 
 namespace {
 
+void drop_graph(rn_plan *pl) {
+    if (pl->exec) (void)hipGraphExecDestroy(pl->exec), pl->exec = nullptr;
+    if (pl->graph) (void)hipGraphDestroy(pl->graph), pl->graph = nullptr;
+}
+
 // Capture the plan's call into a graph (descriptors already uploaded).
 rn_status capture_plan(rn_plan *pl, const Prepared &p) {
     rn_graph *g = pl->g;
-    if (pl->exec) (void)hipGraphExecDestroy(pl->exec), pl->exec = nullptr;
-    if (pl->graph) (void)hipGraphDestroy(pl->graph), pl->graph = nullptr;
+    drop_graph(pl);
     RN_HIP(hipStreamBeginCapture(pl->cap_stream, hipStreamCaptureModeThreadLocal), "starting the capture");
     const rn_status st = enqueue_call(g, pl->ws, p, pl->out, pl->cap, pl->cap_stream, false);
     hipGraph_t graph = nullptr;
@@ -1756,7 +1760,7 @@ rn_status rn_plan_create(rn_graph *g, const rn_query *q, int32_t nq, rn_pair *ou
 }
 
 rn_status rn_plan_run(rn_plan *pl, int64_t *offsets, int32_t *status, void *stream) {
-    if (!pl || !pl->exec) return fail(RN_ERR_ARG, "plan is NULL");
+    if (!pl) return fail(RN_ERR_ARG, "plan is NULL");
     if (!offsets) return fail(RN_ERR_ARG, "offsets is NULL");
     rn_graph *g = pl->g;
     BusyGuard guard(g);
@@ -1764,14 +1768,21 @@ rn_status rn_plan_run(rn_plan *pl, int64_t *offsets, int32_t *status, void *stre
     RN_HIP(hipSetDevice(g->device), "selecting the device");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     Prepared &p = pl->prep;
+    if (!pl->exec) {   // the last run could not build it again
+        RN_TRY(prepare_again(g, pl->q.data(), p, 0));
+        return plan_build(pl, p, s, offsets, status);
+    }
     RN_HIP(hipGraphLaunch(pl->exec, s), "launching the graph");
     RN_TRY(read_back(pl->ws, p, s));
     bool regrow = false;
     uint32_t unmet = 0;
     const rn_status st = finish(g, pl->ws, p, pl->out, pl->cap, offsets, status, false, &regrow, &unmet, s);
     if (!regrow) return st;
+    // the records outgrew the buffer (grown by finish): run eagerly, re-capture.
+    // The graph names buffers that may be freed on the way: it goes first, so
+    // that after a failure the next run builds it instead of replaying it
+    drop_graph(pl);
     if (st == RN_OK && unmet) RN_TRY(prepare_again(g, pl->q.data(), p, unmet));   // (from now on)
-    // the records outgrew the buffer (grown by finish): run eagerly, re-capture
     return plan_build(pl, p, s, offsets, status);
 }
 

@@ -1,0 +1,61 @@
+"""A plan whose records outgrow their buffers while the device has no room for
+larger ones: the replay reports it, and so does the next; with room again, the
+plan is built again and answers."""
+import contextlib
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@contextlib.contextmanager
+def little_memory():
+    """All but some 64 MB of the device's memory taken."""
+    import torch
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hogs, size = [], torch.cuda.mem_get_info()[0]
+    try:
+        while size >= 32 << 20:
+            try:
+                hogs.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
+            except torch.cuda.OutOfMemoryError:
+                size //= 2
+        hogs.pop()
+        torch.cuda.empty_cache()
+        yield
+    finally:
+        hogs.clear()
+        torch.cuda.empty_cache()
+
+
+def test_rebuild_without_memory(orc, rg):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_1607_07696_amd import rn
+    a, b = rg.road_graph(100, 3), rg.road_graph(60, 4)     # two components
+    src = np.concatenate([np.repeat(np.arange(a.V), np.diff(a.row_ptr)),
+                          a.V + np.repeat(np.arange(b.V), np.diff(b.row_ptr))])
+    g = rg.from_edges(a.V + b.V, src, np.concatenate([a.col, a.V + b.col]), np.concatenate([a.w, b.w]), symmetric=False)
+    n = 2500
+    ids = np.random.default_rng(1).permutation(a.V).astype(np.int32)
+    R, near, away = ids[:n], ids[n:2 * n], a.V + np.arange(n, dtype=np.int32)
+    want = orc.dist_join(g, R, near, 0xFFFFFFFE).pairs
+    assert len(want) == n * n
+    net = rn.RoadNetwork.from_graph(g)
+    Sd = torch.from_numpy(away.copy()).cuda()
+    q, keep = net.make_queries([{"R": R, "S": Sd}])
+    plan = net.plan(q, cap=n * n)
+    assert len(plan.run()[0]) == 0
+    Sd.copy_(torch.from_numpy(near))
+    torch.cuda.synchronize()
+    # 6.25 million pairs want two record buffers of 125 MB
+    with little_memory():
+        for _ in range(2):
+            with pytest.raises(rn.RnError):
+                plan.run()
+    for _ in range(3):
+        got = rn.pairs_to_numpy(plan.run()[0])
+        assert got.shape == want.shape and np.array_equal(got, want)
