@@ -1025,16 +1025,25 @@ void choose_quads(rn_graph *g, const std::vector<int32_t> &rrow) {
     }
 }
 
-// Lay out the device copy's arcs as quads.
+// Lay out the device copy's arcs as quads.  A graph whose quads the device has no
+// room for goes without them.
 rn_status upload_quads(rn_graph *g) {
+    if (!g->quads) return RN_OK;
     const size_t dirs = g->rev_rpo ? 2 : 1;
     const uint32_t nquads = g->qbase.back();
     hipError_t e = hipSuccess;
     const size_t ngr = static_cast<size_t>(g->ngraphs), nv = g->voff.size(), nb = dirs * ngr;
     if ((!g->d_quads && (e = dev_alloc(&g->d_quads, 4 * static_cast<size_t>(nquads))) != hipSuccess) ||
         (!g->d_further && (e = dev_alloc(&g->d_further, static_cast<size_t>(nquads))) != hipSuccess) ||
-        (!g->d_qgraph && (e = dev_alloc(&g->d_qgraph, nv + 2 * nb)) != hipSuccess) ||
-        (e = hipMemcpy(g->d_qgraph, g->voff.data(), nv * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess ||
+        (!g->d_qgraph && (e = dev_alloc(&g->d_qgraph, nv + 2 * nb)) != hipSuccess)) {
+        (void)hipGetLastError();   // (not for the next launch to report)
+        dev_free(g->d_quads);
+        dev_free(g->d_further);
+        dev_free(g->d_qgraph);
+        g->quads = g->dense = false;
+        return RN_OK;
+    }
+    if ((e = hipMemcpy(g->d_qgraph, g->voff.data(), nv * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipMemcpy(g->d_qgraph + nv, g->qbase.data(), nb * sizeof(uint32_t), hipMemcpyHostToDevice)) != hipSuccess ||
         (e = launch_build_quads(g->d_row_ptr, g->d_arcs, g->d_further, g->d_qgraph,
                                 reinterpret_cast<const uint32_t *>(g->d_qgraph + nv),
@@ -1144,7 +1153,7 @@ rn_status upload_csr(rn_graph *g, const int32_t *perm) {
         (!arcs.empty() &&
          (e = hipMemcpy(g->d_arcs, arcs.data(), arcs.size() * sizeof(ArcRec), hipMemcpyHostToDevice)) != hipSuccess))
         return hip_fail(e, "uploading the graph");
-    return g->quads ? upload_quads(g) : RN_OK;
+    return RN_OK;
 }
 
 }  // namespace
@@ -1283,6 +1292,7 @@ rn_status rn_graph_load_many(int32_t n, const int32_t *V, const int64_t *A, cons
                                          hipMemcpyHostToDevice)) != hipSuccess)))
             st = hip_fail(e, "uploading the vertex maps");
     }
+    if (st == RN_OK) st = upload_quads(g);
     if (st != RN_OK) {
         rn_graph_free(g);
         return st;
@@ -1554,6 +1564,7 @@ rn_status rn_partition(rn_graph *g, float alpha, int32_t max_leaf, int32_t *part
     RN_HIP(hipSetDevice(g->device), "selecting the device");
     RN_HIP(hipDeviceSynchronize(), "waiting for the device");
     RN_TRY(upload_csr(g, perm.data()));
+    RN_TRY(upload_quads(g));
     RN_HIP(hipMemcpy(g->d_rank, rank.data(), rank.size() * sizeof(int32_t), hipMemcpyHostToDevice), "uploading ranks");
     RN_HIP(hipMemcpy(g->d_order, order.data(), order.size() * sizeof(int32_t), hipMemcpyHostToDevice),
            "uploading ranks");
