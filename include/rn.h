@@ -437,7 +437,18 @@ typedef struct rn_stats {
     int32_t retried;     /* sources re-run after outgrowing the first on-chip table */
     int32_t global_searches; /* sources that outgrew every on-chip table (global-memory tier) */
     int32_t relax_launches; /* relaxation launches (on-chip tiers + the global tier) */
+    int32_t route;       /* RN_ROUTE_* bits: the forms the call's work took */
 } rn_stats;
+
+/* Bits of rn_stats.route. */
+#define RN_ROUTE_QUADS 1         /* some first searches ran over arc quads */
+#define RN_ROUTE_WINDOWS 2       /* some first searches ran over arc windows */
+#define RN_ROUTE_SHORT 4         /* the short form of small one-query calls */
+#define RN_ROUTE_SHORT_LEFT 8    /* it handed the call over to the general form */
+#define RN_ROUTE_GUESS 16        /* some k-closest-pairs query started from a guessed bound */
+#define RN_ROUTE_GUESS_MISSED 32 /* some such query had fewer than k pairs within it */
+#define RN_ROUTE_DENSE_FULL 64   /* a whole-graph search over quads outgrew its ring */
+#define RN_ROUTE_RESORTED 128    /* the radix sort took over from another sort */
 
 /* Profiling flags for rn_set_profiling. */
 #define RN_PROFILE_TIMES 1  /* HIP-event timing of each stage (times are 0 otherwise) */

@@ -901,6 +901,22 @@ rn_status finish(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, in
     return RN_OK;
 }
 
+// RN_ROUTE_* bits of a call as it was enqueued and ended.
+int32_t route_of(const Workspace &ws, const Prepared &p) {
+    const CallCtl &c = *reinterpret_cast<const CallCtl *>(ws.h_state);
+    int32_t r = 0;
+    for (const Group &gr : p.groups)
+        if (gr.hb <= kMaxHB) r |= gr.quads ? RN_ROUTE_QUADS : RN_ROUTE_WINDOWS;
+    for (const QueryDesc &d : p.qd)
+        if (d.guess != kInf) r |= RN_ROUTE_GUESS;
+    if (p.tail_one) r |= RN_ROUTE_SHORT;
+    if (p.tail_one && ((c.unmet & kUnmetTail) || (c.nlist[0] | c.nlist[1] | c.nlist[2]))) r |= RN_ROUTE_SHORT_LEFT;
+    if (c.unmet & kUnmetGuess) r |= RN_ROUTE_GUESS_MISSED;
+    if (c.nfull) r |= RN_ROUTE_DENSE_FULL;
+    if (c.resort) r |= RN_ROUTE_RESORTED;
+    return r;
+}
+
 // Prepare a call again after its state reported unmet (kUnmet* bits).
 rn_status prepare_again(const rn_graph *g, const rn_query *q, Prepared &p, uint32_t unmet) {
     const bool guesses = p.guesses && !(unmet & kUnmetGuess);
@@ -911,6 +927,7 @@ rn_status prepare_again(const rn_graph *g, const rn_query *q, Prepared &p, uint3
 // the record buffer was too small, and without guesses when one was not met.
 rn_status run_eager(rn_graph *g, Workspace &ws, Prepared &p, const rn_query *q, rn_pair *out, int64_t cap,
                     int64_t *offsets, int32_t *status, hipStream_t s, bool timed) {
+    int32_t route = 0;
     for (int attempt = 0; attempt < 6; ++attempt) {
         RN_TRY(ensure_buffers(ws, p));
         if (p.nq > 1) {   // (one query's descriptors go with the first kernel)
@@ -919,9 +936,11 @@ rn_status run_eager(rn_graph *g, Workspace &ws, Prepared &p, const rn_query *q, 
         }
         RN_TRY(enqueue_call(g, ws, p, out, cap, s, timed));
         RN_TRY(read_back(ws, p, s));
+        route |= route_of(ws, p);
         bool regrow = false;
         uint32_t unmet = 0;
         const rn_status st = finish(g, ws, p, out, cap, offsets, status, timed, &regrow, &unmet, s);
+        if (timed) g->stats.route = route;
         if (!regrow) return st;
         if (st == RN_OK && unmet) RN_TRY(prepare_again(g, q, p, unmet));
     }

@@ -119,7 +119,7 @@ struct CallCtl {
     uint32_t resort;            // the call's sort left the output to the radix sort (a bucket-sort bin
                                 //   above kBucketRankMax records, or more than kSmallSort candidates)
     uint32_t unmet;             // kUnmet* bits: the call is to be run again in another form
-    uint32_t pad;
+    uint32_t nfull;             // whole-graph searches over quads that outgrew their ring
 };
 static_assert(sizeof(CallCtl) == 96, "CallCtl is 96 bytes");
 

@@ -2711,7 +2711,10 @@ __global__ __launch_bounds__(1024) void k_join_dense(JoinArgs a, uint32_t *slots
         }
         for (uint32_t j = tid; j < min(st.tail, kDRing); j += kDT) L.ring[j] = make_uint2(0u, 0u);
         if (tid == 0) {
-            if (ovf) queue_next_tier(a, c, u);
+            if (ovf) {
+                queue_next_tier(a, c, u);
+                atomicAdd(&a.ctl->nfull, 1u);
+            }
             L.si = gridDim.x + atomicAdd(a.work, 1u);
         }
         __syncthreads();   // the slot and the ring are clean before the next source starts

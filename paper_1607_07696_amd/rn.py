@@ -16,6 +16,8 @@ LIB_PATH = os.path.join(HERE, "librn.so")
 
 RN_OK, RN_ERR_ARG, RN_ERR_NOMEM, RN_ERR_CAPACITY, RN_ERR_DEVICE, RN_ERR_BUSY = 0, -1, -2, -3, -4, -5
 RN_PROFILE_TIMES, RN_PROFILE_WORK = 1, 2
+(RN_ROUTE_QUADS, RN_ROUTE_WINDOWS, RN_ROUTE_SHORT, RN_ROUTE_SHORT_LEFT, RN_ROUTE_GUESS, RN_ROUTE_GUESS_MISSED,
+ RN_ROUTE_DENSE_FULL, RN_ROUTE_RESORTED) = (1 << i for i in range(8))
 PAIR_DTYPE = np.dtype([("u", "<i4"), ("v", "<i4"), ("dist", "<u4")])
 
 # Every symbol include/rn.h declares.
@@ -71,7 +73,7 @@ class Stats(C.Structure):
                 ("select_ms", C.c_float), ("sort_ms", C.c_float), ("total_ms", C.c_float),
                 ("pairs", C.c_int64), ("arcs", C.c_int64), ("settled", C.c_int64),
                 ("retried", C.c_int32), ("global_searches", C.c_int32),
-                ("relax_launches", C.c_int32)]
+                ("relax_launches", C.c_int32), ("route", C.c_int32)]
 
     def as_dict(self) -> dict:
         return {f: getattr(self, f) for f, _ in self._fields_}
