@@ -238,6 +238,7 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
     p.groups.clear();
     p.nq = nq;
     p.guesses = guesses;
+    p.short_form = short_form;
     p.qd.resize(nq);
     p.ebase.assign(nq + 1, 0);
     p.rbase.assign(nq + 1, 0);
@@ -400,8 +401,10 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
     // other calls with k closest pairs: bins of equal width up to each query's
     // final bound, as many as kMixedBins allows.  (32 mixed queries, 10 digit
     // passes: the radix sort's 30 launches took 115 us.)
+    // A call in the short form keeps some for a hand-over: then it has far more
+    // records than expected.
     p.mixed_bins = false;
-    if (p.any_kcp && !p.small_sort && !p.tail_one && nq <= static_cast<int32_t>(kMixedBins / 16)) {
+    if ((p.any_kcp || p.tail_one) && !p.small_sort && nq <= static_cast<int32_t>(kMixedBins / 16)) {
         bool varied = true;
         for (int32_t i = 0; i < nq; ++i) varied = varied && g->varied[q[i].graph];
         if (varied) {
@@ -417,7 +420,7 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
                     const double r = static_cast<double>(x.theta) / std::max(1.0, g->wmean[x.graph]);
                     const double pairs = static_cast<double>(x.nR) * x.nS;
                     const double expect = x.k > 0 ? 1.5 * x.k : pairs * std::min(1.0, 2.5 * r * r / V);
-                    uint32_t n = 16;
+                    uint32_t n = p.tail_one ? 2048u : 16u;
                     while (n < 8192u && n * per < expect) n *= 2;
                     p.binbase[i] = static_cast<uint32_t>(nb);
                     nb += n;
@@ -597,12 +600,8 @@ static rn_status ensure_side_streams(Workspace &ws, size_t n) {
     return RN_OK;
 }
 
-// Enqueue the whole call on s (descriptors already on the device).  timed:
-// record the profiling events (never during graph capture).
-rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, hipStream_t s,
-                       bool timed, bool shared) {
-    const CallBuffers b = call_buffers(ws, p);
-    record(g, ws, timed, EV_START, s);
+// What the kernels of a call read, on buffers b.
+static JoinArgs join_args(const rn_graph *g, const Prepared &p, const CallBuffers &b) {
     JoinArgs a;
     std::memset(&a, 0, sizeof(a));
     a.row_ptr = g->d_row_ptr;
@@ -624,6 +623,35 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
     a.first = g->d_first;
     a.quads = g->d_quads;
     a.further = g->d_further;
+    return a;
+}
+
+// Whether the re-queued whole-graph searches of the call run over quads, and
+// whether its last group is searched in the global tier from the start, on a side
+// stream of its own (gside: how many).
+struct GlobalPlan {
+    bool dense;
+    bool early;
+    size_t gside;
+};
+static GlobalPlan global_plan(const rn_graph *g, const Workspace &ws, const Prepared &p, bool shared) {
+    const size_t ng = p.groups.size();
+    uint64_t searches = 0;
+    for (const Group &gr : p.groups) searches += gr.sources;
+    GlobalPlan gp;
+    gp.dense = g->dense && searches <= kDenseSources;
+    gp.early = ng > 0 && p.groups[ng - 1].hb == kGlobalHB && ws.d_gslots != nullptr;
+    // (with nothing beside it, it stays on the call's stream: a workspace carved
+    // from the static array has no events to fork with)
+    gp.gside = gp.early && !shared && ng > 1 ? 1 : 0;
+    return gp;
+}
+
+// Staging, bound seeding and the first tiers.
+static rn_status enqueue_searches(rn_graph *g, Workspace &ws, const Prepared &p, hipStream_t s, bool timed, bool shared) {
+    const CallBuffers b = call_buffers(ws, p);
+    const JoinArgs a = join_args(g, p, b);
+    record(g, ws, timed, EV_START, s);
     if (p.nq == 1) {
         DescWords desc;
         uint8_t raw[sizeof(desc.w)];
@@ -634,7 +662,7 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
         const uint32_t dn = static_cast<uint32_t>((p.desc_bytes + 3) / 4);
         uint32_t *dd = reinterpret_cast<uint32_t *>(ws.d_desc);
         if (p.stage_one)
-            RN_HIP(launch_stage_one(a, b, static_cast<uint32_t>(p.off_sbits), static_cast<uint32_t>(p.off_bins - p.off_hists),
+            RN_HIP(launch_stage_one(a, b, static_cast<uint32_t>(p.off_sbits), static_cast<uint32_t>(p.zero_words - p.off_hists),
                                     g->d_rank, desc, dn, dd, s),
                    "staging the query");
         else
@@ -659,15 +687,11 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
     // stream of its own that the re-run tiers do not wait for: only the later
     // global launch, which takes the same slots, waits for it.
     const size_t ng = p.groups.size();
-    uint64_t searches = 0;
-    for (const Group &gr : p.groups) searches += gr.sources;
-    const bool dense = g->dense && searches <= kDenseSources;
-    const bool early_global = ng > 0 && p.groups[ng - 1].hb == kGlobalHB && ws.d_gslots != nullptr;
+    const GlobalPlan gp = global_plan(g, ws, p, shared);
+    const bool dense = gp.dense, early_global = gp.early;
+    const size_t gside = gp.gside;
     const size_t non = ng - (early_global ? 1 : 0);                  // on-chip groups
     const size_t ons = shared ? 1 : std::max<size_t>(1, std::min<size_t>(non, kOnChipStreams));   // their streams
-    // side stream 0: the global group (with nothing beside it, it stays on this
-    // one: a workspace carved from the static array has no events to fork with)
-    const size_t gside = early_global && !shared && ng > 1 ? 1 : 0;
     const bool fork = ons > 1 || gside > 0;
     if (fork) {
         RN_TRY(ensure_side_streams(ws, gside + ons - 1));
@@ -719,20 +743,27 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
         for (size_t i = gside; i < gside + ons - 1; ++i) RN_HIP(hipStreamWaitEvent(s, ws.join[i], 0), "joining streams");
     }
     record(g, ws, timed, EV_TIER0, s);
-    const size_t state_bytes = sizeof(CallCtl) + static_cast<size_t>(p.nq) * sizeof(QueryState);
+    return RN_OK;
+}
+
+static size_t state_bytes(const Prepared &p) {
+    return sizeof(CallCtl) + static_cast<size_t>(p.nq) * sizeof(QueryState);
+}
+
+// Everything behind the first tiers, in the general form.  first_list: the re-run
+// list from which on there may be searches (3: none).
+static rn_status enqueue_rest(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, hipStream_t s,
+                              bool timed, bool shared, int first_list) {
+    const CallBuffers b = call_buffers(ws, p);
+    const JoinArgs a = join_args(g, p, b);
+    const GlobalPlan gp = global_plan(g, ws, p, shared);
+    const bool dense = gp.dense;
+    const size_t gside = gp.gside;
     const uint32_t *state = reinterpret_cast<const uint32_t *>(ws.d_block);
-    const uint32_t state_words = static_cast<uint32_t>(state_bytes / 4);
-    if (p.tail_one) {
-        record(g, ws, timed, EV_RELAXED, s);
-        record(g, ws, timed, EV_SELECTED, s);
-        RN_HIP(launch_tail_one(b, p.vb, out, static_cast<unsigned long long>(cap), state, ws.d_state_map, state_words, s),
-               "sorting pairs");
-        record(g, ws, timed, EV_DONE, s);
-        return RN_OK;
-    }
+    const uint32_t state_words = static_cast<uint32_t>(state_bytes(p) / 4);
     // re-runs: 2^11-slot tables, 2^14-slot tables, then the global tier
     const uint32_t maxs = static_cast<uint32_t>(p.total_R);
-    for (int li = 0; li < 2; ++li) {
+    for (int li = first_list; li < 2; ++li) {
         if (li == 0 && !p.need_list0) continue;
         if (li == 1 && !p.need_list1) continue;
         JoinArgs t = a;
@@ -752,7 +783,7 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
                "launching the relaxation");
     }
     if (gside) RN_HIP(hipStreamWaitEvent(s, ws.join[0], 0), "joining streams");   // the early global launch
-    if (ws.d_gslots) {   // (without slots the call is run again once they exist)
+    if (ws.d_gslots && first_list < 3) {   // (without slots the call is run again once they exist)
         JoinArgs t = a;
         t.src = b.list[2];
         t.srcq = b.listq[2];
@@ -774,9 +805,10 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
         RN_HIP(launch_join_global(t, ws.d_gslots, ws.n_gslots, g->Vmax, maxs, s), "launching the global relaxation");
     }
     record(g, ws, timed, EV_RELAXED, s);
-    if (p.any_kcp) RN_HIP(launch_select(b, s), "selecting candidates");
+    const bool select = p.any_kcp || p.mixed_bins;
+    if (select) RN_HIP(launch_select(b, s), "selecting candidates");
     const bool small = p.small_sort && p.nbins == 0;   // the small sort lays out the output itself
-    if (!small) RN_HIP(launch_layout(b, p.any_kcp ? 1 : 0, p.qb, p.vb, p.nbins != 0, s), "laying out the output");
+    if (!small) RN_HIP(launch_layout(b, select ? 1 : 0, p.qb, p.vb, p.nbins != 0, s), "laying out the output");
     record(g, ws, timed, EV_SELECTED, s);
     bool published = false;   // the sort's kernel published the call state itself
     if (p.nbins) {
@@ -789,12 +821,38 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
                "sorting pairs");
         published = true;
     } else {
-        RN_HIP(launch_sort_out(b, p.any_kcp ? 1 : 0, p.max_passes, p.vb, out, static_cast<unsigned long long>(cap), s),
+        RN_HIP(launch_sort_out(b, select ? 1 : 0, p.max_passes, p.vb, out, static_cast<unsigned long long>(cap), s),
                "sorting pairs");
     }
     record(g, ws, timed, EV_DONE, s);
     if (!published) RN_HIP(launch_publish(state, ws.d_state_map, state_words, s), "publishing the call state");
     return RN_OK;
+}
+
+// Enqueue the whole call on s (descriptors already on the device).  timed:
+// record the profiling events (never during graph capture).
+rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, hipStream_t s,
+                       bool timed, bool shared) {
+    RN_TRY(enqueue_searches(g, ws, p, s, timed, shared));
+    if (!p.tail_one) return enqueue_rest(g, ws, p, out, cap, s, timed, shared, 0);
+    record(g, ws, timed, EV_RELAXED, s);
+    record(g, ws, timed, EV_SELECTED, s);
+    RN_HIP(launch_tail_one(call_buffers(ws, p), p.vb, out, static_cast<unsigned long long>(cap),
+                           reinterpret_cast<const uint32_t *>(ws.d_block), ws.d_state_map,
+                           static_cast<uint32_t>(state_bytes(p) / 4), s),
+           "sorting pairs");
+    record(g, ws, timed, EV_DONE, s);
+    return RN_OK;
+}
+
+// Go on, in the general form, with a call whose short form handed it over (its
+// state read back): the records of its searches are there, what outgrew a table
+// is on the lists, and the bins and the counts of the tail are still zero.
+rn_status enqueue_handed_over(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, hipStream_t s,
+                              bool timed) {
+    const CallCtl &c = *reinterpret_cast<const CallCtl *>(ws.h_state);
+    return enqueue_rest(g, ws, p, out, cap, s, timed, false,
+                        c.nlist[0] ? 0 : (c.nlist[1] ? 1 : (c.nlist[2] ? 2 : 3)));
 }
 
 rn_status enqueue_sort_fallback(const Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, hipStream_t s) {
@@ -826,38 +884,36 @@ float elapsed(const rn_graph *g, const Workspace &ws, int a, int b) {
     return ms;
 }
 
+// Whether a call's short form met what it does not do: a search that outgrew its
+// table, or more records than its tail sorts.
+bool handed_over(const CallCtl &c) { return (c.nlist[0] | c.nlist[1] | c.nlist[2]) != 0 || (c.unmet & kUnmetTail) != 0; }
+
 // Turn the read-back state into offsets / status / the return code (after
 // the radix sort of a bucket-sorted call that found an oversized bin).
-// Sets *regrow when the call must run again (records outgrew the buffer, or
-// a search needed global-tier slots that did not exist yet), and *unmet with it
-// (kUnmet* bits) when that is to be without guessed bounds or the short form.
+// *next: what the call still needs.
+enum class Next {
+    kDone,
+    kAgain,        // run it again (records outgrew the buffer, or a search needed global-tier slots that did not exist yet)
+    kUnguessed,    // run it again without the guessed bounds that were not met
+    kHandOver,     // go on with it in the general form: the short form met what it does not do
+};
 rn_status finish(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, int64_t *offsets,
-                 int32_t *status, bool timed, bool *regrow, uint32_t *unmet, hipStream_t s) {
+                 int32_t *status, bool timed, Next *next, hipStream_t s) {
     const CallCtl &c = *reinterpret_cast<const CallCtl *>(ws.h_state);
     const QueryState *qs = reinterpret_cast<const QueryState *>(ws.h_state + sizeof(CallCtl));
-    *regrow = false;
-    *unmet = 0;
-    if (p.tail_one && (c.nlist[0] | c.nlist[1] | c.nlist[2]) != 0) {
-        // a search outgrew its table: the short form has no tier for it
-        *regrow = true;
-        *unmet = kUnmetTail;
-        return RN_OK;
-    }
-    if (c.nlist[2] > 0 && !ws.d_gslots) {
+    *next = Next::kDone;
+    if (c.nlist[2] > 0 && !ws.d_gslots && !p.tail_one) {
         // some search needed the global tier, which had no slots yet
-        *regrow = true;
+        *next = Next::kAgain;
         RN_TRY(ensure_gslots(ws, g->Vmax, c.nlist[2], s));
     }
-    if (c.npairs > ws.rec_cap && !*regrow) {
-        *regrow = true;
+    if (c.npairs > ws.rec_cap && *next == Next::kDone) {
+        *next = Next::kAgain;
         RN_TRY(grow_recs(ws, c.npairs));
     }
-    if (*regrow) return RN_OK;
-    if (c.unmet) {
-        *regrow = true;
-        *unmet = c.unmet;
-        return RN_OK;
-    }
+    if (*next == Next::kDone && p.tail_one && handed_over(c)) *next = Next::kHandOver;
+    if (*next == Next::kDone && (c.unmet & kUnmetGuess)) *next = Next::kUnguessed;
+    if (*next != Next::kDone) return RN_OK;
     if (c.resort) {
         RN_TRY(enqueue_sort_fallback(ws, p, out, cap, s));
         RN_HIP(hipStreamSynchronize(s), "waiting for the sort");
@@ -910,39 +966,42 @@ int32_t route_of(const Workspace &ws, const Prepared &p) {
     for (const QueryDesc &d : p.qd)
         if (d.guess != kInf) r |= RN_ROUTE_GUESS;
     if (p.tail_one) r |= RN_ROUTE_SHORT;
-    if (p.tail_one && ((c.unmet & kUnmetTail) || (c.nlist[0] | c.nlist[1] | c.nlist[2]))) r |= RN_ROUTE_SHORT_LEFT;
+    if (p.tail_one && handed_over(c)) r |= RN_ROUTE_SHORT_LEFT;
     if (c.unmet & kUnmetGuess) r |= RN_ROUTE_GUESS_MISSED;
     if (c.nfull) r |= RN_ROUTE_DENSE_FULL;
     if (c.resort) r |= RN_ROUTE_RESORTED;
     return r;
 }
 
-// Prepare a call again after its state reported unmet (kUnmet* bits).
-rn_status prepare_again(const rn_graph *g, const rn_query *q, Prepared &p, uint32_t unmet) {
-    const bool guesses = p.guesses && !(unmet & kUnmetGuess);
-    return prepare(g, q, p.nq, p, guesses, p.tail_one && !(unmet & kUnmetTail));
+// Prepare a call again, without guesses where they were not met.
+rn_status prepare_again(const rn_graph *g, const rn_query *q, Prepared &p, bool unguessed) {
+    return prepare(g, q, p.nq, p, p.guesses && !unguessed, p.short_form);
 }
 
-// One eager call on workspace ws (prepared p, from the queries q); retries when
-// the record buffer was too small, and without guesses when one was not met.
+// One eager call on workspace ws (prepared p, from the queries q); runs it again
+// or goes on with it as finish says.
 rn_status run_eager(rn_graph *g, Workspace &ws, Prepared &p, const rn_query *q, rn_pair *out, int64_t cap,
                     int64_t *offsets, int32_t *status, hipStream_t s, bool timed) {
     int32_t route = 0;
-    for (int attempt = 0; attempt < 6; ++attempt) {
-        RN_TRY(ensure_buffers(ws, p));
-        if (p.nq > 1) {   // (one query's descriptors go with the first kernel)
-            fill_host_desc(p, ws.h_desc);
-            RN_HIP(hipMemcpyAsync(ws.d_desc, ws.h_desc, p.desc_bytes, hipMemcpyHostToDevice, s), "uploading queries");
+    Next next = Next::kAgain;
+    for (int attempt = 0; attempt < 7; ++attempt) {
+        if (next == Next::kHandOver) {
+            RN_TRY(enqueue_handed_over(g, ws, p, out, cap, s, timed));
+        } else {
+            RN_TRY(ensure_buffers(ws, p));
+            if (p.nq > 1) {   // (one query's descriptors go with the first kernel)
+                fill_host_desc(p, ws.h_desc);
+                RN_HIP(hipMemcpyAsync(ws.d_desc, ws.h_desc, p.desc_bytes, hipMemcpyHostToDevice, s), "uploading queries");
+            }
+            RN_TRY(enqueue_call(g, ws, p, out, cap, s, timed));
         }
-        RN_TRY(enqueue_call(g, ws, p, out, cap, s, timed));
         RN_TRY(read_back(ws, p, s));
         route |= route_of(ws, p);
-        bool regrow = false;
-        uint32_t unmet = 0;
-        const rn_status st = finish(g, ws, p, out, cap, offsets, status, timed, &regrow, &unmet, s);
+        const rn_status st = finish(g, ws, p, out, cap, offsets, status, timed, &next, s);
         if (timed) g->stats.route = route;
-        if (!regrow) return st;
-        if (st == RN_OK && unmet) RN_TRY(prepare_again(g, q, p, unmet));
+        if (st != RN_OK || next == Next::kDone) return st;
+        if (next == Next::kUnguessed) RN_TRY(prepare_again(g, q, p, true));
+        if (next == Next::kHandOver) p.short_form = p.tail_one = p.stage_one = false;
     }
     return fail(RN_ERR_NOMEM, "record buffer did not settle");
 }
@@ -1746,8 +1805,13 @@ rn_status capture_plan(rn_plan *pl, const Prepared &p) {
 
 // Eager run to size the buffers, then capture.
 rn_status plan_build(rn_plan *pl, Prepared &p, hipStream_t s, int64_t *offsets, int32_t *status) {
+    const bool short_form = p.short_form;
     const rn_status st = run_eager(pl->g, pl->ws, p, pl->q.data(), pl->out, pl->cap, offsets, status, s, false);
     if (st != RN_OK && st != RN_ERR_CAPACITY && st != RN_ERR_ARG) return st;
+    if (short_form && !p.short_form) {   // handed over: from now on in the general form
+        RN_TRY(prepare_again(pl->g, pl->q.data(), p, false));
+        RN_TRY(ensure_buffers(pl->ws, p));
+    }
     RN_TRY(capture_plan(pl, p));
     return st;
 }
@@ -1799,20 +1863,21 @@ rn_status rn_plan_run(rn_plan *pl, int64_t *offsets, int32_t *status, void *stre
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     Prepared &p = pl->prep;
     if (!pl->exec) {   // the last run could not build it again
-        RN_TRY(prepare_again(g, pl->q.data(), p, 0));
+        RN_TRY(prepare_again(g, pl->q.data(), p, false));
         return plan_build(pl, p, s, offsets, status);
     }
     RN_HIP(hipGraphLaunch(pl->exec, s), "launching the graph");
     RN_TRY(read_back(pl->ws, p, s));
-    bool regrow = false;
-    uint32_t unmet = 0;
-    const rn_status st = finish(g, pl->ws, p, pl->out, pl->cap, offsets, status, false, &regrow, &unmet, s);
-    if (!regrow) return st;
-    // the records outgrew the buffer (grown by finish): run eagerly, re-capture.
-    // The graph names buffers that may be freed on the way: it goes first, so
-    // that after a failure the next run builds it instead of replaying it
+    Next next;
+    const rn_status st = finish(g, pl->ws, p, pl->out, pl->cap, offsets, status, false, &next, s);
+    if (next == Next::kDone) return st;
+    // run it eagerly, in the form it needs from now on, and capture that.  The
+    // graph names buffers that may be freed on the way: it goes first, so that
+    // after a failure the next run builds it instead of replaying it
     drop_graph(pl);
-    if (st == RN_OK && unmet) RN_TRY(prepare_again(g, pl->q.data(), p, unmet));   // (from now on)
+    if (st != RN_OK) return st;
+    if (next == Next::kHandOver) p.short_form = false;
+    if (next != Next::kAgain) RN_TRY(prepare_again(g, pl->q.data(), p, next == Next::kUnguessed));
     return plan_build(pl, p, s, offsets, status);
 }
 

@@ -155,8 +155,9 @@ struct Prepared {
     bool need_list1 = false;
     bool all_quads = true;          // every query's first searches are over arc quads
     bool guesses = true;            // k-closest-pairs queries may start from a guessed bound
+    bool short_form = false;        // small one-query calls may take the short form
     bool stage_one = false;         // one-block staging (launch_stage_one)
-    bool tail_one = false;          // one-block tail (launch_tail_one), no re-run tiers
+    bool tail_one = false;          // one-block tail (launch_tail_one), no re-run tiers: the short form
     bool any_global = false;        // a first-tier group runs in the global tier
     uint32_t qb = 0, vb = 1, max_passes = 1;
     uint64_t total_R = 0;
@@ -181,8 +182,9 @@ rn_status check_queries(const rn_graph *g, const rn_query *q, int32_t nq, int32_
 // guesses: k-closest-pairs searches may start from a guessed bound; a call whose
 // state then reports an unmet guess (ctl.unmet) is prepared again without them
 // and run again.  short_form: small one-query calls may take the one-block
-// staging and tail, without the re-run tiers; a call that needs those after all
-// (ctl.unmet, or searches queued on a re-run list) is prepared again without it.
+// staging and tail, without the re-run tiers; a call that needs those after all,
+// or has more records than that tail sorts, is gone on with in the general form
+// (enqueue_handed_over, after clearing short_form, tail_one and stage_one).
 rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p, bool guesses = true,
                   bool short_form = false);
 // Global-tier slots are allocated on demand: a call enqueued while a
@@ -204,6 +206,10 @@ void fill_host_desc(const Prepared &p, uint8_t *h);
 // source so that other streams' kernels interleave).
 rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, hipStream_t s,
                        bool timed, bool shared = false);
+// Go on, in the general form, with a call whose short form met what it does not
+// do: its records and re-run lists are on the device.
+rn_status enqueue_handed_over(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, hipStream_t s,
+                              bool timed);
 // After a call whose sort left the output to the radix sort (its state's
 // resort: a bucket-sort bin too large to rank, or too many candidates for the
 // small sort): enqueue on s the radix sort of the records in recs[1], which

@@ -26,6 +26,7 @@
 // needed and the result is exact.
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <type_traits>
 
 #include "rn_internal.h"
@@ -3781,9 +3782,13 @@ __global__ __launch_bounds__(1024) void k_tail_one(CallBuffers b, uint32_t vb, r
     }
     __syncthreads();
     const uint32_t kept = s_n;
+    // (a search that outgrew its table, or more records than fit here: the host
+    // goes on with the call in the general form, which counts them itself)
+    const bool whole = (ctl->nlist[0] | ctl->nlist[1] | ctl->nlist[2]) == 0u;
     const bool small = fits && n64 <= 4u * kSmallSort && kept <= kSmallSort;
-    const uint32_t nout = st.err || !small ? 0u : (d.k ? min(kept, d.k) : kept);
-    if (small && nout != 0 && nout <= user_cap) {
+    const bool mine = whole && small;
+    const uint32_t nout = st.err || !mine ? 0u : (d.k ? min(kept, d.k) : kept);
+    if (nout != 0 && nout <= user_cap) {
         const unsigned long long vm = (1ull << vb) - 1ull, dm = (1ull << db) - 1ull;
         auto put = [&](unsigned long long key, uint32_t i) {
             if (i >= nout) return;
@@ -3803,16 +3808,19 @@ __global__ __launch_bounds__(1024) void k_tail_one(CallBuffers b, uint32_t vb, r
         }
     }
     if (tid == 0) {
-        if (fits && !small) ctl->unmet = kUnmetTail;
-        else if (small && d.k && st.guessed && !st.err && kept < d.k) ctl->unmet = kUnmetGuess;
-        ctl->nsel = kept;
+        if (mine && d.k && st.guessed && !st.err && kept < d.k) ctl->unmet = kUnmetGuess;
+        ctl->nsel = mine ? kept : 0u;
         ctl->nout = nout;
         st.npairs = n64;
-        st.nsel = kept;
+        st.nsel = mine ? kept : 0u;
         st.nout = nout;
     }
     __syncthreads();   // the state's last writes are seen by the whole block
-    for (uint32_t i = tid; i < state_words; i += 1024) state_map[i] = state[i];
+    for (uint32_t i = tid; i < state_words; i += 1024) {
+        // (kUnmetTail is for the host alone: the call goes on with this state)
+        const bool more = i == offsetof(CallCtl, unmet) / 4u && fits && !small;
+        state_map[i] = more ? kUnmetTail : state[i];
+    }
 }
 
 // Blocks of `lds` bytes of LDS that one CU holds at once.  A CU's LDS is

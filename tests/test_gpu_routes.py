@@ -60,30 +60,61 @@ def test_short_form_and_guess(rnmod, orc, rg):
         assert not net.stats()["route"] & rnmod.RN_ROUTE_SHORT
 
 
-def dense_patch(rg):
-    """A path of long arcs, its first vertices joined by many short ones: balls
-    and pair counts far above the estimate from the mean weight."""
-    rng = np.random.default_rng(3)
-    n, m = 8000, 2500
-    path = np.arange(n - 1)
-    cycles = [rng.permutation(m) for _ in range(3)]
-    src = np.concatenate([path] + cycles)
-    dst = np.concatenate([path + 1] + [np.roll(c, 1) for c in cycles])
-    w = np.concatenate([rng.integers(400, 500, n - 1), rng.integers(1, 30, 3 * m)])
-    return rg.from_edges(n, src, dst, w, symmetric=True), rng.permutation(m).astype(np.int32)
+def dense_patch(rg, n, seed=3):
+    """A road graph, n vertices of it joined by short arcs: balls and pair counts
+    far above the estimate from the mean weight.  (From id 700 on: between two of
+    the 32 places where loading looks how dense the graph is, when n <= 1000.)"""
+    rng = np.random.default_rng(seed)
+    r = rg.road_graph(200, 5)
+    cycles = [700 + rng.permutation(n) for _ in range(3)]
+    src = np.concatenate([np.repeat(np.arange(r.V), np.diff(r.row_ptr))] + cycles + [np.roll(c, 1) for c in cycles])
+    dst = np.concatenate([r.col] + [np.roll(c, 1) for c in cycles] + cycles)
+    w = rng.integers(1, 6, 3 * n)
+    g = rg.from_edges(r.V, src, dst, np.concatenate([r.w, w, w]), symmetric=False)
+    return g, 700 + rng.permutation(n).astype(np.int32)
 
 
 def test_short_form_hands_over(rnmod, orc, rg):
-    g, ids = dense_patch(rg)
+    g, ids = dense_patch(rg, 1000)
     net = rnmod.RoadNetwork.from_graph(g)
-    left = rnmod.RN_ROUTE_SHORT | rnmod.RN_ROUTE_SHORT_LEFT
+    left = rnmod.RN_ROUTE_QUADS | rnmod.RN_ROUTE_SHORT | rnmod.RN_ROUTE_SHORT_LEFT
     # balls that outgrow the table; more records than the tail sorts; both
-    for nR, nS, theta in ((30, 40, 300), (900, 900, 16), (120, 900, 60)):
+    for nR, nS, theta in ((30, 40, 60), (450, 450, 5), (120, 850, 60)):
         R, S = ids[:nR], ids[nR:nR + nS]
-        same(rnmod.pairs_to_numpy(net.dist_join(R, S, theta)), orc.dist_join(g, R, S, theta).pairs)
-        st = net.stats()
-        assert st["route"] & left == left, (nR, nS, theta)
-        assert (st["pairs"] > 4096) == (nR > 30) and (st["retried"] > 0) == (theta > 16), st
+        want = orc.dist_join(g, R, S, theta).pairs
+        for _ in range(2):
+            same(rnmod.pairs_to_numpy(net.dist_join(R, S, theta)), want)
+            st = net.stats()
+            assert st["route"] & ~rnmod.RN_ROUTE_RESORTED == left, (nR, nS, theta)
+            assert (st["pairs"] > 4096) == (nR > 30) and (st["retried"] > 0) == (theta > 5), st
+        # (from the first run of a plan on, it is captured in the general form)
+        q, keep = net.make_queries([{"R": R, "S": S, "theta": theta}])
+        plan = net.plan(q, cap=len(want))
+        for _ in range(3):
+            same(rnmod.pairs_to_numpy(plan.run()[0]), want)
+        plan.close()
+    # k closest pairs whose balls outgrow the table
+    R, S = ids[:300], ids[300:700]
+    same(rnmod.pairs_to_numpy(net.kcp_join(R, S, 900)), orc.kcp_join(g, R, S, 900))
+    assert net.stats()["route"] & left == left
+
+
+def test_plan_hands_over_in_a_replay(rnmod, orc, rg):
+    # sets that lie in the sparse part when the plan is made, then in the dense one
+    import torch
+    g, ids = dense_patch(rg, 1000)
+    net = rnmod.RoadNetwork.from_graph(g)
+    far = 20000 + np.arange(500, dtype=np.int32)
+    Rd, Sd = torch.from_numpy(far[:100].copy()).cuda(), torch.from_numpy(far[100:].copy()).cuda()
+    q, keep = net.make_queries([{"R": Rd, "S": Sd, "theta": 60}])
+    plan = net.plan(q, cap=100000)
+    for R, S in ((far[:100], far[100:]), (ids[:100], ids[100:500]), (far[:100], far[100:])):
+        Rd.copy_(torch.from_numpy(R.copy()))
+        Sd.copy_(torch.from_numpy(S.copy()))
+        torch.cuda.synchronize()
+        for _ in range(2):
+            same(rnmod.pairs_to_numpy(plan.run()[0]), orc.dist_join(g, R, S, 60).pairs)
+    plan.close()
 
 
 def flat_grid(rg):
