@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <limits>
 #include <memory>
 #include <new>
 #include <string>
@@ -120,13 +121,16 @@ uint32_t guess_bound(const rn_graph *g, const rn_query &x, double *ball) {
     return static_cast<uint32_t>(d) + 1u;
 }
 
-// Mean distances within which 2^3 .. 2^8 vertices lie, over a few vertices of
-// graph i spread over its numbering (0: not reached).
+// Over vertices of graph i spread over its numbering: the mean distances within
+// which 2^3 .. 2^8 vertices lie, of a few (0: not reached), and the least distance
+// within which kDenseBall lie, of more.
 // dist: per vertex 1 + tentative distance, all 0 before and after.
 void measure_radii(rn_graph *g, int32_t i, uint64_t *dist) {
-    constexpr int kSamples = 4;
+    constexpr int kFull = 4, kSamples = 32;
     const int32_t vo = g->voff[i], V = g->voff[i + 1] - vo;
     double *r = g->radius.data() + static_cast<size_t>(i) * kBalls;
+    double &least = g->least_radius[i];
+    least = std::numeric_limits<double>::infinity();
     int reached[kBalls] = {};
     std::vector<std::pair<uint64_t, int32_t>> heap;
     std::vector<int32_t> touched;
@@ -136,18 +140,22 @@ void measure_radii(rn_graph *g, int32_t i, uint64_t *dist) {
         touched.assign(1, s);
         dist[s] = 1;
         int32_t settled = 0;
+        const bool full = smp % (kSamples / kFull) == kSamples / kFull / 2;
+        const int32_t most = full ? 1 << (kBallMinLog2 + kBalls - 1) : kDenseBall;
         const auto later = [](const std::pair<uint64_t, int32_t> &a, const std::pair<uint64_t, int32_t> &b) { return a > b; };
-        while (!heap.empty() && settled < (1 << (kBallMinLog2 + kBalls - 1))) {
+        while (!heap.empty() && settled < most) {
             std::pop_heap(heap.begin(), heap.end(), later);
             const auto [d, x] = heap.back();
             heap.pop_back();
             if (d + 1 != dist[x]) continue;
             ++settled;
-            for (int b = 0; b < kBalls; ++b)
-                if (settled == (1 << (kBallMinLog2 + b))) {
-                    r[b] += static_cast<double>(d);
-                    ++reached[b];
-                }
+            if (settled == kDenseBall) least = std::min(least, static_cast<double>(d));
+            if (full && (settled & (settled - 1)) == 0 && settled >= (1 << kBallMinLog2)) {
+                const int b = 31 - __builtin_clz(static_cast<uint32_t>(settled)) - kBallMinLog2;
+                r[b] += static_cast<double>(d);
+                ++reached[b];
+            }
+            if (settled == most) break;
             for (int32_t a = g->row_ptr[x]; a < g->row_ptr[x + 1]; ++a) {
                 const int32_t y = g->col[a];
                 const uint64_t nd = d + g->w[a];
@@ -160,17 +168,31 @@ void measure_radii(rn_graph *g, int32_t i, uint64_t *dist) {
         }
         for (int32_t x : touched) dist[x] = 0;
     }
-    for (int b = 0; b < kBalls; ++b) r[b] = reached[b] == kSamples ? r[b] / kSamples : 0.0;
+    for (int b = 0; b < kBalls; ++b) r[b] = reached[b] == kFull ? r[b] / kFull : 0.0;
+}
+
+// Vertices that a table below 2^11 slots has to have room for: the expected ball
+// (about 2 (theta / mean arc weight)^2 vertices on a planar road graph) with a
+// margin of 1.8, and the ball in the densest part met when the graph was loaded,
+// with 1.2 (on the synthetic road graphs that is the less of the two).  A query's
+// sets often lie in one part of a graph, a city say: if all its searches outgrow
+// their table the call takes up to three times as long (1 000 searches of 190 to
+// 700 vertices where arcs are a quarter as long as on average: 110 us with 2^11
+// slots from the start, 317 with 2^8 and a re-run).
+double room_needed(const rn_graph *g, const rn_query &x) {
+    const double r = static_cast<double>(x.theta) / std::max(1.0, g->wmean[x.graph]);
+    const double V = static_cast<double>(g->voff[x.graph + 1] - g->voff[x.graph]);
+    const double t = static_cast<double>(x.theta) / std::max(g->least_radius[x.graph], 1e-3);
+    return std::max(1.8 * 2.0 * r * r, 1.2 * std::min(V, kDenseBall * t * t));
 }
 
 // First on-chip table of a query when the caller set none: for a theta-join the
-// smallest whose fill limit (3/4) holds the expected ball (about
-// 2 (theta / mean arc weight)^2 vertices on a planar road graph) with a margin of
-// 1.3; balls of less than 2^11 slots vary more and take 1.8.  (Over quads only:
-// the window search keeps 2^11 as its smallest.  32 768 searches of 66 vertices:
-// 153 us with 2^8 slots, 384 with 2^11.)  A larger ball overflows the table and
-// is searched again.  A k-closest-pairs query whose searches start from a guess
-// takes the ball expected within it.
+// smallest whose fill limit (3/4) holds the expected ball with a margin of 1.3;
+// below 2^11 slots as room_needed says.  (Over quads only: the window search
+// keeps 2^11 as its smallest.  32 768 searches of 66 vertices: 153 us with 2^8
+// slots, 384 with 2^11.)  A larger ball overflows the table and is searched again.
+// A k-closest-pairs query whose searches start from a guess takes the ball
+// expected within it.
 int first_table(const rn_graph *g, const rn_query &x, bool guesses) {
     if (x.k == 0 && !g->hash_auto) return g->hash_log2;
     const bool quads = g->quads && (x.delta == RN_DELTA_DEFAULT ? g->delta : x.delta) == 0;
@@ -184,7 +206,7 @@ int first_table(const rn_graph *g, const rn_query &x, bool guesses) {
         return hb;
     }
     if (quads)
-        while (hb < 11 && !fits(hb, 1.8 * 2.0 * r * r)) ++hb;
+        while (hb < 11 && !fits(hb, room_needed(g, x))) ++hb;
     else
         hb = 11;
     while (hb < kMaxHB && hb >= 11 && !fits(hb, 1.3 * 2.0 * r * r)) ++hb;
@@ -344,13 +366,17 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
                      (quads || g->A * (g->rev_rpo ? 2 : 1) < static_cast<int64_t>(kCompactArcs)) &&
                      ((x.k > 0 && hb[i] >= kCompactMinHB) ||
                       (x.k > 0 ? std::min(x.theta, d.guess) : x.theta) <= compact_max_dist(hb[i]));
+        // (the same for what the re-run at 2^11 takes)
+        if (hb[i] < kRetryHB1)
+            p.compact_list0 = p.compact_list0 && quads && g->Vmax < kCompactVertices &&
+                              (x.k > 0 || x.theta <= compact_max_dist(kRetryHB1));
     }
     p.rbase[nq] = static_cast<uint32_t>(rw);
     p.total_elems = p.ebase[nq];
     p.sbits_words = static_cast<uint32_t>(sw);
     p.rbits_words = static_cast<uint32_t>(rw);
     for (const Group &gr : p.groups) {
-        p.need_list0 |= gr.hb < kRetryHB1 && !gr.sized;
+        p.need_list0 |= gr.hb < kRetryHB1;
         p.need_list1 |= gr.hb < kMaxHB;
         p.any_global |= gr.hb == kGlobalHB;
     }
@@ -366,7 +392,7 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
         const double expect = x.k > 0 ? 1.5 * x.k : pairs * std::min(1.0, 2.5 * r * r / V);
         const uint32_t dbits = bitlen(x.k > 0 ? std::min(x.theta, p.qd[0].guess) : x.theta);
         const uint32_t vbits = std::max<uint32_t>(1u, bitlen(static_cast<uint64_t>(std::max(g->Vmax - 1, 0))));
-        const bool roomy = x.k > 0 || 0.75 * static_cast<double>(1u << p.groups[0].hb) >= 1.8 * 2.0 * r * r;
+        const bool roomy = x.k > 0 || 0.75 * static_cast<double>(1u << p.groups[0].hb) >= room_needed(g, x);
         p.tail_one = roomy && (pairs <= kSmallSort || expect <= kSmallSort / 2) && dbits + 2 * vbits <= 63u;
         p.stage_one = p.tail_one && g->voff[x.graph + 1] - g->voff[x.graph] <= kStage1Vertices &&
                       p.total_elems <= kStage1Elems;
@@ -727,7 +753,7 @@ static rn_status enqueue_searches(rn_graph *g, Workspace &ws, const Prepared &p,
             // (without global-tier slots yet, a global group takes the largest
             // table, whose overflows get the slots and a re-run of the call)
             const int hbt = std::min(gr.hb, kMaxHB);
-            const int li = gr.sized && hbt < kMaxHB ? 1 : retry_list_after(hbt);
+            const int li = retry_list_after(hbt);
             t.ovf = b.list[li];
             t.ovfq = b.listq[li];
             t.novf = &b.ctl->nlist[li];
@@ -776,10 +802,13 @@ static rn_status enqueue_rest(rn_graph *g, Workspace &ws, const Prepared &p, rn_
         t.novf = &b.ctl->nlist[li + 1];
         t.first_tier = 0;
         t.tier = 1 + li;
-        // the re-run tiers take wide tables: they must hold any search the
-        // first tiers sent on, whatever its distances (a compact 2^14 re-run
-        // could only send those on to the global tier)
-        RN_HIP(launch_join(t, li == 0 ? kRetryHB1 : kMaxHB, true, false, p.all_quads, maxs, !shared, s),
+        // the 2^14 re-run takes wide tables: it must hold any search the
+        // tiers before sent on, whatever its distances (a compact one could
+        // only send those on to the global tier); that at 2^11 compact ones
+        // where the distances fit, for where a call's searches all lie in a
+        // part of the graph so dense that each comes here
+        RN_HIP(launch_join(t, li == 0 ? kRetryHB1 : kMaxHB, true, li == 0 && p.all_quads && p.compact_list0, p.all_quads,
+                           maxs, !shared, s),
                "launching the relaxation");
     }
     if (gside) RN_HIP(hipStreamWaitEvent(s, ws.join[0], 0), "joining streams");   // the early global launch
@@ -1273,6 +1302,7 @@ rn_status rn_graph_load_many(int32_t n, const int32_t *V, const int64_t *A, cons
         g->wmean.assign(n, 1.0);
         g->varied.assign(n, 0);
         g->radius.assign(static_cast<size_t>(n) * kBalls, 0.0);
+        g->least_radius.assign(n, 0.0);
         dist.reset(static_cast<uint64_t *>(std::calloc(static_cast<size_t>(totV), sizeof(uint64_t))));
         if (!dist) throw std::bad_alloc();
         g->row_ptr.resize(static_cast<size_t>(totV) + 1);

@@ -62,6 +62,8 @@ constexpr unsigned long long kRecCapMax = 1ull << 31;
 // Ball sizes whose radii are measured when a graph is loaded (2^3 .. 2^8 vertices).
 constexpr int kBallMinLog2 = 3;
 constexpr int kBalls = 6;
+// ... and the one whose least radius tells how dense its densest part is.
+constexpr int kDenseBall = 32;
 
 inline size_t round_up(size_t x, size_t m) { return (x + m - 1) / m * m; }
 
@@ -135,8 +137,7 @@ struct Group {
     bool kcp;               // some query of the group asks for k closest pairs
     bool compact;           // its launch uses compact on-chip tables
     bool quads;             // its launch searches over arc quads
-    bool sized;             // queries whose table was chosen for their balls: the few searches
-                            // that outgrow it go on to the largest table at once
+    bool sized;             // queries whose table was chosen for their balls
     int32_t first;          // staging positions [first, end)
     int32_t end;
     uint64_t sources;       // sum of nR
@@ -154,6 +155,7 @@ struct Prepared {
     bool need_list0 = false;
     bool need_list1 = false;
     bool all_quads = true;          // every query's first searches are over arc quads
+    bool compact_list0 = true;      // the re-run at 2^11 may take compact tables (over quads)
     bool guesses = true;            // k-closest-pairs queries may start from a guessed bound
     bool short_form = false;        // small one-query calls may take the short form
     bool stage_one = false;         // one-block staging (launch_stage_one)
@@ -258,6 +260,7 @@ struct rn_graph {
     bool hash_auto = true;          // no first table size set: theta-joins size it from theta
     std::vector<double> wmean;      // per graph: mean arc weight
     std::vector<double> radius;     // per graph: mean distance within which kBalls vertices lie
+    std::vector<double> least_radius;   // per graph: least distance within which kDenseBall vertices lie
     std::vector<char> varied;       // per graph: at least 16 distinct arc weights
 
     rn::host::Workspace ws;

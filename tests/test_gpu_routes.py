@@ -117,6 +117,22 @@ def test_plan_hands_over_in_a_replay(rnmod, orc, rg):
     plan.close()
 
 
+def test_tables_hold_the_densest_part(rnmod, orc, rg):
+    # a fifth of a road graph with arcs a quarter as long, and queries in it: the
+    # tables are large enough, in the short form and beyond it
+    r = rg.road_graph(300, 0)
+    src = np.repeat(np.arange(r.V), np.diff(r.row_ptr))
+    lo, hi = int(.4 * r.V), int(.6 * r.V)
+    w = np.where((src >= lo) & (src < hi) & (r.col >= lo) & (r.col < hi), np.maximum(1, r.w // 4), r.w)
+    g = rg.from_edges(r.V, src, r.col, w, symmetric=False)
+    net = rnmod.RoadNetwork.from_graph(g)
+    ids = lo + np.random.default_rng(4).permutation(hi - lo).astype(np.int32)
+    for nR, theta in ((30, 500), (1000, 250), (5000, 500), (6000, 250)):
+        R, S = ids[:nR], ids[nR:2 * nR]
+        same(rnmod.pairs_to_numpy(net.dist_join(R, S, theta)), orc.dist_join(g, R, S, theta).pairs)
+        assert net.stats()["retried"] == 0, (nR, theta)
+
+
 def flat_grid(rg):
     """Weights of 100 but for a few: most distances are multiples of 100."""
     g = rg.road_graph(120, 5)
