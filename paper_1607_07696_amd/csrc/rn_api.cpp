@@ -132,6 +132,9 @@ void measure_radii(rn_graph *g, int32_t i, uint64_t *dist) {
     double &least = g->least_radius[i];
     least = std::numeric_limits<double>::infinity();
     int reached[kBalls] = {};
+    // (a guess needs balls up to V / 64, and interpolates to twice that)
+    int32_t largest = kDenseBall;
+    while (largest < (1 << (kBallMinLog2 + kBalls - 1)) && 32 * static_cast<int64_t>(largest) < V) largest *= 2;
     std::vector<std::pair<uint64_t, int32_t>> heap;
     std::vector<int32_t> touched;
     for (int smp = 0; smp < kSamples; ++smp) {
@@ -141,7 +144,7 @@ void measure_radii(rn_graph *g, int32_t i, uint64_t *dist) {
         dist[s] = 1;
         int32_t settled = 0;
         const bool full = smp % (kSamples / kFull) == kSamples / kFull / 2;
-        const int32_t most = full ? 1 << (kBallMinLog2 + kBalls - 1) : kDenseBall;
+        const int32_t most = full ? largest : kDenseBall;
         const auto later = [](const std::pair<uint64_t, int32_t> &a, const std::pair<uint64_t, int32_t> &b) { return a > b; };
         while (!heap.empty() && settled < most) {
             std::pop_heap(heap.begin(), heap.end(), later);
@@ -1094,11 +1097,6 @@ const char *rn_version(void) { return "rn 0.2 (gfx950)"; }
 
 namespace {
 
-// Graph index of global vertex x.
-int32_t graph_of(const rn_graph *g, int32_t x) {
-    return static_cast<int32_t>(std::upper_bound(g->voff.begin(), g->voff.end(), x) - g->voff.begin()) - 1;
-}
-
 // Whether the graphs keep arc quads (rrow: row pointers of the reversed arcs),
 // and where each graph's start: the vertices' first quads, then the further
 // quads of its vertices of more than 4 arcs (a renumbering of the vertices
@@ -1141,18 +1139,14 @@ rn_status upload_quads(rn_graph *g) {
     hipError_t e = hipSuccess;
     const size_t ngr = static_cast<size_t>(g->ngraphs), nv = g->voff.size(), nb = dirs * ngr;
     if ((!g->d_quads && (e = dev_alloc(&g->d_quads, 4 * static_cast<size_t>(nquads))) != hipSuccess) ||
-        (!g->d_further && (e = dev_alloc(&g->d_further, static_cast<size_t>(nquads))) != hipSuccess) ||
-        (!g->d_qgraph && (e = dev_alloc(&g->d_qgraph, nv + 2 * nb)) != hipSuccess)) {
+        (!g->d_further && (e = dev_alloc(&g->d_further, static_cast<size_t>(nquads))) != hipSuccess)) {
         (void)hipGetLastError();   // (not for the next launch to report)
         dev_free(g->d_quads);
         dev_free(g->d_further);
-        dev_free(g->d_qgraph);
         g->quads = g->dense = false;
         return RN_OK;
     }
-    if ((e = hipMemcpy(g->d_qgraph, g->voff.data(), nv * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(g->d_qgraph + nv, g->qbase.data(), nb * sizeof(uint32_t), hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = launch_build_quads(g->d_row_ptr, g->d_arcs, g->d_further, g->d_qgraph,
+    if ((e = launch_build_quads(g->d_row_ptr, g->d_arcs, g->d_further, g->d_qgraph,
                                 reinterpret_cast<const uint32_t *>(g->d_qgraph + nv),
                                 reinterpret_cast<uint32_t *>(g->d_qgraph + nv + nb), static_cast<uint32_t>(ngr),
                                 static_cast<uint32_t>(dirs), static_cast<uint32_t>(g->V), nquads, g->d_quads, nullptr)) !=
@@ -1176,37 +1170,45 @@ rn_status upload_csr(rn_graph *g, const int32_t *perm) {
     std::vector<uint32_t> ww, rww;
     std::vector<ArcRec> arcs;
     try {
-        rp.assign(static_cast<size_t>(V) + 1, 0);
-        cl.resize(static_cast<size_t>(A));
-        ww.resize(static_cast<size_t>(A));
-        std::vector<int32_t> inv(static_cast<size_t>(V));
-        for (int32_t x = 0; x < V; ++x) inv[perm ? perm[x] : x] = x;
-        for (int32_t i = 0; i < V; ++i) rp[i + 1] = rp[i] + (g->row_ptr[inv[i] + 1] - g->row_ptr[inv[i]]);
-        for (int32_t i = 0; i < V; ++i) {
-            int32_t o = rp[i];
-            for (int32_t a = g->row_ptr[inv[i]]; a < g->row_ptr[inv[i] + 1]; ++a, ++o) {
-                cl[o] = perm ? perm[g->col[a]] : g->col[a];
-                ww[o] = g->w[a];
+        const int32_t *pcl = g->col.data();
+        const uint32_t *pww = g->w.data();
+        if (perm) {
+            rp.assign(static_cast<size_t>(V) + 1, 0);
+            cl.resize(static_cast<size_t>(A));
+            ww.resize(static_cast<size_t>(A));
+            std::vector<int32_t> inv(static_cast<size_t>(V));
+            for (int32_t x = 0; x < V; ++x) inv[perm[x]] = x;
+            for (int32_t i = 0; i < V; ++i) rp[i + 1] = rp[i] + (g->row_ptr[inv[i] + 1] - g->row_ptr[inv[i]]);
+            for (int32_t i = 0; i < V; ++i) {
+                int32_t o = rp[i];
+                for (int32_t a = g->row_ptr[inv[i]]; a < g->row_ptr[inv[i] + 1]; ++a, ++o) {
+                    cl[o] = perm[g->col[a]];
+                    ww[o] = g->w[a];
+                }
             }
+            pcl = cl.data();
+            pww = ww.data();
+        } else {
+            rp = g->row_ptr;
         }
         if (rev) {
             rrp.assign(static_cast<size_t>(V) + 1, 0);
             rcl.resize(static_cast<size_t>(A));
             rww.resize(static_cast<size_t>(A));
-            for (int64_t a = 0; a < A; ++a) rrp[cl[a] + 1] += 1;
+            for (int64_t a = 0; a < A; ++a) rrp[pcl[a] + 1] += 1;
             for (int32_t x = 0; x < V; ++x) rrp[x + 1] += rrp[x];
             std::vector<int32_t> fill(rrp.begin(), rrp.end() - 1);
             for (int32_t x = 0; x < V; ++x)
                 for (int32_t a = rp[x]; a < rp[x + 1]; ++a) {
-                    const int32_t b = fill[cl[a]]++;
+                    const int32_t b = fill[pcl[a]]++;
                     rcl[b] = x;
-                    rww[b] = ww[a];
+                    rww[b] = pww[a];
                 }
         }
         arcs.resize(static_cast<size_t>(A) * (rev ? 2 : 1));
         for (int64_t a = 0; a < A; ++a) {
-            const int32_t y = cl[a];
-            arcs[a] = ArcRec{y, ww[a], rp[y], rp[y + 1]};
+            const int32_t y = pcl[a];
+            arcs[a] = ArcRec{y, pww[a], rp[y], rp[y + 1]};
         }
         if (rev) {
             for (int64_t b = 0; b < A; ++b) {
@@ -1230,6 +1232,19 @@ rn_status upload_csr(rn_graph *g, const int32_t *perm) {
             if (e <= b) continue;
             if (e - b == 1) {
                 first[static_cast<size_t>(b) >> 5] |= 1u << (b & 31);
+                continue;
+            }
+            if (e - b <= 16) {
+                // (compared pair by pair: sorting a million short rows took a third of the load)
+                for (int64_t a = b; a < e; ++a) {
+                    const ArcRec &ra = arcs[static_cast<size_t>(a)];
+                    bool lightest = true;
+                    for (int64_t c = b; c < e; ++c) {
+                        const ArcRec &rc = arcs[static_cast<size_t>(c)];
+                        lightest = lightest && !(rc.y == ra.y && (rc.w < ra.w || (rc.w == ra.w && c < a)));
+                    }
+                    first[static_cast<size_t>(a) >> 5] |= (lightest ? 1u : 0u) << (a & 31);
+                }
                 continue;
             }
             idx.resize(static_cast<size_t>(e - b));
@@ -1389,16 +1404,24 @@ rn_status rn_graph_load_many(int32_t n, const int32_t *V, const int64_t *A, cons
     // identity maps between the two numberings
     rn_status st = upload_csr(g, nullptr);
     if (st == RN_OK) {
-        std::vector<int32_t> ident(static_cast<size_t>(totV));
-        for (int32_t i = 0; i < totV; ++i) ident[i] = i - g->voff[graph_of(g, i)];
-        std::vector<int32_t> rank_ident(ident);
-        if ((e = dev_alloc(&g->d_rank, static_cast<size_t>(totV))) != hipSuccess ||
-            (e = dev_alloc(&g->d_order, static_cast<size_t>(totV))) != hipSuccess ||
-            (totV > 0 && ((e = hipMemcpy(g->d_rank, rank_ident.data(), ident.size() * sizeof(int32_t),
-                                         hipMemcpyHostToDevice)) != hipSuccess ||
-                          (e = hipMemcpy(g->d_order, ident.data(), ident.size() * sizeof(int32_t),
-                                         hipMemcpyHostToDevice)) != hipSuccess)))
+        // one array and one copy: rank | order | voff | qbase | counters of the quads' build
+        const size_t nv = static_cast<size_t>(totV), nb = g->qbase.size() - 1;
+        std::vector<int32_t> maps;
+        try {
+            maps.assign(2 * nv + g->voff.size() + 2 * nb, 0);
+        } catch (...) {
+            rn_graph_free(g);
+            return fail(RN_ERR_NOMEM, "uploading the vertex maps");
+        }
+        for (int32_t i = 0; i < n; ++i)
+            for (int32_t x = g->voff[i]; x < g->voff[i + 1]; ++x) maps[x] = maps[nv + x] = x - g->voff[i];
+        std::copy(g->voff.begin(), g->voff.end(), maps.begin() + 2 * nv);
+        std::copy(g->qbase.begin(), g->qbase.end() - 1, maps.begin() + 2 * nv + g->voff.size());
+        if ((e = dev_alloc(&g->d_rank, maps.size())) != hipSuccess ||
+            (e = hipMemcpy(g->d_rank, maps.data(), maps.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess)
             st = hip_fail(e, "uploading the vertex maps");
+        g->d_order = g->d_rank + nv;
+        g->d_qgraph = g->d_order + nv;
     }
     if (st == RN_OK) st = upload_quads(g);
     if (st != RN_OK) {
@@ -1550,9 +1573,7 @@ void rn_graph_free(rn_graph *g) {
     dev_free(g->d_arcs);
     dev_free(g->d_quads);
     dev_free(g->d_further);
-    dev_free(g->d_qgraph);
-    dev_free(g->d_rank);
-    dev_free(g->d_order);
+    dev_free(g->d_rank);   // (d_order and d_qgraph lie in it)
     dev_free(g->d_first);
     delete g;
 }

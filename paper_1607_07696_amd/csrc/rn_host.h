@@ -246,12 +246,12 @@ struct rn_graph {
     std::vector<uint32_t> qbase;    // first quad of each graph, then of each reversed graph, then their number
     uint2 *d_quads = nullptr;
     uint32_t *d_further = nullptr;  // per quad: the next quad of its vertex (of more than 4 arcs)
-    int32_t *d_qgraph = nullptr;    // voff, then qbase, then counters of the build
+    int32_t *d_qgraph = nullptr;    // voff, then qbase, then counters of the build (in d_rank's allocation)
     // The device copy of the graphs is numbered in partition-leaf order once
     // rn_partition has run (identity until then); the two maps, both
     // allocated at load:
     int32_t *d_rank = nullptr;      // global vertex (caller numbering) -> local id in the device copy
-    int32_t *d_order = nullptr;     // global vertex of the device copy -> local id in the caller numbering
+    int32_t *d_order = nullptr;     // global vertex of the device copy -> local id in the caller numbering (likewise)
     uint32_t *d_first = nullptr;    // per arc record: first lightest arc of its (tail, target) pair
     std::vector<char> renumbered;   // per graph: the device copy is in leaf order (else as loaded)
 
