@@ -364,7 +364,7 @@ typedef struct rn_server_stats {
     int64_t submitted;      /* requests accepted */
     int64_t completed;      /* requests answered (including argument errors) */
     int64_t batches;        /* batches launched */
-    int64_t reruns;         /* batches re-run with larger buffers */
+    int64_t reruns;         /* batches re-run with larger buffers, requests re-run without a guessed bound */
     int64_t peak_budget;    /* largest estimated footprint in flight, bytes */
     int64_t device_bytes;   /* largest device memory held by the lanes (all their buffers), bytes */
     int32_t max_in_flight;  /* most requests in flight at once */

@@ -196,7 +196,7 @@ double room_needed(const rn_graph *g, const rn_query &x) {
 // slots, 384 with 2^11.)  A larger ball overflows the table and is searched again.
 // A k-closest-pairs query whose searches start from a guess takes the ball
 // expected within it.
-int first_table(const rn_graph *g, const rn_query &x, bool guesses) {
+int first_table(const rn_graph *g, const rn_query &x, bool guess) {
     if (x.k == 0 && !g->hash_auto) return g->hash_log2;
     const bool quads = g->quads && (x.delta == RN_DELTA_DEFAULT ? g->delta : x.delta) == 0;
     const double r = static_cast<double>(x.theta) / std::max(1.0, g->wmean[x.graph]);
@@ -204,7 +204,7 @@ int first_table(const rn_graph *g, const rn_query &x, bool guesses) {
     int hb = kMinHB;
     if (x.k > 0) {
         double ball = 0;
-        if (!quads || !guesses || guess_bound(g, x, &ball) == kInf) return hb;
+        if (!quads || !guess || guess_bound(g, x, &ball) == kInf) return hb;
         while (hb < kMaxHB && !fits(hb, 1.8 * ball)) ++hb;
         return hb;
     }
@@ -244,7 +244,7 @@ uint32_t ring_slack(double wmean) {
     return s >= 2147483647.0 ? 0x7FFFFFFFu : static_cast<uint32_t>(s + 0.5);
 }
 
-rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p, bool guesses, bool short_form) {
+rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p, bool short_form) {
     // reset in place: the vectors keep their capacity, so a Prepared reused for
     // calls of the same shape allocates nothing after its first call
     auto qd = std::move(p.qd);
@@ -253,6 +253,7 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
     auto perm = std::move(p.perm);
     auto groups = std::move(p.groups);
     auto binbase = std::move(p.binbase);
+    auto noguess = std::move(p.noguess);
     p = Prepared{};
     p.qd = std::move(qd);
     p.ebase = std::move(ebase);
@@ -260,20 +261,21 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
     p.perm = std::move(perm);
     p.groups = std::move(groups);
     p.binbase = std::move(binbase);
+    p.noguess = std::move(noguess);
     p.groups.clear();
     p.nq = nq;
-    p.guesses = guesses;
     p.short_form = short_form;
     p.qd.resize(nq);
     p.ebase.assign(nq + 1, 0);
     p.rbase.assign(nq + 1, 0);
     p.perm.resize(nq);
     std::vector<int> hb(nq);
+    auto may_guess = [&](int32_t i) { return p.noguess.empty() || !p.noguess[static_cast<size_t>(i)]; };
     uint32_t dmax = 0;
     for (int32_t i = 0; i < nq; ++i) {
         const rn_query &x = q[i];
         hb[i] = x.hash_log2 ? x.hash_log2
-                            : (sure_global(g, x) ? kGlobalHB : first_table(g, x, guesses));
+                            : (sure_global(g, x) ? kGlobalHB : first_table(g, x, may_guess(i)));
         p.any_kcp |= x.k > 0;
         dmax = std::max(dmax, x.theta);
         p.total_R += static_cast<uint64_t>(std::max(x.nR, 0));
@@ -337,7 +339,7 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
         d.gdelta = g->gdelta[x.graph];
         d.wmin = g->w_min[x.graph];
         d.slack = ring_slack(g->wmean[x.graph]);
-        d.guess = x.k > 0 && guesses && hb[i] != kGlobalHB ? guess_bound(g, x, nullptr) : kInf;
+        d.guess = x.k > 0 && may_guess(static_cast<int32_t>(i)) && hb[i] != kGlobalHB ? guess_bound(g, x, nullptr) : kInf;
         d.sbits = static_cast<uint32_t>(sw);
         d.rbits = static_cast<uint32_t>(rw);
         d.hist = x.k ? nkcp * kHistWords : 0;
@@ -989,14 +991,18 @@ rn_status finish(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, in
     return RN_OK;
 }
 
+const QueryState *query_states(const Workspace &ws) {
+    return reinterpret_cast<const QueryState *>(ws.h_state + sizeof(CallCtl));
+}
+
 // RN_ROUTE_* bits of a call as it was enqueued and ended.
 int32_t route_of(const Workspace &ws, const Prepared &p) {
     const CallCtl &c = *reinterpret_cast<const CallCtl *>(ws.h_state);
     int32_t r = 0;
     for (const Group &gr : p.groups)
         if (gr.hb <= kMaxHB) r |= gr.quads ? RN_ROUTE_QUADS : RN_ROUTE_WINDOWS;
-    for (const QueryDesc &d : p.qd)
-        if (d.guess != kInf) r |= RN_ROUTE_GUESS;
+    for (int32_t i = 0; i < p.nq; ++i)
+        if (query_states(ws)[i].guessed & kGuessMade) r |= RN_ROUTE_GUESS;
     if (p.tail_one) r |= RN_ROUTE_SHORT;
     if (p.tail_one && handed_over(c)) r |= RN_ROUTE_SHORT_LEFT;
     if (c.unmet & kUnmetGuess) r |= RN_ROUTE_GUESS_MISSED;
@@ -1005,11 +1011,16 @@ int32_t route_of(const Workspace &ws, const Prepared &p) {
     return r;
 }
 
-// Prepare a call again, without guesses where they were not met.
-rn_status prepare_again(const rn_graph *g, const rn_query *q, Prepared &p, bool unguessed) {
-    return prepare(g, q, p.nq, p, p.guesses && !unguessed, p.short_form);
+// Prepare a call again.  qs (or null): its state; no guess any more for the
+// queries that missed theirs.
+rn_status prepare_again(const rn_graph *g, const rn_query *q, Prepared &p, const QueryState *qs) {
+    if (qs) {
+        p.noguess.resize(static_cast<size_t>(p.nq), 0);
+        for (int32_t i = 0; i < p.nq; ++i)
+            if (qs[i].guessed & kGuessMissed) p.noguess[static_cast<size_t>(i)] = 1;
+    }
+    return prepare(g, q, p.nq, p, p.short_form);
 }
-
 // One eager call on workspace ws (prepared p, from the queries q); runs it again
 // or goes on with it as finish says.
 rn_status run_eager(rn_graph *g, Workspace &ws, Prepared &p, const rn_query *q, rn_pair *out, int64_t cap,
@@ -1032,8 +1043,10 @@ rn_status run_eager(rn_graph *g, Workspace &ws, Prepared &p, const rn_query *q, 
         const rn_status st = finish(g, ws, p, out, cap, offsets, status, timed, &next, s);
         if (timed) g->stats.route = route;
         if (st != RN_OK || next == Next::kDone) return st;
-        if (next == Next::kUnguessed) RN_TRY(prepare_again(g, q, p, true));
-        if (next == Next::kHandOver) p.short_form = p.tail_one = p.stage_one = false;
+        if (next == Next::kUnguessed) RN_TRY(prepare_again(g, q, p, query_states(ws)));
+        if (next == Next::kHandOver) {
+            p.short_form = p.tail_one = p.stage_one = false;
+        }
     }
     return fail(RN_ERR_NOMEM, "record buffer did not settle");
 }
@@ -1044,7 +1057,7 @@ rn_status run_batch(rn_graph *g, const rn_query *q, int32_t nq, rn_pair *out, in
     RN_TRY(check_queries(g, q, nq, status));
     RN_HIP(hipSetDevice(g->device), "selecting the device");
     Prepared p;
-    RN_TRY(prepare(g, q, nq, p, true, true));
+    RN_TRY(prepare(g, q, nq, p, true));
     return run_eager(g, g->ws, p, q, out, cap, offsets, status, s, true);
 }
 
@@ -1789,7 +1802,8 @@ rn_status rn_autotune(rn_graph *g, rn_query *q, int32_t nq, int32_t sample, void
                 t.delta = di < 3 ? deltas[di] : g->delta;
                 t.hash_log2 = di < 3 ? hbs[hi] : kGlobalHB;
                 Prepared p;
-                result = prepare(g, &t, 1, p, false);   // (a guess would hide what the setting costs)
+                p.noguess.assign(1, 1);   // (a guess would hide what the setting costs)
+                result = prepare(g, &t, 1, p);
                 if (result != RN_OK) break;
                 float ms = 3.4e38f;
                 for (int rep = 0; rep < 3 && result == RN_OK; ++rep) {
@@ -1860,7 +1874,7 @@ rn_status plan_build(rn_plan *pl, Prepared &p, hipStream_t s, int64_t *offsets, 
     const rn_status st = run_eager(pl->g, pl->ws, p, pl->q.data(), pl->out, pl->cap, offsets, status, s, false);
     if (st != RN_OK && st != RN_ERR_CAPACITY && st != RN_ERR_ARG) return st;
     if (short_form && !p.short_form) {   // handed over: from now on in the general form
-        RN_TRY(prepare_again(pl->g, pl->q.data(), p, false));
+        RN_TRY(prepare_again(pl->g, pl->q.data(), p, nullptr));
         RN_TRY(ensure_buffers(pl->ws, p));
     }
     RN_TRY(capture_plan(pl, p));
@@ -1887,7 +1901,7 @@ rn_status rn_plan_create(rn_graph *g, const rn_query *q, int32_t nq, rn_pair *ou
     pl->cap = cap;
     pl->q.assign(q, q + nq);
     Prepared &p = pl->prep;
-    rn_status st = prepare(g, q, nq, p, true, true);
+    rn_status st = prepare(g, q, nq, p, true);
     hipError_t e = hipSuccess;
     if (st == RN_OK && (e = hipStreamCreateWithFlags(&pl->cap_stream, hipStreamNonBlocking)) != hipSuccess)
         st = hip_fail(e, "creating the capture stream");
@@ -1914,7 +1928,7 @@ rn_status rn_plan_run(rn_plan *pl, int64_t *offsets, int32_t *status, void *stre
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     Prepared &p = pl->prep;
     if (!pl->exec) {   // the last run could not build it again
-        RN_TRY(prepare_again(g, pl->q.data(), p, false));
+        RN_TRY(prepare_again(g, pl->q.data(), p, nullptr));
         return plan_build(pl, p, s, offsets, status);
     }
     RN_HIP(hipGraphLaunch(pl->exec, s), "launching the graph");
@@ -1928,7 +1942,8 @@ rn_status rn_plan_run(rn_plan *pl, int64_t *offsets, int32_t *status, void *stre
     drop_graph(pl);
     if (st != RN_OK) return st;
     if (next == Next::kHandOver) p.short_form = false;
-    if (next != Next::kAgain) RN_TRY(prepare_again(g, pl->q.data(), p, next == Next::kUnguessed));
+    if (next != Next::kAgain) 
+        RN_TRY(prepare_again(g, pl->q.data(), p, next == Next::kUnguessed ? query_states(pl->ws) : nullptr));
     return plan_build(pl, p, s, offsets, status);
 }
 

@@ -156,7 +156,8 @@ struct Prepared {
     bool need_list1 = false;
     bool all_quads = true;          // every query's first searches are over arc quads
     bool compact_list0 = true;      // the re-run at 2^11 may take compact tables (over quads)
-    bool guesses = true;            // k-closest-pairs queries may start from a guessed bound
+    std::vector<char> noguess;      // set by the caller, or empty: per query, its searches may not start
+                                    // from a guessed bound
     bool short_form = false;        // small one-query calls may take the short form
     bool stage_one = false;         // one-block staging (launch_stage_one)
     bool tail_one = false;          // one-block tail (launch_tail_one), no re-run tiers: the short form
@@ -181,14 +182,14 @@ struct Prepared {
 std::string describe_err(uint32_t err);
 // Host-side checks of a batch (status[i] marks the malformed queries).
 rn_status check_queries(const rn_graph *g, const rn_query *q, int32_t nq, int32_t *status);
-// guesses: k-closest-pairs searches may start from a guessed bound; a call whose
-// state then reports an unmet guess (ctl.unmet) is prepared again without them
-// and run again.  short_form: small one-query calls may take the one-block
-// staging and tail, without the re-run tiers; a call that needs those after all,
-// or has more records than that tail sorts, is gone on with in the general form
-// (enqueue_handed_over, after clearing short_form, tail_one and stage_one).
-rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p, bool guesses = true,
-                  bool short_form = false);
+// k-closest-pairs searches may start from a guessed bound (but for p.noguess); where
+// the call's state then reports an unmet guess (ctl.unmet, and kGuessMissed of the
+// queries), it is run again without those.  short_form: small one-query calls may
+// take the one-block staging and tail, without the re-run tiers; a call that needs
+// those after all, or has more records than that tail sorts, is gone on with in the
+// general form (enqueue_handed_over, after clearing short_form, tail_one and
+// stage_one).
+rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p, bool short_form = false);
 // Global-tier slots are allocated on demand: a call enqueued while a
 // workspace has none skips the global tier, and if any of its searches needed
 // it (ctl.nlist[2] > 0) the call is run again once slots exist.  Allocate (once)

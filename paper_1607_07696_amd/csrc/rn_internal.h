@@ -79,9 +79,12 @@ static_assert(sizeof(QueryDesc) == 80, "QueryDesc is 80 bytes");
 constexpr uint32_t kOrientSwap = 1u << 31;
 
 // CallCtl::unmet: a k-query found fewer than k pairs within its guess (run again
-// without guesses); the call has more candidates than its one-block tail sorts
-// (run again without it).
+// without that guess); the call has more candidates than its one-block tail sorts
+// (gone on with in the general form).
 constexpr uint32_t kUnmetGuess = 1u, kUnmetTail = 2u;
+// QueryState::guessed (k > 0): the searches started from the query's guess; fewer
+// than k pairs lie within it.
+constexpr uint32_t kGuessMade = 1u, kGuessMissed = 2u;
 
 // Per-query device state of one call.  Zeroed first.
 struct QueryState {
@@ -96,7 +99,7 @@ struct QueryState {
     unsigned long long start;   // first kept record of the query in the sorted order
     unsigned long long nout;    // pairs written for the query
     unsigned long long off;     // first output position of the query
-    uint32_t guessed;           // k > 0: the searches started from the query's guess
+    uint32_t guessed;           // kGuess* bits
     uint32_t pad2;
 };
 static_assert(sizeof(QueryState) == 64, "QueryState is 64 bytes");

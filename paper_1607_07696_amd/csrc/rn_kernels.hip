@@ -2916,7 +2916,7 @@ __global__ __launch_bounds__(64) void k_kcp_seed_bound(const QueryDesc *qd, Quer
     const uint32_t b = min(sure, d.guess);
     if (threadIdx.x == 0) {
         qs[blockIdx.x].bound = b;
-        qs[blockIdx.x].guessed = b < sure ? 1u : 0u;
+        qs[blockIdx.x].guessed = b < sure ? kGuessMade : 0u;
         qs[blockIdx.x].direct =
             allow_direct && static_cast<uint64_t>(b) < 2ull * static_cast<uint64_t>(d.wmin) ? 1u : 0u;
     }
@@ -3113,7 +3113,7 @@ __global__ __launch_bounds__(1024) void k_stage_one(JoinArgs a, CallBuffers b, u
             const uint32_t bd = min(sure, d.guess);
             if (tid == 0) {
                 b.qs[0].bound = bd;
-                b.qs[0].guessed = bd < sure ? 1u : 0u;
+                b.qs[0].guessed = bd < sure ? kGuessMade : 0u;
             }
         }
     }
@@ -3252,7 +3252,10 @@ __device__ __forceinline__ void layout_block(const CallBuffers &b, int selected,
             if (b.nq == 1) st.npairs = b.ctl->npairs;   // (counted for the call only)
             nsel = (selected && d.k) ? st.nsel : st.npairs;   // a theta-join keeps every record
             // every pair within the guess was found, but not k of them
-            if (d.k && st.guessed && !st.err && nsel < d.k) b.ctl->unmet = kUnmetGuess;
+            if (d.k && (st.guessed & kGuessMade) && !st.err && nsel < d.k) {
+                st.guessed = kGuessMade | kGuessMissed;
+                b.ctl->unmet = kUnmetGuess;
+            }
             nout = st.err ? 0ull : (d.k ? min(nsel, static_cast<unsigned long long>(d.k)) : nsel);
             if (nsel) atomicMax(&s_dmax, d.k ? st.bound : d.theta);
         }
@@ -3808,7 +3811,10 @@ __global__ __launch_bounds__(1024) void k_tail_one(CallBuffers b, uint32_t vb, r
         }
     }
     if (tid == 0) {
-        if (mine && d.k && st.guessed && !st.err && kept < d.k) ctl->unmet = kUnmetGuess;
+        if (mine && d.k && (st.guessed & kGuessMade) && !st.err && kept < d.k) {
+            st.guessed = kGuessMade | kGuessMissed;
+            ctl->unmet = kUnmetGuess;
+        }
         ctl->nsel = mine ? kept : 0u;
         ctl->nout = nout;
         st.npairs = n64;

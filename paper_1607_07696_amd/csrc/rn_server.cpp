@@ -43,6 +43,7 @@ struct Request {
     double footprint = 0;           // estimated device bytes while in flight
     bool heavy = false;             // estimated search work above kHeavyWork
     bool held = false;              // was once held back by the HBM budget
+    bool noguess = false;           // k > 0: missed its guessed bound, to be searched without
     Clock::time_point t_submit, t_done;
     std::vector<rn_pair> result;
     rn_status status = RN_OK;
@@ -194,6 +195,7 @@ rn_status launch_lane(rn_server *s, Lane &L) {
         L.ids_cap = cap;
     }
     L.q.assign(L.batch.size(), rn_query{});
+    L.prep.noguess.assign(L.batch.size(), 0);
     size_t off = 0;
     for (size_t i = 0; i < L.batch.size(); ++i) {
         const Request *r = L.batch[i];
@@ -209,6 +211,7 @@ rn_status launch_lane(rn_server *s, Lane &L) {
         q.theta = r->theta;
         q.delta = RN_DELTA_DEFAULT;
         q.hash_log2 = 0;
+        L.prep.noguess[i] = r->noguess ? 1 : 0;
         off += r->R.size() + r->S.size();
     }
     RN_HIP(hipMemcpyAsync(L.d_ids, L.h_ids, words * sizeof(int32_t), hipMemcpyHostToDevice, L.stream),
@@ -253,19 +256,7 @@ bool progress_lane(rn_server *s, Lane &L) {
             else L.out_cap = cap;
             rerun = true;
         }
-        if (!rerun && c.unmet) {
-            // a k-query had fewer than k pairs within its guess: again without guesses
-            st = prepare(s->g, L.q.data(), static_cast<int32_t>(L.q.size()), L.prep, false);
-            if (st == RN_OK) st = ensure_buffers(L.ws, L.prep);
-            if (st == RN_OK && L.prep.nq > 1) {
-                fill_host_desc(L.prep, L.ws.h_desc);
-                const hipError_t ec = hipMemcpyAsync(L.ws.d_desc, L.ws.h_desc, L.prep.desc_bytes, hipMemcpyHostToDevice,
-                                                     L.stream);
-                if (ec != hipSuccess) st = hip_fail(ec, "uploading queries");
-            }
-            rerun = true;
-        }
-        if (rerun && st == RN_OK && ++L.reruns <= 4) {
+        if (rerun && st == RN_OK && ++L.reruns <= 3) {
             {
                 std::lock_guard<std::mutex> lk(s->mu);
                 s->stats.reruns += 1;
@@ -315,8 +306,12 @@ bool progress_lane(rn_server *s, Lane &L) {
             return true;
         }
         const QueryState *qs = reinterpret_cast<const QueryState *>(L.ws.h_state + sizeof(CallCtl));
+        // a k-query that had fewer than k pairs within its guess waits again, first
+        // in line, and is searched without one; the others of the batch are done
+        auto missed = [&](size_t i) { return (qs[i].guessed & kGuessMissed) != 0; };
         for (size_t i = 0; i < L.batch.size(); ++i) {
             Request *r = L.batch[i];
+            if (missed(i)) continue;
             r->result.assign(L.h_out + qs[i].off, L.h_out + qs[i].off + qs[i].nout);
         }
         std::lock_guard<std::mutex> lk(s->mu);
@@ -330,12 +325,21 @@ bool progress_lane(rn_server *s, Lane &L) {
                 s->c_ball = 0.8 * s->c_ball + 0.2 * c;
             }
         }
+        int64_t again = 0;
+        for (size_t i = L.batch.size(); i-- > 0;) {
+            if (!missed(i)) continue;
+            L.batch[i]->noguess = true;
+            s->pending.push_front(L.batch[i]);
+            ++again;
+        }
         for (size_t i = 0; i < L.batch.size(); ++i) {
             Request *r = L.batch[i];
+            if (missed(i)) continue;
             if (qs[i].err) finish_request(s, r, RN_ERR_ARG, "invalid node sets:" + describe_err(qs[i].err));
             else finish_request(s, r, RN_OK, std::string());
         }
-        s->stats.completed += static_cast<int64_t>(L.batch.size());
+        s->stats.completed += static_cast<int64_t>(L.batch.size()) - again;
+        s->stats.reruns += again;
         s->budget_used -= L.reserved;
         s->in_flight_requests -= static_cast<int>(L.batch.size());
         L.batch.clear();

@@ -91,3 +91,36 @@ def test_server(rnmod, orc, rg):
     for rid, (R, S) in zip(ids, sets):
         same(server.wait(rid)[0], orc.kcp_join(g, R, S, 25))
     server.close()
+
+
+def test_one_missed_guess_among_others(rnmod, orc, rg):
+    # R and S apart in an order of the ids that does not show it: the guess is
+    # made and missed; the batch's and the server's other queries are not the worse
+    g, perm = rg.shuffle_ids(rg.road_graph(150, 2), 5)[:2]
+    net = rnmod.RoadNetwork.from_graph(g)
+    R2, S2 = (perm[x].astype(np.int32) for x in apart(g.V, 200, 2))
+    sets = [rg.sample_disjoint(g.V, 300, 400, i) for i in range(3)]
+    specs = [{"R": R, "S": S, "k": 50 + i} for i, (R, S) in enumerate(sets)] + [{"R": R2, "S": S2, "k": 20}]
+    want = [orc.kcp_join(g, sp["R"], sp["S"], sp["k"]) for sp in specs]
+    for _ in range(2):
+        out, off, status = net.join_batch(specs)
+        assert not status.any()
+        for a, b in zip(rnmod.split_batch(out, off), want):
+            same(a, b)
+        route = net.stats()["route"]
+        assert route & rnmod.RN_ROUTE_GUESS and route & rnmod.RN_ROUTE_GUESS_MISSED
+    q, keep = net.make_queries(specs)
+    plan = net.plan(q, cap=sum(len(w) for w in want))
+    for _ in range(3):
+        got, off, _ = plan.run()
+        for a, b in zip(rnmod.split_batch(got, off), want):
+            same(a, b)
+    plan.close()
+    server = rnmod.Server(net, lanes=1)
+    for _ in range(2):
+        ids = [server.submit(sp["R"], sp["S"], k=sp["k"]) for sp in specs]
+        for rid, w in zip(ids, want):
+            same(server.wait(rid)[0], w)
+    st = server.stats()
+    assert st["reruns"] >= 2 and st["completed"] == 8, st
+    server.close()

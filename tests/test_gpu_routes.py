@@ -47,7 +47,7 @@ def test_short_form_and_guess(rnmod, orc, rg):
     R, S = rg.sample_disjoint(g.V, 300, 300, 3)
     same(rnmod.pairs_to_numpy(net.dist_join(R, S, 900)), orc.dist_join(g, R, S, 900).pairs)
     assert net.stats()["route"] == rnmod.RN_ROUTE_QUADS | rnmod.RN_ROUTE_SHORT
-    same(rnmod.pairs_to_numpy(net.kcp_join(R, S, 16)), orc.kcp_join(g, R, S, 16))
+    same(rnmod.pairs_to_numpy(net.kcp_join(R, S, 40)), orc.kcp_join(g, R, S, 40))
     assert net.stats()["route"] == rnmod.RN_ROUTE_QUADS | rnmod.RN_ROUTE_SHORT | rnmod.RN_ROUTE_GUESS
     # R among the first rows of the grid, S among the last
     Ra, Sa = np.arange(0, 1500, 7, dtype=np.int32), np.arange(g.V - 1500, g.V, 7, dtype=np.int32)
