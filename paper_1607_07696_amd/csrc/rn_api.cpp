@@ -1046,6 +1046,11 @@ rn_status run_eager(rn_graph *g, Workspace &ws, Prepared &p, const rn_query *q, 
         if (next == Next::kUnguessed) RN_TRY(prepare_again(g, q, p, query_states(ws)));
         if (next == Next::kHandOver) {
             p.short_form = p.tail_one = p.stage_one = false;
+            if (q[0].k > 0 && q[0].k <= static_cast<int32_t>(kSmallSort / 2)) {   // (as prepare chooses)
+                p.small_sort = true;
+                p.mixed_bins = false;
+                p.nbins = 0;
+            }
         }
     }
     return fail(RN_ERR_NOMEM, "record buffer did not settle");

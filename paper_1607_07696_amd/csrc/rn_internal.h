@@ -83,8 +83,8 @@ constexpr uint32_t kOrientSwap = 1u << 31;
 // (gone on with in the general form).
 constexpr uint32_t kUnmetGuess = 1u, kUnmetTail = 2u;
 // QueryState::guessed (k > 0): the searches started from the query's guess; fewer
-// than k pairs lie within it.
-constexpr uint32_t kGuessMade = 1u, kGuessMissed = 2u;
+// than k pairs lie within it; R and S lie apart, so that none was made.
+constexpr uint32_t kGuessMade = 1u, kGuessMissed = 2u, kSetsApart = 4u;
 
 // Per-query device state of one call.  Zeroed first.
 struct QueryState {
@@ -100,7 +100,7 @@ struct QueryState {
     unsigned long long nout;    // pairs written for the query
     unsigned long long off;     // first output position of the query
     uint32_t guessed;           // kGuess* bits
-    uint32_t pad2;
+    uint32_t near;              // k > 0: pairs of an R and an S member in one block of ids (near_shift)
 };
 static_assert(sizeof(QueryState) == 64, "QueryState is 64 bytes");
 

@@ -400,6 +400,7 @@ struct SrcCtx {
     QueryState *qs;                 // the query's state
     const unsigned long long *npairs;   // records the query has emitted
     bool guessed;                   // the searches start from a guessed bound
+    bool apart;                     // R and S lie apart: no guess was made
 };
 
 __device__ __forceinline__ uint32_t uni(uint32_t v) {
@@ -434,7 +435,9 @@ __device__ __forceinline__ SrcCtx load_ctx(const JoinArgs &a, uint32_t q0) {
     c.sbits = a.sbits + same(d.sbits);
     c.hist = c.k ? a.hists + same(d.hist) : nullptr;
     c.qs = a.qs + q;
-    c.guessed = c.k != 0 && c.qs->guessed != 0;
+    const uint32_t guess = c.k != 0 ? same(c.qs->guessed) : 0u;
+    c.guessed = (guess & kGuessMade) != 0;
+    c.apart = (guess & kSetsApart) != 0;
     c.npairs = a.one ? &a.ctl->npairs : &a.qs[q].npairs;
     return c;
 }
@@ -1708,14 +1711,27 @@ __device__ __forceinline__ void probe_step(const SrcCtx &c, uint32_t n, uint32_t
 }
 
 // The bound and the count are read every kPoll steps, and used a step later, so
-// that no step waits for them.
+// that no step waits for them.  Where R and S lie apart, nothing but the others'
+// discoveries bounds the searches: then one-wave searches read them, and wait, in
+// every step (now; 1 000 x 1 000 sets in the two halves of a 300 x 300 graph: with
+// late values 184 searches outgrew their tables, with these none, 79 -> 54 us; the
+// long searches of a block lose by it, whole ones on a 64 x 64 graph 440 -> 635).
 constexpr uint32_t kPoll = 2;
 constexpr uint32_t kPollGuessed = 8;
 __device__ __forceinline__ void poll_bound(const SrcCtx &c, uint32_t &phase, uint32_t &nbound, uint32_t &ncount,
-                                           uint32_t &bound, uint32_t &pnew, bool &probing, uint32_t &seen) {
+                                           uint32_t &bound, uint32_t &pnew, bool &probing, uint32_t &seen,
+                                           bool now) {
     // small searches (the first two steps) never count discoveries, and those
     // that start from a guess hardly gain from it
     const uint32_t first = c.guessed ? kPollGuessed : 2u;
+    if (now) {
+        if (phase >= 2u) {
+            probe_phase(c, pnew, probing, seen);
+            bound = uni(current_bound(c));
+        }
+        ++phase;
+        return;
+    }
     if (phase >= first && phase % kPoll == 0) {
         bound = min(uni(nbound), c.theta);
         probe_step(c, uni(ncount), pnew, probing, seen);
@@ -1766,7 +1782,7 @@ __device__ void search_quads(QuadLds<HB, CT> &L, const JoinArgs &a, const SrcCtx
         const uint32_t np = st.tail - head;
         if (np == 0 || st.ovf) break;
         if (c.hist != nullptr) {
-            poll_bound(c, phase, nbound, ncount, bound, st.pnew, st.probing, seen);
+            poll_bound(c, phase, nbound, ncount, bound, st.pnew, st.probing, seen, c.apart);
         }
         const uint32_t m = min(16u * T::NR, np);
         switch ((m + 15u) / 16u) {
@@ -1924,7 +1940,7 @@ __device__ void search_quads_block(QuadLds<HB, CT> &L, QuadBlock &B, const JoinA
         ovf = (f & kQuadOvf) != 0u;
         if (ovf || st.tail == head) break;
         const uint32_t lim = sat_add(uni(last.dmin), slack);
-        if (c.hist != nullptr) poll_bound(c, phase, nbound, ncount, bound, st.pnew, st.probing, seen);
+        if (c.hist != nullptr) poll_bound(c, phase, nbound, ncount, bound, st.pnew, st.probing, seen, false);
         if (threadIdx.x == 0) B.step[s1] = QuadStep{0u, kInf};   // read in the last step, used in the next one
         const uint32_t m = min(16u * T::NR * NW, st.tail - head);
         const uint32_t rows = (m + 15u) / 16u;
@@ -2624,7 +2640,7 @@ __global__ __launch_bounds__(1024) void k_join_dense(JoinArgs a, uint32_t *slots
             ovf = (f & kQuadOvf) != 0u;
             if (ovf || st.tail == head) break;
             const uint32_t lim = sat_add(uni(last.dmin), slack);
-            if (c.hist != nullptr) poll_bound(c, phase, nbound, ncount, bound, st.pnew, st.probing, seen);
+            if (c.hist != nullptr) poll_bound(c, phase, nbound, ncount, bound, st.pnew, st.probing, seen, false);
             if (tid == 0) L.B.step[s1] = QuadStep{0u, kInf};   // read in the last step, used in the next one
             const uint32_t m = min(16u * kDR * kDW, st.tail - head);
             const uint32_t rows = (m + 15u) / 16u;
@@ -2805,6 +2821,53 @@ __device__ __forceinline__ uint32_t block_excl_scan_1024(uint32_t v, uint32_t *w
     return off + incl - v;
 }
 
+// Whether a k-closest-pairs query may start from its guess: the guess takes R and S
+// to be spread over the same region, and where they lie apart its pass is lost
+// (1 000 x 1 000 sets in the two halves of a 300 x 300 graph: 119 us without, 165
+// with it).  Vertices near in the graph are mostly near in the device copy's
+// numbering (as loaded, or leaf by leaf), so the members that share a block of
+// about as many ids as the guessed ball has vertices tell: if R and S are spread
+// alike there are about as many such pairs as the guess aims at, and a guess with
+// less than an eighth of that is not made.  (In a numbering without order there
+// are as many wherever the sets lie: then a guess may still be missed.)
+// Blocks are of 2^near_shift words of 32 ids.
+__device__ __forceinline__ uint32_t guess_aim(uint32_t k) { return k + k / 2u + 8u; }
+__device__ __forceinline__ uint32_t near_shift(const QueryDesc &d) {
+    const float ball = static_cast<float>(guess_aim(d.k)) * static_cast<float>(d.V) /
+                       (static_cast<float>(d.nR) * static_cast<float>(d.nS));
+    uint32_t sh = 0;
+    while (sh < 6u && ball >= static_cast<float>(64u << sh)) ++sh;
+    return sh;
+}
+__device__ __forceinline__ bool sets_apart(const QueryDesc &d, uint32_t near) {
+    const float expect = static_cast<float>(d.nR) * static_cast<float>(d.nS) *
+                         static_cast<float>(32u << near_shift(d)) / static_cast<float>(d.V);
+    return expect >= 4.0f && static_cast<float>(near) < 0.125f * expect;
+}
+// Pairs in one block, of the words r and s of this lane and its wave's (words in
+// order; q: the lane's query, kInf: none; sh: its near_shift).  Whole wave; the
+// block's first lane gets them, the others 0.
+__device__ __forceinline__ uint32_t near_pairs(uint32_t r, uint32_t s, uint32_t q, uint32_t sh) {
+    const uint32_t lane = lane_id();
+    uint32_t nr = __popc(r), ns = __popc(s);
+    for (uint32_t t = 0; __ballot(t < sh) != 0; ++t) {
+        const int o = 1 << t;
+        const uint32_t xr = static_cast<uint32_t>(__shfl_xor(static_cast<int>(nr), o));
+        const uint32_t xs = static_cast<uint32_t>(__shfl_xor(static_cast<int>(ns), o));
+        const uint32_t xq = static_cast<uint32_t>(__shfl_xor(static_cast<int>(q), o));
+        if (t < sh && xq == q) {
+            nr += xr;
+            ns += xs;
+        }
+    }
+    return q != kInf && (lane & ((1u << sh) - 1u)) == 0u ? nr * ns : 0u;   // (at most 2 048 each)
+}
+
+// (Sums that far above any expected number need not be exact.)
+__device__ __forceinline__ void add_near(QueryState &st, uint32_t n) {
+    if (__hip_atomic_load(&st.near, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < 0x40000000u) atomicAdd(&st.near, n);
+}
+
 // Source listing, pass 1 (calls of more than kListOnePass rank words): the marked
 // ranks per 1024-word block of the rank pool.
 __global__ __launch_bounds__(1024) void k_rank_count(CallBuffers b) {
@@ -2823,7 +2886,25 @@ __global__ __launch_bounds__(1024) void k_rank_count(CallBuffers b) {
 constexpr uint32_t kListOnePass = 65536;
 __global__ __launch_bounds__(1024) void k_rank_emit(CallBuffers b, const uint32_t *bsum) {
     __shared__ uint32_t wsum[16];
+    __shared__ uint32_t s_near, s_q;
     const uint32_t tid = threadIdx.x;
+    // this thread's word and its query, read before the counting that waits
+    const uint32_t i = blockIdx.x * 1024u + tid;
+    const bool valid = i < b.rwords;
+    uint32_t bits = 0, sw = 0, q = kInf, lw = 0, sh = 0;
+    int32_t voff = 0;
+    bool may = false;
+    if (valid) {
+        bits = b.rbits[i];
+        const uint32_t p = seg_of(b.rbase, static_cast<uint32_t>(b.nq), i);
+        q = b.perm[p];
+        lw = i - b.rbase[p];
+        const QueryDesc &d = b.qd[q];
+        voff = d.voff;
+        sw = b.sbits[d.sbits + lw];
+        may = d.k != 0 && d.guess != kInf;
+        if (may) sh = near_shift(d);
+    }
     uint32_t acc = 0;
     if (bsum) {
         for (uint32_t j = tid; j < blockIdx.x; j += 1024) acc += bsum[j];
@@ -2835,20 +2916,27 @@ __global__ __launch_bounds__(1024) void k_rank_emit(CallBuffers b, const uint32_
             acc += __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
         }
     }
+    if (tid == 0) {
+        s_near = 0;
+        s_q = q;
+    }
     uint32_t pre;
     block_excl_scan_1024(acc, wsum, &pre);
-    const uint32_t i = blockIdx.x * 1024u + tid;
-    const bool valid = i < b.rwords;
-    uint32_t bits = valid ? b.rbits[i] : 0u;
+    // k closest pairs that may start from a guess: pairs within a block of ids,
+    // summed over the block for the query of its first word (one atomic; one a wave
+    // took 11 us for a million vertices), by a lane's own atomic for others
+    if (__ballot(may) != 0) {
+        const uint32_t n = near_pairs(bits, sw, may ? q : kInf, sh);
+        const uint32_t sum = readlane(wave_incl_scan(q == s_q ? n : 0u), 63);
+        if (lane_id() == 0 && sum != 0) atomicAdd(&s_near, sum);
+        if (n != 0 && q != s_q) add_near(b.qs[q], n);
+    }
     uint32_t total;
     uint32_t pos = pre + block_excl_scan_1024(__popc(bits), wsum, &total);
+    if (tid == 0 && s_near != 0) add_near(b.qs[q], s_near);
     if (valid) {
-        const uint32_t p = seg_of(b.rbase, static_cast<uint32_t>(b.nq), i);
-        const uint32_t q = b.perm[p];
-        const uint32_t lw = i - b.rbase[p];
-        const int32_t voff = b.qd[q].voff;
         if (lw == 0) b.qs[q].src_start = pos;
-        if (bits && (bits & b.sbits[b.qd[q].sbits + lw])) {
+        if (bits & sw) {
             atomicOr(&b.qs[q].err, kErrOverlap);
             atomicOr(&b.ctl->err, kErrOverlap);
         }
@@ -2913,10 +3001,11 @@ __global__ __launch_bounds__(64) void k_kcp_seed_bound(const QueryDesc *qd, Quer
     const QueryDesc &d = qd[blockIdx.x];
     if (d.k == 0) return;
     const uint32_t sure = min(wave_bound_from_hist(hists + d.hist + kHistSeed, d.k), d.theta);
-    const uint32_t b = min(sure, d.guess);
+    const bool apart = d.guess != kInf && sets_apart(d, qs[blockIdx.x].near);
+    const uint32_t b = apart ? sure : min(sure, d.guess);
     if (threadIdx.x == 0) {
         qs[blockIdx.x].bound = b;
-        qs[blockIdx.x].guessed = b < sure ? kGuessMade : 0u;
+        qs[blockIdx.x].guessed = b < sure ? kGuessMade : (apart ? kSetsApart : 0u);
         qs[blockIdx.x].direct =
             allow_direct && static_cast<uint64_t>(b) < 2ull * static_cast<uint64_t>(d.wmin) ? 1u : 0u;
     }
@@ -3044,7 +3133,7 @@ __global__ __launch_bounds__(1024) void k_stage_one(JoinArgs a, CallBuffers b, u
     __shared__ uint32_t sb[kStage1Vertices / 32], rb[kStage1Vertices / 32];
     alignas(16) __shared__ uint32_t h[KCP ? kDistBins : 4];
     __shared__ uint32_t wsum[16];
-    __shared__ uint32_t s_err;
+    __shared__ uint32_t s_err, s_near;
     const uint32_t tid = threadIdx.x;
     const QueryDesc &d = *reinterpret_cast<const QueryDesc *>(desc.w);
     const uint32_t words = b.rwords;
@@ -3054,7 +3143,7 @@ __global__ __launch_bounds__(1024) void k_stage_one(JoinArgs a, CallBuffers b, u
     for (uint32_t i = tid; i < hist_words; i += 1024) b.hists[i] = 0u;
     if (tid < words) sb[tid] = rb[tid] = 0u;
     if (KCP && tid < kDistBins) h[tid] = 0u;
-    if (tid == 0) s_err = 0u;
+    if (tid == 0) s_err = s_near = 0u;
     __syncthreads();
     uint32_t err = 0;
     const uint32_t nS = static_cast<uint32_t>(d.nS), nE = nS + static_cast<uint32_t>(d.nR);
@@ -3077,6 +3166,11 @@ __global__ __launch_bounds__(1024) void k_stage_one(JoinArgs a, CallBuffers b, u
         b.sbits[d.sbits + tid] = sb[tid];
     }
     if (err) atomicOr(&s_err, err);
+    if (KCP && d.guess != kInf) {
+        const uint32_t n = near_pairs(bits, tid < words ? sb[tid] : 0u, 0u, near_shift(d));
+        const uint32_t sum = readlane(wave_incl_scan(n), 63);
+        if (lane_id() == 0 && sum != 0) atomicAdd(&s_near, sum);
+    }
     uint32_t nsrc;
     uint32_t pos = block_excl_scan_1024(__popc(bits), wsum, &nsrc);
     while (bits) {
@@ -3110,10 +3204,11 @@ __global__ __launch_bounds__(1024) void k_stage_one(JoinArgs a, CallBuffers b, u
             uint32_t *seed = b.hists + d.hist + kHistSeed;
             for (uint32_t j = tid; j < kDistBins; j += 64) seed[j] = h[j];
             const uint32_t sure = min(wave_bound_from_hist(h, d.k), d.theta);
-            const uint32_t bd = min(sure, d.guess);
+            const bool apart = d.guess != kInf && sets_apart(d, s_near);
+            const uint32_t bd = apart ? sure : min(sure, d.guess);
             if (tid == 0) {
                 b.qs[0].bound = bd;
-                b.qs[0].guessed = bd < sure ? kGuessMade : 0u;
+                b.qs[0].guessed = bd < sure ? kGuessMade : (apart ? kSetsApart : 0u);
             }
         }
     }

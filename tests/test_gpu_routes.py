@@ -49,15 +49,38 @@ def test_short_form_and_guess(rnmod, orc, rg):
     assert net.stats()["route"] == rnmod.RN_ROUTE_QUADS | rnmod.RN_ROUTE_SHORT
     same(rnmod.pairs_to_numpy(net.kcp_join(R, S, 40)), orc.kcp_join(g, R, S, 40))
     assert net.stats()["route"] == rnmod.RN_ROUTE_QUADS | rnmod.RN_ROUTE_SHORT | rnmod.RN_ROUTE_GUESS
-    # R among the first rows of the grid, S among the last
+    # R among the first rows of the grid, S among the last: no guess; the same in an
+    # order of the ids that does not show it: a missed one
     Ra, Sa = np.arange(0, 1500, 7, dtype=np.int32), np.arange(g.V - 1500, g.V, 7, dtype=np.int32)
     same(rnmod.pairs_to_numpy(net.kcp_join(Ra, Sa, 9)), orc.kcp_join(g, Ra, Sa, 9))
-    assert net.stats()["route"] & rnmod.RN_ROUTE_GUESS_MISSED
+    assert not net.stats()["route"] & (rnmod.RN_ROUTE_GUESS | rnmod.RN_ROUTE_GUESS_MISSED)
+    h, perm = rg.shuffle_ids(g, 5)[:2]
+    neth = rnmod.RoadNetwork.from_graph(h)
+    Ra, Sa = perm[Ra].astype(np.int32), perm[Sa].astype(np.int32)
+    same(rnmod.pairs_to_numpy(neth.kcp_join(Ra, Sa, 9)), orc.kcp_join(h, Ra, Sa, 9))
+    assert neth.stats()["route"] & rnmod.RN_ROUTE_GUESS_MISSED
     # more searches, and more vertices, than the short form takes
     for nR, theta in ((5000, 900), (300, 4000)):
         R, S = rg.sample_disjoint(g.V, nR, 5000, 4)
         same(rnmod.pairs_to_numpy(net.dist_join(R, S, theta)), orc.dist_join(g, R, S, theta).pairs)
         assert not net.stats()["route"] & rnmod.RN_ROUTE_SHORT
+
+
+@pytest.mark.parametrize("nR,nS,k", [(300, 300, 5), (1000, 1000, 100), (40, 20000, 30), (150, 150, 2), (6000, 6000, 1500)])
+def test_sets_spread_alike_are_guessed(rnmod, orc, rg, nR, nS, k):
+    # one block of ids after another, up to blocks of 2 048; also beside other queries
+    g = rg.road_graph(330, 2)
+    net = rnmod.RoadNetwork.from_graph(g)
+    made = 0
+    for seed in range(6):
+        R, S = rg.sample_disjoint(g.V, nR, nS, seed)
+        want = orc.kcp_join(g, R, S, k)
+        same(rnmod.pairs_to_numpy(net.kcp_join(R, S, k)), want)
+        made += (net.stats()["route"] & rnmod.RN_ROUTE_GUESS) != 0
+        specs = [{"R": R[:50], "S": S[:50], "theta": 300}, {"R": R, "S": S, "k": k}]
+        batch(rnmod, net, specs, [orc.dist_join(g, R[:50], S[:50], 300).pairs, want])
+        made += (net.stats()["route"] & rnmod.RN_ROUTE_GUESS) != 0
+    assert made == 12
 
 
 def dense_patch(rg, n, seed=3):
