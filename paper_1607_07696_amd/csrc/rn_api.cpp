@@ -175,18 +175,17 @@ void measure_radii(rn_graph *g, int32_t i, uint64_t *dist) {
 }
 
 // Vertices that a table below 2^11 slots has to have room for: the expected ball
-// (about 2 (theta / mean arc weight)^2 vertices on a planar road graph) with a
-// margin of 1.8, and the ball in the densest part met when the graph was loaded,
+// (of a theta-join about 2 (theta / mean arc weight)^2 vertices on a planar road
+// graph, of a guess the ball it was made from) with a margin of 1.8, and the ball in the densest part met when the graph was loaded,
 // with 1.2 (on the synthetic road graphs that is the less of the two).  A query's
 // sets often lie in one part of a graph, a city say: if all its searches outgrow
 // their table the call takes up to three times as long (1 000 searches of 190 to
 // 700 vertices where arcs are a quarter as long as on average: 110 us with 2^11
 // slots from the start, 317 with 2^8 and a re-run).
-double room_needed(const rn_graph *g, const rn_query &x) {
-    const double r = static_cast<double>(x.theta) / std::max(1.0, g->wmean[x.graph]);
-    const double V = static_cast<double>(g->voff[x.graph + 1] - g->voff[x.graph]);
-    const double t = static_cast<double>(x.theta) / std::max(g->least_radius[x.graph], 1e-3);
-    return std::max(1.8 * 2.0 * r * r, 1.2 * std::min(V, kDenseBall * t * t));
+double room_needed(const rn_graph *g, int32_t graph, uint32_t theta, double ball) {
+    const double V = static_cast<double>(g->voff[graph + 1] - g->voff[graph]);
+    const double t = static_cast<double>(theta) / std::max(g->least_radius[graph], 1e-3);
+    return std::max(1.8 * ball, 1.2 * std::min(V, kDenseBall * t * t));
 }
 
 // First on-chip table of a query when the caller set none: for a theta-join the
@@ -204,12 +203,14 @@ int first_table(const rn_graph *g, const rn_query &x, bool guess) {
     int hb = kMinHB;
     if (x.k > 0) {
         double ball = 0;
-        if (!quads || !guess || guess_bound(g, x, &ball) == kInf) return hb;
-        while (hb < kMaxHB && !fits(hb, 1.8 * ball)) ++hb;
+        const uint32_t d = quads && guess ? guess_bound(g, x, &ball) : kInf;
+        if (d == kInf) return hb;
+        while (hb < 11 && !fits(hb, room_needed(g, x.graph, d, ball))) ++hb;
+        while (hb < kMaxHB && hb >= 11 && !fits(hb, 1.8 * ball)) ++hb;
         return hb;
     }
     if (quads)
-        while (hb < 11 && !fits(hb, room_needed(g, x))) ++hb;
+        while (hb < 11 && !fits(hb, room_needed(g, x.graph, x.theta, 2.0 * r * r))) ++hb;
     else
         hb = 11;
     while (hb < kMaxHB && hb >= 11 && !fits(hb, 1.3 * 2.0 * r * r)) ++hb;
@@ -397,7 +398,8 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
         const double expect = x.k > 0 ? 1.5 * x.k : pairs * std::min(1.0, 2.5 * r * r / V);
         const uint32_t dbits = bitlen(x.k > 0 ? std::min(x.theta, p.qd[0].guess) : x.theta);
         const uint32_t vbits = std::max<uint32_t>(1u, bitlen(static_cast<uint64_t>(std::max(g->Vmax - 1, 0))));
-        const bool roomy = x.k > 0 || 0.75 * static_cast<double>(1u << p.groups[0].hb) >= room_needed(g, x);
+        const bool roomy = x.k > 0 || 0.75 * static_cast<double>(1u << p.groups[0].hb) >=
+                                          room_needed(g, x.graph, x.theta, 2.0 * r * r);
         p.tail_one = roomy && (pairs <= kSmallSort || expect <= kSmallSort / 2) && dbits + 2 * vbits <= 63u;
         p.stage_one = p.tail_one && g->voff[x.graph + 1] - g->voff[x.graph] <= kStage1Vertices &&
                       p.total_elems <= kStage1Elems;

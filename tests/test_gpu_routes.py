@@ -154,6 +154,11 @@ def test_tables_hold_the_densest_part(rnmod, orc, rg):
         R, S = ids[:nR], ids[nR:2 * nR]
         same(rnmod.pairs_to_numpy(net.dist_join(R, S, theta)), orc.dist_join(g, R, S, theta).pairs)
         assert net.stats()["retried"] == 0, (nR, theta)
+    # (a guess of 30 vertices a ball on average)
+    R, S = ids[:500], ids[500:1500]
+    same(rnmod.pairs_to_numpy(net.kcp_join(R, S, 100)), orc.kcp_join(g, R, S, 100))
+    st = net.stats()
+    assert st["route"] & rnmod.RN_ROUTE_GUESS and st["retried"] == 0, st
 
 
 def flat_grid(rg):
