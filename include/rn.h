@@ -297,11 +297,13 @@ rn_status rn_join_batch(rn_graph *g, const rn_query *q, int32_t nq, rn_pair *out
 /*
  * rn_autotune -- choose delta and hash_log2 for each query by timing a few
  * candidate settings on a sample of its sources (the first min(nR, sample)
- * entries of R) and keeping the one with the least relaxation time: delta in
- * {0, w_min, 4 w_min} times first table sizes (2^9..2^12 for theta-joins,
- * 2^8..2^10 for k > 0), plus the global tier from the start (RN_TABLE_GLOBAL)
- * with the default delta.  Writes q[i].delta and q[i].hash_log2; results
- * never depend on them.  The device work runs on `stream`.
+ * entries of R) and keeping the one with the least relaxation time: the query's
+ * own (with the table size it takes; another has to beat it by a tenth), delta
+ * in {0, w_min, 4 w_min} times first table sizes (2^9..2^12 for theta-joins,
+ * 2^8..2^10 for k > 0), and the global tier from the start (RN_TABLE_GLOBAL)
+ * with the default delta, which several queries try where their own searches
+ * reach it.  Writes q[i].delta and q[i].hash_log2; results never depend on
+ * them.  The device work runs on `stream`.
  */
 rn_status rn_autotune(rn_graph *g, rn_query *q, int32_t nq, int32_t sample, void *stream);
 

@@ -1799,36 +1799,58 @@ rn_status rn_autotune(rn_graph *g, rn_query *q, int32_t nq, int32_t sample, void
         const int hbs_kcp[3] = {8, 9, 10};
         const int *hbs = t.k ? hbs_kcp : hbs_join;
         const int nh = t.k ? 3 : 4;
+        // (delta, table size), in the form the query will run in: first the query
+        // as it is, which a setting has to beat by a tenth (a sample's searches
+        // leave most of the device idle, where a smaller table gains nothing),
+        // then each delta and size, last the global tier from the start (its
+        // buckets have their own width, so delta does not apply).  That one's
+        // blocks take a CU each, which queries beside it pay for: with several
+        // queries it is tried where the query's own searches reach it (128
+        // queries, 7 of which were alone a little faster in it: 3.7 ms against 2.6)
+        std::vector<std::pair<uint32_t, int>> settings(1, {t.delta, t.hash_log2});
+        for (const uint32_t d : deltas)
+            for (int hi = 0; hi < nh; ++hi) settings.push_back({d, hbs[hi]});
+        settings.push_back({g->delta, kGlobalHB});
         float best = 3.4e38f;
         uint32_t best_delta = g->delta;
         int best_hb = t.k ? kMinHB : g->hash_log2;
-        for (int di = 0; di < 4 && result == RN_OK; ++di) {
-            for (int hi = 0; hi < (di < 3 ? nh : 1) && result == RN_OK; ++hi) {
-                // the fourth setting: the global tier from the start (its
-                // buckets have their own width, so delta does not apply)
-                t.delta = di < 3 ? deltas[di] : g->delta;
-                t.hash_log2 = di < 3 ? hbs[hi] : kGlobalHB;
-                Prepared p;
-                p.noguess.assign(1, 1);   // (a guess would hide what the setting costs)
-                result = prepare(g, &t, 1, p);
-                if (result != RN_OK) break;
-                float ms = 3.4e38f;
-                for (int rep = 0; rep < 3 && result == RN_OK; ++rep) {
-                    result = run_eager(g, g->ws, p, &t, nullptr, 0, nullptr, nullptr, s, true);
-                    if (result == RN_ERR_CAPACITY) result = RN_OK;   // counts only: no output wanted
-                    if (result == RN_ERR_ARG) {
-                        result = RN_OK;   // invalid node sets: keep the defaults for this query
-                        break;
-                    }
-                    if (rep > 0) ms = std::min(ms, g->stats.relax_ms + g->stats.retry_ms);
+        bool reaches_global = nq == 1;
+        for (size_t si = 0; si < settings.size() && result == RN_OK; ++si) {
+            t.delta = settings[si].first;
+            t.hash_log2 = settings[si].second;
+            if (si != 0 && t.hash_log2 == kGlobalHB && !reaches_global) continue;
+            Prepared p;
+            result = prepare(g, &t, 1, p, nq == 1);
+            if (result != RN_OK) break;
+            float ms = 3.4e38f;
+            bool bad = false;
+            for (int rep = 0; rep < 3 && result == RN_OK; ++rep) {
+                result = run_eager(g, g->ws, p, &t, nullptr, 0, nullptr, nullptr, s, true);
+                if (result == RN_ERR_CAPACITY) result = RN_OK;   // counts only: no output wanted
+                if (result == RN_ERR_ARG) {
+                    result = RN_OK;   // invalid node sets: keep the defaults for this query
+                    bad = true;
+                    break;
                 }
-                if (ms < best) {
-                    best = ms;
-                    best_delta = t.delta;
-                    best_hb = t.hash_log2;
-                }
+                // (re-run tiers that had nothing to do are the call's, not the query's)
+                const rn_stats &st = g->stats;
+                const bool reran = st.retried > 0 || st.global_searches > 0 || p.groups[0].hb == kGlobalHB;
+                if (rep > 0) ms = std::min(ms, st.relax_ms + (reran ? st.retry_ms : 0.f));
+                if (si == 0) reaches_global = reaches_global || st.global_searches > 0 || p.groups[0].hb == kGlobalHB;
+            }
+            if (bad) break;
+            if (ms < best) {
+                best = si == 0 ? 0.9f * ms : ms;
+                best_delta = t.delta;
+                best_hb = t.hash_log2;
             }
         }
+        if (result == RN_OK && best_hb == 0) {   // as it is: the table that all its sources take
+            Prepared p;
+            result = prepare(g, &q[i], 1, p);
+            if (result == RN_OK) best_hb = p.groups[0].hb;
+        }
+        if (result != RN_OK) break;
         q[i].delta = best_delta;
         q[i].hash_log2 = best_hb;
     }
