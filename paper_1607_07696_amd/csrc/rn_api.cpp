@@ -1140,7 +1140,7 @@ void choose_quads(rn_graph *g, const std::vector<int32_t> &rrow) {
         }
     }
     g->qbase[static_cast<size_t>(dirs) * g->ngraphs] = static_cast<uint32_t>(n);
-    g->quads = n < 0x7FFFFFFFLL && 8 * n <= 3 * g->A * dirs;
+    g->quads = 2 * n <= 3 * static_cast<int64_t>(g->V) * dirs && n <= g->A * dirs && n <= kQuadMaxAll;
     g->dense = g->quads;
     for (int32_t i = 0; i < g->ngraphs; ++i) {
         // a shortest path has at most V - 1 arcs

@@ -294,11 +294,16 @@ hipError_t launch_join(const JoinArgs &a, int hash_log2, bool generic, bool comp
 // the reversed arcs), padded with arcs of infinite weight; the further quads of
 // vertices of more arcs follow each graph's.  Kept for graphs whose vertices
 // have at most kQuadMaxDeg arcs each way (a target's flags count up to three
-// further quads) and whose quads hold at most half as many records again as
-// there are arcs: beyond that the padding costs a search more than the arc
-// windows do.
+// further quads), and at most half a further quad each on average: those come a
+// step later each and fill the ring.  Joins of balls of 60 to 8 000 vertices and
+// closest pairs, over windows -> over quads: with 0.08 further quads a vertex
+// (3.4 arcs) 0.93 to 1.6 times as fast, with 0.36 (4.1 arcs) 0.88 to 1.6, with 0.57
+// (4.8) 0.94 to 1.6, with 1 (6 arcs) 0.65 to 1.4, with 2 (12) 0.12 to 1.4 (balls of
+// 8 000: 2.6 -> 21.9 ms).  The padding of vertices of few arcs costs less than it
+// saves: 2.5 arcs 0.93 to 1.7, 2.2 arcs 1.0 to 1.9, 2.04 arcs 1.0 to 2.2.
 constexpr int32_t kQuadMaxDeg = 16;
 constexpr int32_t kQuadMaxIds = 1 << 27;   // per graph: quad numbers below the flags
+constexpr int64_t kQuadMaxAll = 1 << 29;   // of all graphs (a launch's threads are fewer than 2^32)
 __host__ __device__ inline int32_t row_quads(int32_t deg) { return deg <= 4 ? 1 : (deg + 3) / 4; }
 hipError_t launch_build_quads(const int32_t *row_ptr, const ArcRec *arcs, uint32_t *further, const int32_t *voff,
                               const uint32_t *qbase, uint32_t *next, uint32_t ngr, uint32_t dirs, uint32_t V,

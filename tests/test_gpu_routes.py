@@ -29,16 +29,54 @@ def batch(rnmod, net, specs, want):
 
 
 def test_degrees(rnmod, orc, rg):
-    # 16 arcs a vertex are searched over quads, 17 over windows
-    for degree, want in ((16, rnmod.RN_ROUTE_QUADS), (17, rnmod.RN_ROUTE_WINDOWS)):
-        n = 300
-        src = np.concatenate([np.arange(n - j) for j in range(1, degree + 1)])
-        dst = np.concatenate([np.arange(j, n) for j in range(1, degree + 1)])
-        g = rg.from_edges(n, src, dst, 1 + (src * 7 + dst) % 50, symmetric=False)
+    # vertices of more than 16 arcs, or of more than half a further quad each on
+    # average, are searched over windows; the others over quads
+    def ring(n, reach):
+        src = np.concatenate([np.arange(n) for _ in reach])
+        dst = np.concatenate([(np.arange(n) + j) % n for j in reach])
+        return rg.from_edges(n, src, dst, 1 + (src * 7 + dst) % 50, symmetric=True)
+
+    def with_hubs(hubs, arcs):
+        g = ring(900, (1, 2))        # 4 arcs a vertex
+        src, dst = np.repeat(np.arange(900), np.diff(g.row_ptr)), g.col
+        h = np.repeat(np.arange(hubs) * 2, arcs)
+        to = (h + 5 + np.tile(np.arange(arcs), hubs)) % 900
+        # (one way, so that the hubs' arcs add to few others' in the reversed graph)
+        return rg.from_edges(900, np.concatenate([src, h]), np.concatenate([dst, to]),
+                             np.concatenate([g.w, 1 + (h + to) % 50]), symmetric=False)
+
+    q, w = rnmod.RN_ROUTE_QUADS, rnmod.RN_ROUTE_WINDOWS
+    for g, want in ((ring(900, (1,)), q), (ring(900, (1, 2)), q), (ring(900, (1, 2, 3)), w),
+                    (with_hubs(1, 12), q), (with_hubs(1, 13), w), (with_hubs(140, 4), q)):
         net = rnmod.RoadNetwork.from_graph(g)
-        R, S = rg.sample_disjoint(n, 20, 60, 1)
-        same(rnmod.pairs_to_numpy(net.dist_join(R, S, 200)), orc.dist_join(g, R, S, 200).pairs)
-        assert net.stats()["route"] & (rnmod.RN_ROUTE_QUADS | rnmod.RN_ROUTE_WINDOWS) == want
+        for nR, nS in ((20, 60), (60, 20)):
+            R, S = rg.sample_disjoint(g.V, nR, nS, 1)
+            same(rnmod.pairs_to_numpy(net.dist_join(R, S, 200)), orc.dist_join(g, R, S, 200).pairs)
+            assert net.stats()["route"] & (q | w) == want, (g.A, want)
+
+
+@pytest.mark.parametrize("parts", [2, 3, 8])
+def test_chains_of_two_arcs(rnmod, orc, rg, parts):
+    # a road graph whose edges are cut into parts: 2.5 to 2.1 arcs a vertex
+    r = rg.road_graph(60, 3)
+    src = np.repeat(np.arange(r.V), np.diff(r.row_ptr))
+    m = src < r.col
+    a, b, w = src[m], r.col[m], np.maximum(1, r.w[m] // parts)
+    mids = r.V + np.arange(len(a) * (parts - 1)).reshape(len(a), parts - 1)
+    chain = np.concatenate([a[:, None], mids, b[:, None]], axis=1)
+    g = rg.from_edges(r.V + mids.size, chain[:, :-1].ravel(), chain[:, 1:].ravel(), np.repeat(w, parts), symmetric=True)
+    net = rnmod.RoadNetwork.from_graph(g)
+    for nR, nS in ((50, 300), (3000, 400), (5000, 5000)):
+        R, S = rg.sample_disjoint(g.V, min(nR, g.V // 3), min(nS, g.V // 3), nR)
+        for theta in (60, 300, 1200):
+            same(rnmod.pairs_to_numpy(net.dist_join(R, S, theta)), orc.dist_join(g, R, S, theta).pairs)
+            assert net.stats()["route"] & rnmod.RN_ROUTE_QUADS
+        same(rnmod.pairs_to_numpy(net.kcp_join(R, S, 200)), orc.kcp_join(g, R, S, 200))
+    for sp, want in (({"theta": 0xFFFFFFFE}, orc.dist_join(g, R[:20], S, 0xFFFFFFFE).pairs),
+                     ({"k": 3000}, orc.kcp_join(g, R[:20], S, 3000))):
+        for _ in range(2):
+            out, off, status = net.join_batch([{"R": R[:20], "S": S, "hash_log2": rnmod.RN_TABLE_GLOBAL, **sp}])
+            same(rnmod.pairs_to_numpy(out[:off[1]]), want)
 
 
 def test_short_form_and_guess(rnmod, orc, rg):
