@@ -138,12 +138,14 @@ void measure_radii(rn_graph *g, int32_t i, uint64_t *dist) {
     std::vector<std::pair<uint64_t, int32_t>> heap;
     std::vector<int32_t> touched;
     for (int smp = 0; smp < kSamples; ++smp) {
-        const int32_t s = vo + static_cast<int32_t>((2 * smp + 1) * static_cast<int64_t>(V) / (2 * kSamples));
+        const bool full = smp % (kSamples / kFull) == kSamples / kFull / 2;
+        // (the few at odd eighths of the numbering, the others at odd sixty-fourths)
+        const int64_t at = full ? 2 * smp : 2 * smp + 1;
+        const int32_t s = vo + static_cast<int32_t>(at * V / (2 * kSamples));
         heap.assign(1, {0, s});
         touched.assign(1, s);
         dist[s] = 1;
         int32_t settled = 0;
-        const bool full = smp % (kSamples / kFull) == kSamples / kFull / 2;
         const int32_t most = full ? largest : kDenseBall;
         const auto later = [](const std::pair<uint64_t, int32_t> &a, const std::pair<uint64_t, int32_t> &b) { return a > b; };
         while (!heap.empty() && settled < most) {
@@ -695,7 +697,7 @@ static rn_status enqueue_searches(rn_graph *g, Workspace &ws, const Prepared &p,
         const uint32_t dn = static_cast<uint32_t>((p.desc_bytes + 3) / 4);
         uint32_t *dd = reinterpret_cast<uint32_t *>(ws.d_desc);
         if (p.stage_one)
-            RN_HIP(launch_stage_one(a, b, static_cast<uint32_t>(p.off_sbits), static_cast<uint32_t>(p.zero_words - p.off_hists),
+            RN_HIP(launch_stage_one(a, b, static_cast<uint32_t>(p.off_sbits), static_cast<uint32_t>(p.off_bins - p.off_hists),
                                     g->d_rank, desc, dn, dd, s),
                    "staging the query");
         else
@@ -883,10 +885,12 @@ rn_status enqueue_call(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *o
 
 // Go on, in the general form, with a call whose short form handed it over (its
 // state read back): the records of its searches are there, what outgrew a table
-// is on the lists, and the bins and the counts of the tail are still zero.
+// is on the lists, and the counts of the tail are still zero.
 rn_status enqueue_handed_over(rn_graph *g, Workspace &ws, const Prepared &p, rn_pair *out, int64_t cap, hipStream_t s,
                               bool timed) {
     const CallCtl &c = *reinterpret_cast<const CallCtl *>(ws.h_state);
+    if (p.nbins)   // (the one-block staging leaves them)
+        RN_HIP(launch_fill_u32(call_buffers(ws, p).bins, 2ull * bin_stride(p.nbins), 0u, s), "clearing the bins");
     return enqueue_rest(g, ws, p, out, cap, s, timed, false,
                         c.nlist[0] ? 0 : (c.nlist[1] ? 1 : (c.nlist[2] ? 2 : 3)));
 }
