@@ -451,6 +451,7 @@ typedef struct rn_stats {
 #define RN_ROUTE_GUESS_MISSED 32 /* some such query had fewer than k pairs within it */
 #define RN_ROUTE_DENSE_FULL 64   /* a whole-graph search over quads outgrew its ring */
 #define RN_ROUTE_RESORTED 128    /* the radix sort took over from another sort */
+#define RN_ROUTE_BINS 256        /* the pairs were sorted through bins of (query, distance) */
 
 /* Profiling flags for rn_set_profiling. */
 #define RN_PROFILE_TIMES 1  /* HIP-event timing of each stage (times are 0 otherwise) */

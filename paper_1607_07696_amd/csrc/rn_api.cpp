@@ -434,8 +434,8 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
     p.vb = std::max<uint32_t>(1u, bitlen(static_cast<uint64_t>(std::max(g->Vmax - 1, 0))));
     p.max_passes = std::max<uint32_t>(1u, (p.qb + std::max<uint32_t>(bitlen(dmax), 1u) + 2u * p.vb + 7u) / 8u);
     // other calls with k closest pairs: bins of equal width up to each query's
-    // final bound, as many as kMixedBins allows.  (32 mixed queries, 10 digit
-    // passes: the radix sort's 30 launches took 115 us.)
+    // final bound, as many as kMixedBins allows, where few records share one.
+    // (32 mixed queries, 10 digit passes: the radix sort's 30 launches took 115 us.)
     // A call in the short form keeps some for a hand-over: then it has far more
     // records than expected.
     p.mixed_bins = false;
@@ -446,9 +446,10 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
             // a power of two for each query's expected records, 8 a bin where
             // that fits (equal shares left some bins hundreds long: 297 us to
             // rank 825 000 pairs of 128 queries)
-            p.mixed_bins = true;
+            double total = 0.0, compares = 0.0;
             for (double per = 8.0;; per *= 2.0) {
                 uint64_t nb = 0;
+                total = compares = 0.0;
                 for (int32_t i = 0; i < nq; ++i) {
                     const rn_query &x = q[i];
                     const double V = static_cast<double>(g->voff[x.graph + 1] - g->voff[x.graph]);
@@ -459,11 +460,26 @@ rn_status prepare(const rn_graph *g, const rn_query *q, int32_t nq, Prepared &p,
                     while (n < 8192u && n * per < expect) n *= 2;
                     p.binbase[i] = static_cast<uint32_t>(nb);
                     nb += n;
+                    // the bins in use, as rec_bin finds them: up to the ball in
+                    // which so many of the pairs lie (theta may lie far beyond)
+                    const double ball = std::sqrt(expect * V / (2.5 * std::max(1.0, pairs))) * std::max(1.0, g->wmean[x.graph]);
+                    const uint64_t reach = static_cast<uint64_t>(std::min<double>(ball, x.theta));
+                    const uint32_t bits = bitlen(x.k > 0 ? reach : x.theta), have = bitlen(n) - 1u;
+                    total += expect;
+                    compares += expect * expect / static_cast<double>((reach >> (bits > have ? bits - have : 0u)) + 1u);
                 }
                 p.binbase[nq] = static_cast<uint32_t>(nb);
                 if (nb <= kMixedBins) break;
             }
-            p.nbins = p.binbase[nq];
+            // Ranking a bin grows with its square, and the selection's adds to
+            // one bin's count wait for each other, so long bins go to the radix
+            // sort: where kMixedBinMean records share an average record's bin.
+            // (Selecting and sorting, radix against bins: 85 300 pairs, 102 a
+            // bin expected, 94 us and 68; 207 000, 115: 129 and 100; 357 000,
+            // 205: 138 and 166; 863 000, 230: 249 and 316; 2 230 000, 1280: 399
+            // and 2225; k = 400 000, 124: 295 and 254, 495: 288 and 472.)
+            p.mixed_bins = compares <= kMixedBinMean * total;
+            p.nbins = p.mixed_bins ? p.binbase[nq] : 0u;
         }
     }
     // call block: words, every region 64-word (256-byte) aligned
@@ -1013,6 +1029,7 @@ int32_t route_of(const Workspace &ws, const Prepared &p) {
     if (p.tail_one && handed_over(c)) r |= RN_ROUTE_SHORT_LEFT;
     if (c.unmet & kUnmetGuess) r |= RN_ROUTE_GUESS_MISSED;
     if (c.nfull) r |= RN_ROUTE_DENSE_FULL;
+    if (p.nbins && !(p.tail_one && !handed_over(c))) r |= RN_ROUTE_BINS;
     if (c.resort) r |= RN_ROUTE_RESORTED;
     return r;
 }

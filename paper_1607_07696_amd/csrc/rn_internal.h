@@ -368,6 +368,7 @@ constexpr int32_t kMaxQueries = 65536;
 // recs[1]) with the radix sort instead (launch_sort_out, selected = 1).
 constexpr uint32_t kMaxBins = 65536;
 constexpr uint32_t kMixedBins = 32768;
+constexpr double kMixedBinMean = 128.0;
 constexpr uint32_t kBucketRankMax = 4096;
 __host__ __device__ inline uint32_t bin_stride(uint32_t nbins) { return (nbins + 3u) / 4u * 4u; }
 inline size_t bucket_words(uint32_t nbins) { return 4 * static_cast<size_t>(bin_stride(nbins)) + 1; }

@@ -17,7 +17,7 @@ LIB_PATH = os.path.join(HERE, "librn.so")
 RN_OK, RN_ERR_ARG, RN_ERR_NOMEM, RN_ERR_CAPACITY, RN_ERR_DEVICE, RN_ERR_BUSY = 0, -1, -2, -3, -4, -5
 RN_PROFILE_TIMES, RN_PROFILE_WORK = 1, 2
 (RN_ROUTE_QUADS, RN_ROUTE_WINDOWS, RN_ROUTE_SHORT, RN_ROUTE_SHORT_LEFT, RN_ROUTE_GUESS, RN_ROUTE_GUESS_MISSED,
- RN_ROUTE_DENSE_FULL, RN_ROUTE_RESORTED) = (1 << i for i in range(8))
+ RN_ROUTE_DENSE_FULL, RN_ROUTE_RESORTED, RN_ROUTE_BINS) = (1 << i for i in range(9))
 PAIR_DTYPE = np.dtype([("u", "<i4"), ("v", "<i4"), ("dist", "<u4")])
 
 # Every symbol include/rn.h declares.

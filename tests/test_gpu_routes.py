@@ -146,7 +146,7 @@ def test_short_form_hands_over(rnmod, orc, rg):
         for _ in range(2):
             same(rnmod.pairs_to_numpy(net.dist_join(R, S, theta)), want)
             st = net.stats()
-            assert st["route"] & ~rnmod.RN_ROUTE_RESORTED == left, (nR, nS, theta)
+            assert st["route"] & ~(rnmod.RN_ROUTE_RESORTED | rnmod.RN_ROUTE_BINS) == left, (nR, nS, theta)
             assert (st["pairs"] > 4096) == (nR > 30) and (st["retried"] > 0) == (theta > 5), st
         # (from the first run of a plan on, it is captured in the general form)
         q, keep = net.make_queries([{"R": R, "S": S, "theta": theta}])
@@ -212,7 +212,7 @@ def test_mixed_bins_too_full(rnmod, orc, rg, kcp_first):
     # several thousand pairs at one distance: beyond what the ranking takes
     g = flat_grid(rg)
     net = rnmod.RoadNetwork.from_graph(g)
-    R, S = rg.sample_disjoint(g.V, 3000, 7000, 1)
+    R, S = rg.sample_disjoint(g.V, 3000, 5000, 1)
     R2, S2 = rg.sample_disjoint(g.V, 400, 500, 2)
     specs, want = [{"R": R, "S": S, "theta": 300}], [orc.dist_join(g, R, S, 300).pairs]
     assert np.unique(want[0]["dist"], return_counts=True)[1].max() > 4096
@@ -221,6 +221,35 @@ def test_mixed_bins_too_full(rnmod, orc, rg, kcp_first):
     want.insert(0 if kcp_first else 1, orc.kcp_join(g, R2, S2, 2000))
     for _ in range(2):
         assert batch(rnmod, net, specs, want) & rnmod.RN_ROUTE_RESORTED
+
+
+@pytest.mark.parametrize("nR,nS,theta,bins", [(300, 500, 2000, True), (3000, 3000, 300, True), (3000, 3000, 700, True),
+                                              (5000, 5000, 700, False), (5000, 5000, 2000, False),
+                                              (200, 300, 0xFFFFFFFE, False)])
+@pytest.mark.parametrize("nq", [1, 6])
+def test_long_bins_are_not_made(rnmod, orc, rg, nR, nS, theta, bins, nq):
+    # a theta-join beside closest-pairs queries: binned where few pairs share one
+    g = rg.road_graph(120, 3)
+    net = rnmod.RoadNetwork.from_graph(g)
+    R, S = rg.sample_disjoint(g.V, nR, nS, 1)
+    specs, want = [{"R": R, "S": S, "theta": theta}], [orc.dist_join(g, R, S, theta).pairs]
+    for i in range(nq):
+        R2, S2 = rg.sample_disjoint(g.V, 400, 500, 2 + i)
+        specs.insert(i % 2, {"R": R2, "S": S2, "k": 1500})
+        want.insert(i % 2, orc.kcp_join(g, R2, S2, 1500))
+    for _ in range(2):
+        route = batch(rnmod, net, specs, want)
+        assert bool(route & rnmod.RN_ROUTE_BINS) == bins and not route & rnmod.RN_ROUTE_RESORTED
+
+
+@pytest.mark.parametrize("nR,nS,k,bins", [(1500, 1500, 3000, True), (4500, 9000, 30000, False), (400, 500, 100000, True)])
+def test_long_bins_of_closest_pairs_are_not_made(rnmod, orc, rg, nR, nS, k, bins):
+    g = rg.road_graph(120, 3)
+    net = rnmod.RoadNetwork.from_graph(g)
+    R, S = rg.sample_disjoint(g.V, nR, nS, 1)
+    for _ in range(2):
+        same(rnmod.pairs_to_numpy(net.kcp_join(R, S, k)), orc.kcp_join(g, R, S, k))
+        assert bool(net.stats()["route"] & rnmod.RN_ROUTE_BINS) == bins
 
 
 def test_theta_bins_too_full(rnmod, orc, rg):

@@ -15,6 +15,6 @@ def test_stats_size():
 
 def test_route_bits():
     bits = re.findall(r"#define\s+(RN_ROUTE_\w+)\s+(\d+)", open(HEADER).read())
-    assert len(bits) == 8
+    assert len(bits) == 9
     for name, value in bits:
         assert getattr(rn, name) == int(value), name
