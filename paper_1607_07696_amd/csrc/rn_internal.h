@@ -42,7 +42,7 @@ constexpr uint32_t kDistBins = 512;   // 464 used
 // Histogram region of one k-closest-pairs query (words): the weights of direct
 // R-S arcs | the distances of emitted pairs | for each search tier, the first
 // tentative distance of every (source, S member) pair its searches discovered |
-// the four discovery counts.  Each histogram counts a pair at most once, and
+// the five discovery counts.  Each histogram counts a pair at most once, and
 // every value counted is the length of a real path, so each one alone bounds
 // the k-th smallest distance from above once it holds k counts.
 constexpr uint32_t kHistSeed = 0;
@@ -255,7 +255,8 @@ hipError_t launch_stage_one(const JoinArgs &a, const CallBuffers &b, uint32_t he
 // Tail of a one-query call with few records in one block (instead of
 // launch_select, launch_layout and a sort): keeps the records within the bound,
 // sorts them in LDS, lays out and writes the output, and publishes the call
-// state.  More than kSmallSort kept: ctl->unmet (kUnmetTail).
+// state.  More than kSmallSort kept: kUnmetTail in the published unmet; searches on a
+// re-run list: nothing but the state.
 hipError_t launch_tail_one(const CallBuffers &b, uint32_t vb, rn_pair *out, unsigned long long user_cap,
                            const uint32_t *state, uint32_t *state_map, uint32_t state_words, hipStream_t s);
 
@@ -309,18 +310,20 @@ hipError_t launch_build_quads(const int32_t *row_ptr, const ArcRec *arcs, uint32
                               const uint32_t *qbase, uint32_t *next, uint32_t ngr, uint32_t dirs, uint32_t V,
                               uint32_t nquads, uint2 *quads, hipStream_t s);
 int join_tier_supported(int hash_log2);
-// The global-memory tier: one block per source, nslots slots of
-// global_slot_words(Vmax) words in the layout above.
-// The same over arc quads, for graphs whose path lengths fit 31 bits, and calls of
-// at most kDenseSources searches; searches whose pending set outgrows its ring are
-// queued on a.ovf.  Its step waits less but asks for more of the memory system
-// (an atomic per entry taken as well), which many searches side by side share:
-// whole or large searches on road graphs of a million vertices, general -> over
-// quads: 60 searches 3.37 -> 2.89 ms, 120 8.10 -> 8.55 ms, 180 5.06 -> 5.93 ms; 23 on
-// 160 000 vertices 2.81 -> 2.19 ms.
+// The global-memory tier over arc quads, for graphs whose path lengths fit 31 bits
+// and calls of at most kDenseSources searches; searches whose pending set outgrows
+// its ring are queued on a.ovf.  Its step waits less but asks for more of the memory
+// system (an atomic per entry taken as well), which searches side by side share: road
+// graphs of 130 x 130 to 1024 x 1024, whole, partial and k-closest-pairs searches,
+// time of the general tier over its: 64 side by side 1.08 to 1.59, 80 1.01 to 1.6,
+// 96 0.93 to 1.53, 128 0.75 to 1.43, 256 0.58 to 1.16 (64 whole searches of 1024 x
+// 1024: 19.0 -> 15.0 ms).  What counts is how many run at once, which is at most the
+// slots; a call of more searches has slots for as many as ran before on the handle.
 constexpr uint64_t kDenseSources = 64;
 hipError_t launch_join_dense(const JoinArgs &a, uint32_t *slots, uint32_t nslots, int32_t Vmax, uint32_t max_sources,
                              hipStream_t s);
+// The general global-memory tier: one block per source, nslots slots of
+// global_slot_words(Vmax) words in the layout above.
 hipError_t launch_join_global(const JoinArgs &a, uint32_t *slots, uint32_t nslots, int32_t Vmax,
                               uint32_t max_sources, hipStream_t s);
 
@@ -353,8 +356,9 @@ constexpr int32_t kMaxQueries = 65536;
 
 // Bucket sort.  Calls with k-closest-pairs queries (of more candidates than the
 // small sort takes) use up to kMixedBins bins, a power of two of equal width for
-// each query from 0 to its final bound; the selection counts the records per bin
-// as it keeps them.  Calls of theta-joins only whose bins (query, dist), theta+1
+// each query from 0 to its final bound, where no more than kMixedBinMean records
+// are expected in an average record's bin; the selection counts the records per
+// bin as it keeps them.  Calls of theta-joins only whose bins (query, dist), theta+1
 // per query, number at most kMaxBins: the relaxation kernels count the records
 // per bin as they store them (the count's old value is the record's place in
 // its bin); the layout launch scans the counts; the scatter copies each record

@@ -2462,8 +2462,8 @@ __global__ __launch_bounds__(1024) void k_join_global(JoinArgs a, uint32_t *slot
 // goes on to the atomic, costs as much as it saves: 2 392 us against 2 116.)  The
 // pairs come from the query's list of S where that is shorter than the list of
 // vertices reached.  23 whole searches of the 400 x 400 road graph: 2 778 us by
-// k_join_global, 2 116 here (slack 3: 2 224; 8 waves: 2 619); 60 of the 1024 x 1024
-// graph 9.40 -> 8.53 ms.  A search whose pending set outgrows the ring goes on to
+// k_join_global, 2 116 here (slack 3: 2 224; 8 waves: 2 619); 64 of the 1024 x 1024
+// graph 19.0 -> 15.0 ms.  A search whose pending set outgrows the ring goes on to
 // k_join_global, whose lists have room for any.
 constexpr uint32_t kDT = 1024;
 constexpr uint32_t kDW = kDT / 64;
@@ -3848,7 +3848,9 @@ __global__ __launch_bounds__(1024) void k_sort_small(CallBuffers b, uint32_t qb,
 // the bound become (dist, u, v) keys in LDS, are placed there and written out; the
 // call's counts come from the same block, which publishes them.  One launch
 // where the bucket sort takes three and k closest pairs two, at 3 to 7 us each
-// and as much again between them.
+// and as much again between them.  Where searches wait on a re-run list, or more
+// records than fit here, it only publishes that: the host enqueues the general
+// form from there on.
 __global__ __launch_bounds__(1024) void k_tail_one(CallBuffers b, uint32_t vb, rn_pair *out, unsigned long long user_cap,
                                                    const uint32_t *state, uint32_t *state_map, uint32_t state_words) {
     __shared__ SmallLds L;
